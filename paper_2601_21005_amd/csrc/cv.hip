@@ -242,9 +242,24 @@ void features(sgw_ctx *ctx, const float *phi, int K, int64_t ld, uint64_t seed, 
 }
 
 // ---------------------------------------------------------------- MLP GEMM
-// C(m, n) = sum_k A(m, k) B(k, n) for strided FP32 operands, rounded to BF16
-// in LDS; 64 x 64 output tile per workgroup, wave w owns rows 16 w .. 16 w + 15.
+// C(m, n) = sum_k A(m, k) B(k, n) for strided FP32 operands (one stride of
+// each operand is 1), rounded to BF16 in LDS; a BM x BN output tile per
+// workgroup, K in chunks of BK, the next chunk's loads in flight behind the
+// current chunk's products.  The network's matrices are small (256 x 256
+// weights, a few hundred to a few thousand samples), so what bounds these
+// products is the number of workgroups and the round trips to memory one
+// after another, not MFMA: 64 x 32 tiles and chunks of 64 for short K, 32 x 32
+// tiles with 1024 threads and chunks of 256 for long K (the weight gradients'
+// K is the sample count: both products of 1536 samples in one launch of 21
+// us, 38 us with 256 threads and chunks of 128, 123 us in two launches of
+// 64 x 64 tiles and chunks of 32).  Each output keeps ONE accumulator over
+// ascending K groups of 32, so the tile never changes a result: Adam turns
+// the last bits of a nearly vanishing gradient into whole steps, which is why
+// the products are not split over the samples.  A training step of 1536
+// samples took 1400 us in 17 launches, now 70 us in six.
 enum Epi { EPI_STORE = 0, EPI_TANH_BIAS = 1, EPI_DTANH = 2 };
+// the standardization (b - mean) * inv_std of B, by its K or its N index
+enum BStd { BSTD_NONE = 0, BSTD_K = 1, BSTD_N = 2 };
 
 struct GemmArgs {
   const float *a; int64_t sam, sak;
@@ -252,117 +267,370 @@ struct GemmArgs {
   float *c; int64_t scm, scn;
   const float *bias;        // EPI_TANH_BIAS: [M]
   const float *aux;         // EPI_DTANH: activation at the strides of C
+  const float *mean, *inv_std;   // BSTD_K, BSTD_N
   int M, N, K;
+  int avec, bvec, cvec;     // 16-byte accesses allowed (set by finish_args)
 };
 
-template <int EPI>
-__global__ __launch_bounds__(NT) void k_gemm(GemmArgs g) {
-  constexpr int P = 40;                       // LDS pitch (bf16): 80 B, conflict-free 16 B reads
-  __shared__ __align__(16) uint16_t As[64 * P], Bs[64 * P];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, col = lane & 15;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  f32x4 acc[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const bool ak = g.sak == 1, bk = g.sbk == 1;
-  for (int k0 = 0; k0 < g.K; k0 += 32) {
-    float av[8], bv[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int idx = tid + NT * i;
-      const int am = ak ? idx / 32 : idx % 64, akk = ak ? idx % 32 : idx / 64;
-      const int bn = bk ? idx / 32 : idx % 64, bkk = bk ? idx % 32 : idx / 64;
-      av[i] = (m0 + am < g.M && k0 + akk < g.K) ? g.a[(m0 + am) * g.sam + (k0 + akk) * g.sak] : 0.f;
-      bv[i] = (n0 + bn < g.N && k0 + bkk < g.K) ? g.b[(k0 + bkk) * g.sbk + (n0 + bn) * g.sbn] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int idx = tid + NT * i;
-      const int am = ak ? idx / 32 : idx % 64, akk = ak ? idx % 32 : idx / 64;
-      const int bn = bk ? idx / 32 : idx % 64, bkk = bk ? idx % 32 : idx / 64;
-      As[am * P + akk] = (uint16_t)bf16r(av[i]);
-      Bs[bn * P + bkk] = (uint16_t)bf16r(bv[i]);
-    }
-    __syncthreads();
-    const u32x4 a = *reinterpret_cast<const u32x4 *>(As + (16 * w + col) * P + 8 * q);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const u32x4 b = *reinterpret_cast<const u32x4 *>(Bs + (16 * t + col) * P + 8 * q);
-      mma(acc[t], a, b);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = m0 + 16 * w + 4 * q + r, n = n0 + 16 * t + col;
-      if (m >= g.M || n >= g.N) continue;
-      const int64_t o = m * g.scm + n * g.scn;
-      float v = acc[t][r];
-      if (EPI == EPI_TANH_BIAS) v = tanhf(v + g.bias[m]);
-      if (EPI == EPI_DTANH) {
-        const float h = g.aux[o];
-        v *= 1.f - h * h;
-      }
-      g.c[o] = v;
-    }
+template <int BM_, int BN_, int BK_, int THREADS_, int NBUF_> struct Tile {
+  static constexpr int BM = BM_, BN = BN_, BK = BK_, THREADS = THREADS_, NBUF = NBUF_;
+  static constexpr int P = BK + 8;            // LDS pitch (bf16): 16 B reads spread over the banks
+  static constexpr int WM = BM / 16 < 4 ? BM / 16 : 4;   // of the four multiplying waves, along M
+  static constexpr int NT_W = BN / 16 / (4 / WM);        // 16 x 16 tiles of a wave
+  static_assert(WM * 16 == BM && NT_W * 16 * (4 / WM) == BN, "tile does not split over four waves");
+  struct Lds {
+    __align__(16) uint16_t a[NBUF][BM * P], b[NBUF][BN * P];
+  };
+  static int count(int M, int N) { return ((N + BN - 1) / BN) * ((M + BM - 1) / BM); }
+};
+using WideTile = Tile<64, 32, 64, 256, 2>;
+using DeepTile = Tile<32, 32, 256, 1024, 1>;
+constexpr int DEEP = DeepTile::THREADS;
+
+inline GemmArgs finish_args(GemmArgs g) {
+  auto ok = [](const void *p, int64_t s0, int64_t s1) {
+    return ((uintptr_t)p & 15) == 0 && (s0 == 1 ? s1 : s0) % 4 == 0;
+  };
+  g.avec = ok(g.a, g.sam, g.sak);
+  g.bvec = ok(g.b, g.sbn, g.sbk);
+  g.cvec = g.scm == 1 && ok(g.c, g.scm, g.scn) && (!g.aux || ((uintptr_t)g.aux & 15) == 0);
+  return g;
 }
 
-template <int EPI> void gemm(hipStream_t st, const GemmArgs &g) {
-  if (g.M <= 0 || g.N <= 0) return;
-  const dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);
-  SGW_REQUIRE(grid.y <= 65535, SGW_EUNSUPPORTED, "GEMM: M too large");
-  hipLaunchKernelGGL(k_gemm<EPI>, grid, dim3(NT), 0, st, g);
+// A chunk of ROWS rows x BK K values as 4-value groups along the contiguous
+// axis, in registers: along the rows, groups 2 i and 2 i + 1 are the K values 2 kp, 2 kp + 1 of
+// one row group, so that a pair of K neighbours is written to LDS at once.
+// Values outside the matrix are zero.
+template <int ROWS, int BK, int THREADS> struct Chunk {
+  static constexpr int NG = ROWS * BK / 4 / THREADS, GP = BK + 8;
+  static_assert(NG % 2 == 0, "groups come in pairs");
+  float v[NG][4];
+  __device__ static void place(bool kc, int i, int tid, int &row, int &k) {
+    if (kc) {
+      const int idx = tid + THREADS * i;
+      row = idx / (BK / 4);
+      k = 4 * (idx % (BK / 4));
+    } else {
+      const int idx = tid + THREADS * (i / 2);
+      row = 4 * (idx % (ROWS / 4));
+      k = 2 * (idx / (ROWS / 4)) + (i & 1);
+    }
+  }
+  __device__ void load(const float *p, int64_t sr, int64_t sk, bool vec, int r0, int rows, int k0,
+                       int kend, int tid) {
+    const bool kc = sk == 1;
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+      int row, k;
+      place(kc, i, tid, row, k);
+      const int r = r0 + row, kk = k0 + k;
+      const float *q = p + r * sr + kk * sk;
+      const bool in = kc ? r < rows && kk + 4 <= kend : kk < kend && r + 4 <= rows;
+      if (vec && in) {
+        const float4 f = *reinterpret_cast<const float4 *>(q);
+        v[i][0] = f.x; v[i][1] = f.y; v[i][2] = f.z; v[i][3] = f.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v[i][e] = (kc ? r < rows && kk + e < kend : kk < kend && r + e < rows)
+                        ? q[kc ? (int64_t)e : e * sr] : 0.f;
+      }
+    }
+  }
+  template <int STD>
+  __device__ void stage(uint16_t *s, bool kc, int tid, int r0, int rows, int k0, int kend,
+                        const float *mean, const float *inv_std) {
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+      int row, k;
+      place(kc, i, tid, row, k);
+      if constexpr (STD != BSTD_NONE) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = r0 + row + (kc ? 0 : e), kk = k0 + k + (kc ? e : 0);
+          const int j = STD == BSTD_K ? kk : r;
+          if (r < rows && kk < kend) v[i][e] = (v[i][e] - mean[j]) * inv_std[j];
+        }
+      }
+      if (kc) {
+        const uint2 w = make_uint2(bf16r(v[i][0]) | bf16r(v[i][1]) << 16,
+                                   bf16r(v[i][2]) | bf16r(v[i][3]) << 16);
+        *reinterpret_cast<uint2 *>(s + row * GP + k) = w;
+      } else if (i & 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          *reinterpret_cast<uint32_t *>(s + (row + e) * GP + k - 1) =
+              bf16r(v[i - 1][e]) | bf16r(v[i][e]) << 16;
+      }
+    }
+  }
+};
+
+template <class T, int EPI, int STD>
+__device__ __forceinline__ void gemm_tile(const GemmArgs &g, int nb, int mb, typename T::Lds &l) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, col = lane & 15;
+  const int m0 = mb * T::BM, n0 = nb * T::BN;
+  const int wm = 16 * (w % T::WM), wn = 16 * T::NT_W * (w / T::WM);
+  const bool ak = g.sak == 1, bk = g.sbk == 1;
+  f32x4 acc[T::NT_W];
+#pragma unroll
+  for (int t = 0; t < T::NT_W; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Chunk<T::BM, T::BK, T::THREADS> ca;
+  Chunk<T::BN, T::BK, T::THREADS> cb;
+  auto load = [&](int k0) {
+    ca.load(g.a, g.sam, g.sak, g.avec, m0, g.M, k0, g.K, tid);
+    cb.load(g.b, g.sbn, g.sbk, g.bvec, n0, g.N, k0, g.K, tid);
+  };
+  load(0);
+  int buf = 0;
+  for (int k0 = 0; k0 < g.K; k0 += T::BK) {
+    ca.template stage<BSTD_NONE>(l.a[buf], ak, tid, m0, g.M, k0, g.K, nullptr, nullptr);
+    cb.template stage<STD>(l.b[buf], bk, tid, n0, g.N, k0, g.K, g.mean, g.inv_std);
+    __syncthreads();
+    if (k0 + T::BK < g.K) load(k0 + T::BK);
+    if (T::THREADS == 256 || w < 4) {
+#pragma unroll
+      for (int h = 0; h < T::BK / 32; ++h) {
+        const u32x4 a = *reinterpret_cast<const u32x4 *>(l.a[buf] + (wm + col) * T::P + 32 * h + 8 * q);
+#pragma unroll
+        for (int t = 0; t < T::NT_W; ++t) {
+          const u32x4 b = *reinterpret_cast<const u32x4 *>(l.b[buf] + (wn + 16 * t + col) * T::P + 32 * h + 8 * q);
+          mma(acc[t], a, b);
+        }
+      }
+    }
+    if constexpr (T::NBUF == 2) buf ^= 1;   // the other buffer's readers all passed this chunk's barrier
+    else if (k0 + T::BK < g.K) __syncthreads();
+  }
+  if (T::THREADS > 256 && w >= 4) return;
+  const int m = m0 + wm + 4 * q;
+  float *c = g.c;
+#pragma unroll
+  for (int t = 0; t < T::NT_W; ++t) {
+    const int n = n0 + wn + 16 * t + col;
+    if (n >= g.N || m >= g.M) continue;
+    const int64_t o = m * g.scm + n * g.scn;
+    const bool vec = g.cvec && m + 4 <= g.M;
+    float v[4], x[4];
+    if (EPI == EPI_DTANH) {
+      if (vec) {
+        const float4 f = *reinterpret_cast<const float4 *>(g.aux + o);
+        x[0] = f.x; x[1] = f.y; x[2] = f.z; x[3] = f.w;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = m + r < g.M ? g.aux[o + r * g.scm] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      v[r] = acc[t][r];
+      if (EPI == EPI_TANH_BIAS) v[r] = tanhf(v[r] + (m + r < g.M ? g.bias[m + r] : 0.f));
+      if (EPI == EPI_DTANH) v[r] *= 1.f - x[r] * x[r];
+    }
+    if (vec) {
+      *reinterpret_cast<float4 *>(c + o) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (m + r < g.M) c[o + r * g.scm] = v[r];
+    }
+  }
+}
+
+template <class T, int EPI, int STD>
+__global__ __launch_bounds__(T::THREADS) void k_gemm(GemmArgs g) {
+  __shared__ typename T::Lds l;
+  gemm_tile<T, EPI, STD>(g, blockIdx.x, blockIdx.y, l);
+}
+
+template <class T, int EPI, int STD> void launch_gemm(hipStream_t st, const GemmArgs &g) {
+  hipLaunchKernelGGL((k_gemm<T, EPI, STD>), dim3((g.N + T::BN - 1) / T::BN, (g.M + T::BM - 1) / T::BM),
+                     dim3(T::THREADS), 0, st, g);
   SGW_HIP(hipGetLastError());
 }
 
-// ---------------------------------------------------------------- small kernels
-// xh[s][k] = (x[s][k] - mean[k]) * inv_std[k]
-__global__ void k_standardize(const float *x, const float *mean, const float *inv_std, int din,
-                              int64_t n, float *xh) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * din) return;
-  const int k = (int)(i % din);
-  xh[i] = (x[i] - mean[k]) * inv_std[k];
+template <int EPI, int STD> void gemm(hipStream_t st, const GemmArgs &a) {
+  if (a.M <= 0 || a.N <= 0) return;
+  const GemmArgs g = finish_args(a);
+  // deep tiles where their chunks of 256 are filled and the launch is at most
+  // four workgroups per CU (256 x 256 layer, 1536 samples: 7.8 against 9.4 us;
+  // 64 inputs: 14.2 against 7.8, so wide; beyond, wide tiles read less)
+  if (g.K > 128 && DeepTile::count(g.M, g.N) <= 1024) launch_gemm<DeepTile, EPI, STD>(st, g);
+  else launch_gemm<WideTile, EPI, STD>(st, g);
 }
 
-// g[s] = w3 . a2[s] + b3  (FP32, fixed order)
-__global__ void k_output(const float *a2, const float *w3, const float *b3, int h2, int64_t n,
-                         float *g) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
+// ---------------------------------------------------------------- output layer
+// g = w3 . a2 + b3 (FP32, in order of j) and, in training, the residual's
+// dg = 2 (g - y) / n, its square (FP64) and the layer's d2[j] = dg w3[j]
+// (1 - a2[j]^2).  16 samples per workgroup: their a2 rows are read coalesced
+// into LDS, one thread per sample adds its row (a chain of h2 FMAs, 1 us at
+// 256; one thread per sample straight from memory took 33 us at 1536 samples).
+constexpr int OUT_S = 16, OUT_J = 256;
+
+template <bool TRAIN>
+__global__ __launch_bounds__(NT) void k_output(const float *a2, const float *w3, const float *b3,
+                                               int h2, int64_t n, float *g, const float *y,
+                                               float *dg, double *e2, float *d2) {
+  __shared__ float sh[OUT_S * (OUT_J + 1)], sw[OUT_J], sd[OUT_S];
+  const int64_t s0 = (int64_t)blockIdx.x * OUT_S;
+  const int tid = threadIdx.x, ns = (int)min((int64_t)OUT_S, n - s0);
   float acc = 0.f;
-  for (int j = 0; j < h2; ++j) acc += w3[j] * a2[s * h2 + j];
-  g[s] = acc + b3[0];
+  for (int j0 = 0; j0 < h2; j0 += OUT_J) {
+    const int nj = min(OUT_J, h2 - j0);
+    if (tid < nj) {
+      sw[tid] = w3[j0 + tid];
+#pragma unroll
+      for (int i = 0; i < OUT_S; ++i)
+        if (i < ns) sh[i * (OUT_J + 1) + tid] = a2[(s0 + i) * h2 + j0 + tid];
+    }
+    __syncthreads();
+    if (tid < ns) {
+#pragma unroll 16
+      for (int j = 0; j < nj; ++j) acc += sw[j] * sh[tid * (OUT_J + 1) + j];
+    }
+    __syncthreads();
+  }
+  if (tid < ns) {
+    const float gs = acc + b3[0];
+    g[s0 + tid] = gs;
+    if constexpr (TRAIN) {
+      const double r = (double)gs - (double)y[s0 + tid];
+      sd[tid] = dg[s0 + tid] = (float)(2.0 * r / (double)n);
+      e2[s0 + tid] = r * r;
+    }
+  }
+  if constexpr (TRAIN) {
+    __syncthreads();
+    for (int j = tid; j < h2; j += NT) {
+      const float w = w3[j];
+#pragma unroll
+      for (int i = 0; i < OUT_S; ++i) {
+        if (i < ns) {
+          const float h = a2[(s0 + i) * h2 + j];
+          d2[(s0 + i) * h2 + j] = sd[i] * w * (1.f - h * h);
+        }
+      }
+    }
+  }
 }
 
-// dg[s] = 2 (g[s] - y[s]) / n;  e2[s] = (g[s] - y[s])^2 (FP64)
-__global__ void k_residual(const float *g, const float *y, int64_t n, float *dg, double *e2) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  const double r = (double)g[s] - (double)y[s];
-  dg[s] = (float)(2.0 * r / (double)n);
-  e2[s] = r * r;
+// ---------------------------------------------------------------- weight gradients
+// Everything that is summed over samples, in one launch: dW2 = d2^T a1 and
+// dW1 = d1^T xh, and the column sums of d2, a2 dg and d1 and the sums of dg
+// and of the squared residuals (FP64) over ranges of samples, which k_grad
+// adds in order.  (One thread per column over all samples took 352 us per
+// sum at 1536 samples, the two products on 16 and 4 workgroups 60 us each.)
+struct WGradArgs {
+  GemmArgs w2, w1;
+  int tiles2, tiles1, S;           // output tiles of the two products, sample ranges of the sums
+  const float *d2, *d1, *a2, *dg;
+  const double *e2;
+  int h1, h2, chunk;
+  int64_t n;
+  double *cols;                    // [S][2 h2 + h1 + 2]: d2, a2 dg, d1, dg, e2
+};
+
+__global__ __launch_bounds__(DEEP) void k_wgrads(WGradArgs a) {
+  __shared__ DeepTile::Lds l;
+  int b = blockIdx.x;
+  if (b < a.tiles2) {
+    const int nbx = (a.w2.N + DeepTile::BN - 1) / DeepTile::BN;
+    gemm_tile<DeepTile, EPI_STORE, BSTD_NONE>(a.w2, b % nbx, b / nbx, l);
+    return;
+  }
+  b -= a.tiles2;
+  if (b < a.tiles1) {
+    const int nbx = (a.w1.N + DeepTile::BN - 1) / DeepTile::BN;
+    gemm_tile<DeepTile, EPI_STORE, BSTD_N>(a.w1, b % nbx, b / nbx, l);
+    return;
+  }
+  b -= a.tiles1;
+  // sums: four units of 256 threads per workgroup, each one range of samples
+  // and one block of columns
+  const int c2 = (a.h2 + NT - 1) / NT, c1 = (a.h1 + NT - 1) / NT, per = c2 + c1 + 1;
+  const int unit = b * (DEEP / NT) + threadIdx.x / NT, tid = threadIdx.x % NT;
+  const int z = unit / per, kind = unit % per;
+  if (z >= a.S) return;
+  const int64_t s0 = (int64_t)z * a.chunk, s1 = min(a.n, s0 + a.chunk);
+  double *out = a.cols + (int64_t)z * (2 * a.h2 + a.h1 + 2);
+  if (kind < c2) {
+    const int j = kind * NT + tid;
+    if (j >= a.h2) return;
+    double b2 = 0.0, w3 = 0.0;
+#pragma unroll 8
+    for (int64_t s = s0; s < s1; ++s) {
+      b2 += (double)a.d2[s * a.h2 + j];
+      w3 += (double)a.a2[s * a.h2 + j] * (double)a.dg[s];
+    }
+    out[j] = b2;
+    out[a.h2 + j] = w3;
+  } else if (kind < c2 + c1) {
+    const int j = (kind - c2) * NT + tid;
+    if (j >= a.h1) return;
+    double b1 = 0.0;
+#pragma unroll 8
+    for (int64_t s = s0; s < s1; ++s) b1 += (double)a.d1[s * a.h1 + j];
+    out[2 * a.h2 + j] = b1;
+  } else {
+    if (tid >= 64) return;
+    double d = 0.0, e = 0.0;
+    for (int64_t s = s0 + tid; s < s1; s += 64) {
+      d += (double)a.dg[s];
+      e += a.e2[s];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      d += __shfl_xor(d, o, 64);
+      e += __shfl_xor(e, o, 64);
+    }
+    if (tid == 0) {
+      out[2 * a.h2 + a.h1] = d;
+      out[2 * a.h2 + a.h1 + 1] = e;
+    }
+  }
 }
 
-// d2[s][j] = dg[s] w3[j] (1 - a2[s][j]^2)
-__global__ void k_back_out(const float *dg, const float *w3, const float *a2, int h2, int64_t n,
-                           float *d2) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * h2) return;
-  const int j = (int)(i % h2);
-  const float h = a2[i];
-  d2[i] = dg[i / h2] * w3[j] * (1.f - h * h);
+// The bias gradients, dw3 and the loss from the sample ranges' sums, and
+// (train) the Adam update with bias-corrected moments, c1 = 1 / (1 - b1^t),
+// c2 = 1 / (1 - b2^t); one thread per parameter, one more for the loss.
+struct AdamArgs {
+  float *theta, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ void adam_update(const AdamArgs &p, int64_t i, float gi) {
+  const float mi = p.b1 * p.m[i] + (1.f - p.b1) * gi;
+  const float vi = p.b2 * p.v[i] + (1.f - p.b2) * gi * gi;
+  p.m[i] = mi;
+  p.v[i] = vi;
+  p.theta[i] -= p.lr * (mi * p.c1) / (sqrtf(vi * p.c2) + p.eps);
 }
 
-// out[j] = sum_s a[s][j] * (wt ? wt[s] : 1) for j < cols (FP64 accumulation, fixed order)
-__global__ void k_colsum(const float *a, const float *wt, int cols, int64_t n, float *out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= cols) return;
-  double acc = 0.0;
-  for (int64_t s = 0; s < n; ++s) acc += (double)a[s * cols + j] * (wt ? (double)wt[s] : 1.0);
-  out[j] = (float)acc;
+template <bool TRAIN>
+__global__ __launch_bounds__(NT) void k_grad(const double *cols, int din, int h1, int h2, int S,
+                                             float *grad, double *loss, AdamArgs p) {
+  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  const int64_t n1 = (int64_t)h1 * din, n2 = (int64_t)h2 * h1, nc = 2 * h2 + h1 + 2;
+  const int64_t last = n1 + h1 + n2 + 2 * h2 + 1;
+  if (i > last) return;
+  int64_t j = -1;                                     // column of the sums
+  if (i >= n1 && i < n1 + h1) j = 2 * h2 + (i - n1);  // b1
+  else if (i >= n1 + h1 + n2) j = i - (n1 + h1 + n2) + (i >= last - 1 ? h1 : 0);   // b2, w3; b3, loss
+  float gi;
+  if (j >= 0) {
+    double acc = 0.0;
+#pragma unroll 8
+    for (int z = 0; z < S; ++z) acc += cols[z * nc + j];
+    if (i == last) {
+      *loss = acc;
+      return;
+    }
+    gi = (float)acc;
+    grad[i] = gi;
+  } else if (TRAIN) {
+    gi = grad[i];
+  }
+  if constexpr (TRAIN) adam_update(p, i, gi);
 }
 
 // deterministic FP64 sums: stage 1 per block, stage 2 in block order
@@ -383,11 +651,13 @@ __global__ void k_sum1(const float *x, const double *xd, int64_t n, double *part
   if (threadIdx.x == 0) partial[blockIdx.x] = sh[0];
 }
 
+// one wave: each lane adds every 64th partial, the lanes are added in a tree
 __global__ void k_sum2(const double *partial, int nblk, double *out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
   double acc = 0.0;
-  for (int i = 0; i < nblk; ++i) acc += partial[i];
-  out[0] = acc;
+  for (int i = threadIdx.x; i < nblk; i += 64) acc += partial[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  if (threadIdx.x == 0) out[0] = acc;
 }
 
 constexpr int SUM_BLOCKS = 256;
@@ -401,116 +671,130 @@ void dsum(hipStream_t st, const float *x, const double *xd, int64_t n, double *p
   SGW_HIP(hipGetLastError());
 }
 
-// Adam with bias-corrected moments; c1 = 1 / (1 - b1^t), c2 = 1 / (1 - b2^t)
-__global__ void k_adam(float *theta, float *m, float *v, const float *grad, int64_t n, float lr,
-                       float b1, float b2, float eps, float c1, float c2) {
+__global__ void k_adam(AdamArgs p, const float *grad, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = grad[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  theta[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+  if (i < n) adam_update(p, i, grad[i]);
 }
 
 inline unsigned blocks(int64_t n) { return (unsigned)((n + NT - 1) / NT); }
 
 // ---------------------------------------------------------------- network passes
 struct Acts {
-  float *xh, *a1, *a2, *g;
+  float *a1, *a2, *g;
 };
 
 Acts activations(sgw_mlp *M, int64_t n) {
   Acts a;
-  a.xh = M->buf("xh", sizeof(float) * n * M->din).as<float>();
   a.a1 = M->buf("a1", sizeof(float) * n * M->h1).as<float>();
   a.a2 = M->buf("a2", sizeof(float) * n * M->h2).as<float>();
   a.g = M->buf("g", sizeof(float) * n).as<float>();
   return a;
 }
 
-// g = network(x) for n samples (x [n][din]); activations kept in `a`
-void forward(sgw_mlp *M, const float *x, int64_t n, const Acts &a) {
+// both hidden layers for n samples (x [n][din])
+void hidden(sgw_mlp *M, const float *x, int64_t n, const Acts &a) {
   const float *th = M->theta.as<float>();
   hipStream_t st = M->stream;
-  hipLaunchKernelGGL(k_standardize, dim3(blocks(n * M->din)), dim3(NT), 0, st, x,
-                     M->mean.as<float>(), M->inv_std.as<float>(), M->din, n, a.xh);
-  SGW_HIP(hipGetLastError());
   GemmArgs g{};
-  // a1[s][j] = tanh(sum_k W1[j][k] xh[s][k] + b1[j])
+  // a1[s][j] = tanh(sum_k W1[j][k] xh[s][k] + b1[j]), xh standardized as it is loaded
   g.a = th + M->oW1(); g.sam = M->din; g.sak = 1;
-  g.b = a.xh; g.sbk = 1; g.sbn = M->din;
+  g.b = x; g.sbk = 1; g.sbn = M->din;
+  g.mean = M->mean.as<float>(); g.inv_std = M->inv_std.as<float>();
   g.c = a.a1; g.scm = 1; g.scn = M->h1;
   g.bias = th + M->ob1(); g.M = M->h1; g.N = (int)n; g.K = M->din;
-  gemm<EPI_TANH_BIAS>(st, g);
+  gemm<EPI_TANH_BIAS, BSTD_K>(st, g);
   // a2[s][j] = tanh(sum_k W2[j][k] a1[s][k] + b2[j])
   g.a = th + M->oW2(); g.sam = M->h1; g.sak = 1;
   g.b = a.a1; g.sbk = 1; g.sbn = M->h1;
   g.c = a.a2; g.scm = 1; g.scn = M->h2;
   g.bias = th + M->ob2(); g.M = M->h2; g.K = M->h1;
-  gemm<EPI_TANH_BIAS>(st, g);
-  hipLaunchKernelGGL(k_output, dim3(blocks(n)), dim3(NT), 0, st, a.a2, th + M->ow3(),
-                     th + M->ob3(), M->h2, n, a.g);
+  gemm<EPI_TANH_BIAS, BSTD_NONE>(st, g);
+}
+
+unsigned output_blocks(int64_t n) { return (unsigned)((n + OUT_S - 1) / OUT_S); }
+
+// out = network(x) for n samples (x [n][din]); activations kept in `a`
+void forward(sgw_mlp *M, const float *x, int64_t n, const Acts &a, float *out) {
+  const float *th = M->theta.as<float>();
+  hidden(M, x, n, a);
+  hipLaunchKernelGGL(k_output<false>, dim3(output_blocks(n)), dim3(NT), 0, M->stream, a.a2,
+                     th + M->ow3(), th + M->ob3(), M->h2, n, out, nullptr, nullptr, nullptr,
+                     nullptr);
   SGW_HIP(hipGetLastError());
 }
 
-// gradient of L = (1/n) sum (g - y)^2 into M->grad; the loss (FP64) into *d_loss
-void backward(sgw_mlp *M, const float *y, int64_t n, const Acts &a, double *d_loss) {
+AdamArgs adam_args(sgw_mlp *M, double lr, double b1, double b2, double eps) {
+  M->t += 1;
+  AdamArgs p;
+  p.theta = M->theta.as<float>(); p.m = M->m.as<float>(); p.v = M->v.as<float>();
+  p.lr = (float)lr; p.b1 = (float)b1; p.b2 = (float)b2; p.eps = (float)eps;
+  p.c1 = (float)(1.0 / (1.0 - std::pow(b1, (double)M->t)));
+  p.c2 = (float)(1.0 / (1.0 - std::pow(b2, (double)M->t)));
+  return p;
+}
+
+// Forward pass and gradient of L = (1/n) sum (g - y)^2 into M->grad, the sum
+// of squares (FP64) into *d_loss; with train, the Adam update too.  Six
+// launches a step.
+template <bool TRAIN>
+void gradient(sgw_mlp *M, const float *x, const float *y, int64_t n, const Acts &a,
+              double *d_loss, double lr) {
   const float *th = M->theta.as<float>();
-  float *gr = M->grad.as<float>();
   hipStream_t st = M->stream;
   float *dg = M->buf("dg", sizeof(float) * n).as<float>();
   double *e2 = M->buf("e2", sizeof(double) * n).as<double>();
-  double *part = M->buf("part", sizeof(double) * SUM_BLOCKS).as<double>();
   float *d2 = M->buf("d2", sizeof(float) * n * M->h2).as<float>();
   float *d1 = M->buf("d1", sizeof(float) * n * M->h1).as<float>();
-  hipLaunchKernelGGL(k_residual, dim3(blocks(n)), dim3(NT), 0, st, a.g, y, n, dg, e2);
+  hidden(M, x, n, a);
+  hipLaunchKernelGGL(k_output<true>, dim3(output_blocks(n)), dim3(NT), 0, st, a.a2,
+                     th + M->ow3(), th + M->ob3(), M->h2, n, a.g, y, dg, e2, d2);
   SGW_HIP(hipGetLastError());
-  dsum<1>(st, nullptr, e2, n, part, d_loss);
-  // dw3 = sum_s dg[s] a2[s], db3 = sum_s dg[s]
-  hipLaunchKernelGGL(k_colsum, dim3(blocks(M->h2)), dim3(NT), 0, st, a.a2, dg, M->h2, n,
-                     gr + M->ow3());
-  hipLaunchKernelGGL(k_colsum, dim3(1), dim3(NT), 0, st, dg, nullptr, 1, n, gr + M->ob3());
-  hipLaunchKernelGGL(k_back_out, dim3(blocks(n * M->h2)), dim3(NT), 0, st, dg, th + M->ow3(),
-                     a.a2, M->h2, n, d2);
-  SGW_HIP(hipGetLastError());
-  GemmArgs g{};
-  // dW2[j][k] = sum_s d2[s][j] a1[s][k]
-  g.a = d2; g.sam = 1; g.sak = M->h2;
-  g.b = a.a1; g.sbk = M->h1; g.sbn = 1;
-  g.c = gr + M->oW2(); g.scm = M->h1; g.scn = 1;
-  g.M = M->h2; g.N = M->h1; g.K = (int)n;
-  gemm<EPI_STORE>(st, g);
-  hipLaunchKernelGGL(k_colsum, dim3(blocks(M->h2)), dim3(NT), 0, st, d2, nullptr, M->h2, n,
-                     gr + M->ob2());
   // d1[s][k] = (sum_j W2[j][k] d2[s][j]) (1 - a1[s][k]^2)
-  g = GemmArgs{};
+  GemmArgs g{};
   g.a = th + M->oW2(); g.sam = 1; g.sak = M->h1;
   g.b = d2; g.sbk = 1; g.sbn = M->h2;
   g.c = d1; g.scm = 1; g.scn = M->h1;
   g.aux = a.a1; g.M = M->h1; g.N = (int)n; g.K = M->h2;
-  gemm<EPI_DTANH>(st, g);
-  // dW1[j][k] = sum_s d1[s][j] xh[s][k]
+  gemm<EPI_DTANH, BSTD_NONE>(st, g);
+  WGradArgs w{};
+  // sums over at most 64 ranges of at least 64 samples each
+  const int64_t S = std::max<int64_t>(1, std::min<int64_t>((n + 63) / 64, 64));
+  w.chunk = (int)((n + S - 1) / S);
+  w.S = (int)((n + w.chunk - 1) / w.chunk);
+  w.cols = M->buf("cols", sizeof(double) * w.S * (2 * M->h2 + M->h1 + 2)).as<double>();
+  float *gr = M->grad.as<float>();
+  // dW2[j][k] = sum_s d2[s][j] a1[s][k] (C transposed: M runs over k, the contiguous index)
   g = GemmArgs{};
+  g.a = a.a1; g.sam = 1; g.sak = M->h1;
+  g.b = d2; g.sbk = M->h2; g.sbn = 1;
+  g.c = gr + M->oW2(); g.scm = 1; g.scn = M->h1;
+  g.M = M->h1; g.N = M->h2; g.K = (int)n;
+  w.w2 = finish_args(g);
+  // dW1[j][k] = sum_s d1[s][j] xh[s][k]
   g.a = d1; g.sam = 1; g.sak = M->h1;
-  g.b = a.xh; g.sbk = M->din; g.sbn = 1;
+  g.b = x; g.sbk = M->din; g.sbn = 1;
+  g.mean = M->mean.as<float>(); g.inv_std = M->inv_std.as<float>();
   g.c = gr + M->oW1(); g.scm = M->din; g.scn = 1;
-  g.M = M->h1; g.N = M->din; g.K = (int)n;
-  gemm<EPI_STORE>(st, g);
-  hipLaunchKernelGGL(k_colsum, dim3(blocks(M->h1)), dim3(NT), 0, st, d1, nullptr, M->h1, n,
-                     gr + M->ob1());
+  g.M = M->h1; g.N = M->din;
+  w.w1 = finish_args(g);
+  w.tiles2 = DeepTile::count(w.w2.M, w.w2.N);
+  w.tiles1 = DeepTile::count(w.w1.M, w.w1.N);
+  w.d2 = d2; w.d1 = d1; w.a2 = a.a2; w.dg = dg; w.e2 = e2;
+  w.h1 = M->h1; w.h2 = M->h2; w.n = n;
+  const int percol = (M->h2 + NT - 1) / NT + (M->h1 + NT - 1) / NT + 1;
+  hipLaunchKernelGGL(k_wgrads, dim3(w.tiles2 + w.tiles1 + (w.S * percol + DEEP / NT - 1) / (DEEP / NT)),
+                     dim3(DEEP), 0, st, w);
+  SGW_HIP(hipGetLastError());
+  AdamArgs p{};
+  if (TRAIN) p = adam_args(M, lr, 0.9, 0.999, 1e-8);
+  hipLaunchKernelGGL(k_grad<TRAIN>, dim3(blocks(M->nparam + 1)), dim3(NT), 0, st, w.cols,
+                     M->din, M->h1, M->h2, w.S, gr, d_loss, p);
   SGW_HIP(hipGetLastError());
 }
 
 void adam(sgw_mlp *M, double lr, double b1, double b2, double eps) {
-  M->t += 1;
-  const double c1 = 1.0 / (1.0 - std::pow(b1, (double)M->t));
-  const double c2 = 1.0 / (1.0 - std::pow(b2, (double)M->t));
   hipLaunchKernelGGL(k_adam, dim3(blocks(M->nparam)), dim3(NT), 0, M->stream,
-                     M->theta.as<float>(), M->m.as<float>(), M->v.as<float>(),
-                     M->grad.as<float>(), M->nparam, (float)lr, (float)b1, (float)b2,
-                     (float)eps, (float)c1, (float)c2);
+                     adam_args(M, lr, b1, b2, eps), M->grad.as<float>(), M->nparam);
   SGW_HIP(hipGetLastError());
 }
 
@@ -629,9 +913,7 @@ sgw_status sgw_mlp_forward(sgw_mlp *M, const float *x, int64_t n, float *g) {
   return guard_mlp(M, [&] {
     SGW_REQUIRE(x && g, SGW_EINVAL, "NULL argument");
     check_n(n);
-    const Acts a = activations(M, n);
-    forward(M, x, n, a);
-    SGW_HIP(hipMemcpyAsync(g, a.g, 4 * n, hipMemcpyDeviceToDevice, M->stream));
+    forward(M, x, n, activations(M, n), g);
   });
 }
 
@@ -643,8 +925,7 @@ sgw_status sgw_mlp_gradient(sgw_mlp *M, const float *x, const float *y, int64_t 
     check_n(n);
     const Acts a = activations(M, n);
     double *d_loss = M->buf("loss1", sizeof(double)).as<double>();
-    forward(M, x, n, a);
-    backward(M, y, n, a, d_loss);
+    gradient<false>(M, x, y, n, a, d_loss, 0.0);
     std::vector<float> f(M->nparam);
     double L = 0;
     SGW_HIP(hipMemcpyAsync(f.data(), M->grad.p, 4 * M->nparam, hipMemcpyDeviceToHost, M->stream));
@@ -683,11 +964,7 @@ sgw_status sgw_mlp_train(sgw_mlp *M, const float *x, const float *y, int64_t n, 
     check_n(n);
     const Acts a = activations(M, n);
     double *d_hist = M->buf("hist", sizeof(double) * std::max(1, (int)steps)).as<double>();
-    for (int s = 0; s < steps; ++s) {
-      forward(M, x, n, a);
-      backward(M, y, n, a, d_hist + s);
-      adam(M, lr, 0.9, 0.999, 1e-8);
-    }
+    for (int s = 0; s < steps; ++s) gradient<true>(M, x, y, n, a, d_hist + s, lr);
     if (loss_hist && steps > 0) {
       std::vector<double> h(steps);
       SGW_HIP(hipMemcpyAsync(h.data(), d_hist, sizeof(double) * steps, hipMemcpyDeviceToHost,
@@ -719,7 +996,7 @@ sgw_status sgw_cv_cheap_moments(sgw_ctx *ctx, sgw_mlp *M, const float *phi, int3
     for (int64_t c = 0; c < nch; ++c) {
       const int64_t s0 = first_sample + c * chunk, n = std::min(chunk, count - c * chunk);
       features(ctx, phi, K, ld_phi, seed, s0, n, xf);
-      forward(M, xf, n, a);
+      forward(M, xf, n, a, a.g);
       dsum<1>(ctx->stream, a.g, nullptr, n, part, sums + 2 * c);
       dsum<2>(ctx->stream, a.g, nullptr, n, part, sums + 2 * c + 1);
     }
@@ -765,7 +1042,7 @@ sgw_status sgw_cv_cheap_moments_mixed(sgw_ctx *ctx, sgw_mlp *M, const float *phi
       const int64_t s0 = first_sample + c * chunk, n = std::min(chunk, count - c * chunk);
       if (Kz > 0) features(ctx, phi_z, Kz, ld_phi, seed, s0, n, xf, 0, K);
       if (Ke > 0) features(ctx, phi_e, Ke, ld_phi, seed, s0, n, xf + Kz, n_eta, K);
-      forward(M, xf, n, a);
+      forward(M, xf, n, a, a.g);
       dsum<1>(ctx->stream, a.g, nullptr, n, part, sums + 2 * c);
       dsum<2>(ctx->stream, a.g, nullptr, n, part, sums + 2 * c + 1);
     }

@@ -210,6 +210,41 @@ def test_gradient_matches_oracle_backprop(net_case):
     assert cos > 0.999
 
 
+@pytest.mark.parametrize("din,h1,h2,n", [(64, 256, 256, 1), (64, 256, 256, 129), (5, 7, 1, 33),
+                                          (1, 1, 3, 200), (36, 70, 130, 4097),
+                                          (64, 256, 256, 9000)])
+def test_gradient_at_tile_and_range_edges(din, h1, h2, n):
+    """Forward, loss and gradient at ragged layer sizes and sample counts (64 x
+    32 and 32 x 32 output tiles, K chunks of 64 and 256, sample ranges) against the
+    rounding model.  FP32 and FP64 pre-activations differ in the last bits, so
+    a BF16 operand may round to the neighbour of the model's, 2^-8 of its
+    value; a parameter block is held to that, normwise."""
+    rs = np.random.default_rng(1000 + n)
+    theta = systems.mlp_init(6, din, h1, h2)
+    theta = (theta + 0.05 * rs.standard_normal(theta.size)).astype(np.float32).astype(np.float64)
+    x = rs.gamma(1.0, 1.0, size=(n, din)).astype(np.float32)
+    y = (1.0 + rs.standard_normal(n)).astype(np.float32)
+    mean, std = np.full(din, 0.9), np.full(din, 1.25)
+    xh = ((x - np.float32(0.9)) * np.float32(1.0 / 1.25)).astype(np.float64)
+    m = sgw.Mlp(theta, din, h1, h2)
+    m.set_standardization(mean, std)
+    # x one float past a 16-byte boundary as well: the element-wise loads
+    xs = torch.empty(n * din + 1, device="cuda")
+    xs[1:] = torch.from_numpy(x.ravel()).cuda()
+    L, gr = m.gradient(f32(x), f32(y))
+    L1, gr1 = m.gradient(xs[1:].view(n, din), f32(y))
+    g = m.forward(f32(x)).cpu().numpy().astype(np.float64)
+    m.close()
+    assert L == L1 and np.array_equal(gr, gr1)
+    gm, _, _ = model_forward(theta, xh, din, h1, h2)
+    assert np.linalg.norm(g - gm) <= 2.0 ** -8 * np.linalg.norm(gm)
+    Lm = np.mean((gm - y) ** 2)
+    assert abs(L - Lm) <= 2.0 ** -7 * Lm
+    mod = model_gradient(theta, xh, y.astype(np.float64), din, h1, h2)
+    for k, (a, b) in enumerate(zip(blocks(gr, din, h1, h2), blocks(mod, din, h1, h2))):
+        assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(b), k
+
+
 def test_adam_steps_match_oracle(net_case):
     """Given gradients (host FP64 inputs), three Adam steps in FP32 against
     the oracle's FP64 Adam: relative 1e-6 of the parameters' scale."""
