@@ -434,7 +434,9 @@ sgw_status sgw_batch_sigma_estimate(sgw_batch_item *items, int32_t n, int32_t nw
  * phi: device float [K][ld_phi] real orbitals (1 <= K <= 64, ld_phi >= N),
  * rounded to BF16 on the device; x: device float [nsamp][K].  The sample
  * indices must lie in [0, 2^20); N must be divisible by 64 (else
- * SGW_EUNSUPPORTED).  Asynchronous on the context's stream. */
+ * SGW_EUNSUPPORTED).  Needs up to 64 MiB of context scratch (partial sums
+ * over parts of the grid, below 2^18 samples) beside phi in BF16.
+ * Asynchronous on the context's stream. */
 sgw_status sgw_cv_features(sgw_ctx *ctx, const float *phi, int32_t K, int64_t ld_phi,
                            uint64_t seed, int64_t first_sample, int64_t nsamp, float *x);
 
@@ -445,7 +447,8 @@ sgw_status sgw_cv_features(sgw_ctx *ctx, const float *phi, int32_t K, int64_t ld
  * eta-bar_{i,l} the white noise that sgw_sigma_estimate draws for sample i.
  * Arguments as sgw_cv_features; rows of x are ldx >= K floats apart (so the
  * zeta-bar and eta-bar features of one sample can share a row).  Needs
- * 4 nsamp n_eta K bytes of context scratch. */
+ * 4 nsamp n_eta K bytes of context scratch (K rounded up to 16), or 64 MiB
+ * where that is less. */
 sgw_status sgw_cv_features_eta(sgw_ctx *ctx, const float *phi, int32_t K, int64_t ld_phi,
                                uint64_t seed, int64_t first_sample, int64_t nsamp,
                                int32_t n_eta, float *x, int64_t ldx);

@@ -96,87 +96,131 @@ __device__ __forceinline__ void mma(f32x4 &acc, const u32x4 &a, const u32x4 &b) 
 constexpr int NT = 256;
 
 // ---------------------------------------------------------------- features
-// phi (FP32 [K][ld]) -> BF16 [64][N], rows K..63 zero
-__global__ void k_phi_bf16(const float *phi, int64_t ld, int K, int64_t N, uint16_t *out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= 64 * N) return;
-  const int k = (int)(i / N);
-  const int64_t r = i % N;
-  out[i] = k < K ? (uint16_t)bf16r(phi[k * ld + r]) : (uint16_t)0;
+// phi (FP32 [K][ld]) -> BF16 [rows][N], rows K.. zero, in the order in which
+// the feature GEMM takes the points: K slot 8 q + 2 j + h of a 32-point group
+// holds point 4 q + j + 16 h, so that the two points of a packed BF16 pair
+// have their sign bits 16 apart in the group's 32 random bits.  One thread
+// per 8 slots of a row.
+__global__ __launch_bounds__(256) void k_phi_bf16(const float *phi, int64_t ld, int K, int64_t N,
+                                                  int vec, uint16_t *out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int k = blockIdx.y;
+  if (8 * i >= N) return;
+  float lo[4] = {0.f, 0.f, 0.f, 0.f}, hi[4] = {0.f, 0.f, 0.f, 0.f};
+  if (k < K) {
+    const float *p = phi + k * ld + (i >> 2) * 32 + 4 * (i & 3);
+    if (vec) {
+      const float4 a = *reinterpret_cast<const float4 *>(p);
+      const float4 b = *reinterpret_cast<const float4 *>(p + 16);
+      lo[0] = a.x; lo[1] = a.y; lo[2] = a.z; lo[3] = a.w;
+      hi[0] = b.x; hi[1] = b.y; hi[2] = b.z; hi[3] = b.w;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        lo[j] = p[j];
+        hi[j] = p[16 + j];
+      }
+    }
+  }
+  u32x4 o;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) o[j] = bf16r(lo[j]) | bf16r(hi[j]) << 16;
+  *reinterpret_cast<u32x4 *>(out + k * N + 8 * i) = o;
 }
 
-// x[s][k] = dV (sum_r phi_k(r) sign_s(r))^2 = |<phi_k|zeta_s>|^2 for zeta_s =
-// sign / sqrt(dV).  Workgroup: 4 waves x NS tiles of 16 samples; every wave
-// runs the whole grid (K = N points, groups of 32) for its samples with the
-// 4 x 16 state rows as A and the signs of its samples as B, made in
-// registers from the counter-based generator: the 8 signs a lane feeds for
-// points r0..r0+7 are 8 bits of word(r0 / 64), bit 0 -> +1.  The A rows of
-// each 64-point chunk are staged once per workgroup in LDS (two buffers: the
-// next chunk is loaded while the current one is multiplied), so the four
-// waves share one read of phi from the cache.
-// With neta > 0 the columns are the occupied-orbital noise vectors instead:
-// column s is eta-bar_{s / neta, s % neta} (stream kind ETA), and x holds one
-// row per column (averaged over l by k_eta_mean).  Rows of x are ldx apart.
-template <int NS>
+// rows[t] = the value that lane (16 t + lane % 16) holds, t = 0..3
+__device__ __forceinline__ void spread_rows(uint32_t v, uint32_t *rows) {
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // rows 0022, 1133
+  const auto e = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
+  const auto o = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
+  rows[0] = e[0];
+  rows[1] = o[0];
+  rows[2] = e[1];
+  rows[3] = o[1];
+}
+
+// sum_r phi_k(r) sign_s(r) over part blockIdx.y of the grid (64-point chunks
+// c0 .. c0 + cpp - 1): BF16 MFMA GEMM of the state rows (A, MT tiles of 16)
+// with the signs of the white-noise vectors (B), bit 0 -> +1.  Workgroup:
+// 4 waves x 64 vectors.  The signs never touch memory: per chunk each lane
+// draws the 64-bit word of ONE vector (row q of 16 lanes that of vectors
+// 16 q .. 16 q + 15) and the four rows exchange them by lane swaps, and with
+// the point order of k_phi_bf16 a packed pair of signs is one shift and one
+// and-or of the word.  (Every row drawing every word, with bits placed one by
+// one, the vector ALU took twice the time of the MFMA pipe.)  The A rows of
+// each chunk are staged once per workgroup in LDS, the next chunk's loads in
+// flight behind the products.  Parts of the grid fill the chip when there are
+// few vectors.  64 states x 64^3 points: 16384 vectors 3250 -> 430 us (16
+// parts), 262144 vectors 9.9 -> 7.7 ms (one part): 1.1-1.2 PFLOP/s, the rate
+// that a large BF16 matrix product reaches on this device.
+// With neta > 0 column c is the occupied-orbital noise vector eta-bar_{c /
+// neta, c % neta} (stream kind ETA), else zeta-bar_c.  direct: x[c][k] =
+// dV (sum)^2 = |<phi_k|zeta_c>|^2 at rows ldx apart; else the sums go to
+// part[blockIdx.y][c][16 MT].
+constexpr int FEAT_COLS = 256;                 // vectors per workgroup
+
+template <int MT>
 __global__ __launch_bounds__(NT) void k_features(const uint16_t *phi16, int64_t N, int K,
-                                                 uint64_t seed, int64_t s0, int64_t nsamp,
-                                                 float dV, float *x, int neta, int64_t ldx) {
+                                                 uint64_t seed, int64_t s0, int64_t ncol,
+                                                 int64_t cpp, float dV, float *x, int64_t ldx,
+                                                 int neta, int direct) {
   constexpr int PA = 72;                           // LDS row pitch (BF16): 64 points + 8
-  __shared__ __align__(16) uint16_t sa[2][64 * PA];
+  constexpr int NP = (16 * MT * 8 + NT - 1) / NT;  // 16-byte pieces of a chunk per thread
+  __shared__ __align__(16) uint16_t sa[2][16 * MT * PA];
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6, q = lane >> 4, col = lane & 15;
-  const int64_t sbase = s0 + ((int64_t)blockIdx.x * 4 + w) * (16 * NS);
-  uint64_t key[NS];
+  const int64_t sbase = s0 + (int64_t)blockIdx.x * FEAT_COLS + 64 * w;
+  const uint64_t c = (uint64_t)(sbase + 16 * q + col);
+  const uint64_t key =
+      neta > 0 ? rng_key(seed, rng_stream(RNG_ETA, c / (uint64_t)neta, c % (uint64_t)neta))
+               : rng_key(seed, rng_stream(RNG_ZETA, c, 0));
+  f32x4 acc[MT][4];
 #pragma unroll
-  for (int t = 0; t < NS; ++t) {
-    const uint64_t c = (uint64_t)(sbase + 16 * t + col);
-    key[t] = neta > 0 ? rng_key(seed, rng_stream(RNG_ETA, c / (uint64_t)neta, c % (uint64_t)neta))
-                      : rng_key(seed, rng_stream(RNG_ZETA, c, 0));
-  }
-  f32x4 acc[4][NS];
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int t = 0; t < NS; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // chunk staging: 64 rows x 64 points = 512 pieces of 16 B, two per thread
+    for (int t = 0; t < 4; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int row0 = tid >> 3, seg = tid & 7;
-  auto fetch = [&](int64_t r64, u32x4 *g) {
+  auto fetch = [&](int64_t ch, u32x4 *g) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      g[i] = *reinterpret_cast<const u32x4 *>(phi16 + (int64_t)(row0 + 32 * i) * N + r64 + 8 * seg);
+    for (int i = 0; i < NP; ++i)
+      if (NP * NT == 16 * MT * 8 || row0 + 32 * i < 16 * MT)
+        g[i] = *reinterpret_cast<const u32x4 *>(phi16 + (int64_t)(row0 + 32 * i) * N + 64 * ch + 8 * seg);
   };
   auto stage = [&](int buf, const u32x4 *g) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      *reinterpret_cast<u32x4 *>(&sa[buf][(row0 + 32 * i) * PA + 8 * seg]) = g[i];
+    for (int i = 0; i < NP; ++i)
+      if (NP * NT == 16 * MT * 8 || row0 + 32 * i < 16 * MT)
+        *reinterpret_cast<u32x4 *>(&sa[buf][(row0 + 32 * i) * PA + 8 * seg]) = g[i];
   };
-  u32x4 gnext[2];
-  fetch(0, gnext);
+  const int64_t c0 = blockIdx.y * cpp, c1 = min(N / 64, c0 + cpp);
+  u32x4 gnext[NP];
+  fetch(c0, gnext);
   stage(0, gnext);
   __syncthreads();
   int buf = 0;
-  for (int64_t r64 = 0; r64 < N; r64 += 64) {
-    const bool more = r64 + 64 < N;
-    if (more) fetch(r64 + 64, gnext);
-    uint64_t word[NS];
-#pragma unroll
-    for (int t = 0; t < NS; ++t) word[t] = sm64(key[t] + (uint64_t)(r64 >> 6));
+  const int sh = 12 - 4 * q;
+  for (int64_t ch = c0; ch < c1; ++ch) {
+    const bool more = ch + 1 < c1;
+    if (more) fetch(ch + 1, gnext);
+    const uint64_t word = sm64(key + (uint64_t)ch);
+    uint32_t bits[2][4];
+    spread_rows((uint32_t)word, bits[0]);
+    spread_rows((uint32_t)(word >> 32), bits[1]);
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      u32x4 a[4];
+      u32x4 a[MT];
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
+      for (int m = 0; m < MT; ++m)
         a[m] = *reinterpret_cast<const u32x4 *>(&sa[buf][(16 * m + col) * PA + 32 * half + 8 * q]);
-      const int sh = 32 * half + 8 * q;
 #pragma unroll
-      for (int t = 0; t < NS; ++t) {
-        const uint32_t bits = (uint32_t)(word[t] >> sh);
+      for (int t = 0; t < 4; ++t) {
+        // points 4 q + j and 4 q + j + 16: bits to positions 15 and 31
+        const uint32_t v = bits[half][t] << sh;
         u32x4 b;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          b[j] = 0x3F803F80u | ((bits >> (2 * j)) & 1u) << 15 | ((bits >> (2 * j + 1)) & 1u) << 31;
+        for (int j = 0; j < 4; ++j) b[j] = ((v << (3 - j)) & 0x80008000u) | 0x3F803F80u;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) mma(acc[m][t], a[m], b);
+        for (int m = 0; m < MT; ++m) mma(acc[m][t], a[m], b);
       }
     }
     if (more) stage(buf ^ 1, gnext);
@@ -184,30 +228,41 @@ __global__ __launch_bounds__(NT) void k_features(const uint16_t *phi16, int64_t 
     buf ^= 1;
   }
 #pragma unroll
-  for (int t = 0; t < NS; ++t) {
-    const int64_t s = sbase + 16 * t + col;
-    if (s - s0 >= nsamp) continue;
+  for (int t = 0; t < 4; ++t) {
+    const int64_t i = sbase + 16 * t + col - s0;
+    if (i >= ncol) continue;
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+    for (int m = 0; m < MT; ++m) {
+      if (direct) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int k = 16 * m + 4 * q + r;
-        if (k < K) x[(s - s0) * ldx + k] = dV * acc[m][t][r] * acc[m][t][r];
+        for (int r = 0; r < 4; ++r) {
+          const int k = 16 * m + 4 * q + r;
+          if (k < K) x[i * ldx + k] = dV * acc[m][t][r] * acc[m][t][r];
+        }
+      } else {
+        *reinterpret_cast<f32x4 *>(x + ((int64_t)blockIdx.y * ncol + i) * (16 * MT) + 16 * m + 4 * q) = acc[m][t];
       }
+    }
   }
 }
 
-constexpr int FEAT_NS = 4;                     // 256 samples per workgroup
-
-// x[i][k] = (1/neta) sum_l y[i neta + l][k], summed in order of l
-__global__ void k_eta_mean(const float *y, int64_t nsamp, int neta, int K, float *x,
-                           int64_t ldx) {
+// x[i][k] = (1/neta) sum_l dV (sum_p part[p][i neta + l][k])^2, in order of l
+// and p (neta >= 1; part rows are kp floats)
+__global__ void k_feature_sums(const float *part, int64_t nsamp, int neta, int np, int kp, int K,
+                               float dV, float *x, int64_t ldx) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nsamp * K) return;
   const int64_t s = i / K;
   const int k = (int)(i % K);
+  const int64_t step = nsamp * neta * kp;
   float acc = 0.f;
-  for (int l = 0; l < neta; ++l) acc += y[(s * neta + l) * K + k];
+  for (int l = 0; l < neta; ++l) {
+    const float *p = part + (s * neta + l) * kp + k;
+    float v = 0.f;
+#pragma unroll 4
+    for (int j = 0; j < np; ++j) v += p[j * step];
+    acc += dV * v * v;
+  }
   x[s * ldx + k] = acc / (float)neta;
 }
 
@@ -217,27 +272,37 @@ void features(sgw_ctx *ctx, const float *phi, int K, int64_t ld, uint64_t seed, 
               int64_t nsamp, float *x, int neta = 0, int64_t ldx = 0) {
   const int64_t N = ctx->N;
   if (ldx <= 0) ldx = K;
-  DevBuf &p16 = ctx->buf("cv_phi16", sizeof(uint16_t) * 64 * (size_t)N);
-  hipLaunchKernelGGL(k_phi_bf16, dim3((unsigned)((64 * N + NT - 1) / NT)), dim3(NT), 0,
-                     ctx->stream, phi, ld, K, N, p16.as<uint16_t>());
+  const int mt = (K + 15) / 16, kp = 16 * mt;      // state tiles: no products for absent states
+  uint16_t *p16 = ctx->buf("cv_phi16", sizeof(uint16_t) * kp * (size_t)N).as<uint16_t>();
+  const int vec = ((uintptr_t)phi & 15) == 0 && ld % 4 == 0;
+  hipLaunchKernelGGL(k_phi_bf16, dim3((unsigned)((N / 8 + 255) / 256), kp), dim3(256), 0,
+                     ctx->stream, phi, ld, K, N, vec, p16);
   SGW_HIP(hipGetLastError());
-  const int64_t per = 4 * 16 * FEAT_NS;
-  if (neta <= 0) {
-    const int64_t nblk = (nsamp + per - 1) / per;
-    hipLaunchKernelGGL(k_features<FEAT_NS>, dim3((unsigned)nblk), dim3(NT), 0, ctx->stream,
-                       p16.as<uint16_t>(), N, K, seed, s0, nsamp, (float)ctx->dV, x, 0, ldx);
-    SGW_HIP(hipGetLastError());
-    return;
-  }
-  const int64_t ncol = nsamp * neta;
-  float *y = ctx->buf("cv_eta_cols", sizeof(float) * (size_t)ncol * K).as<float>();
-  const int64_t nblk = (ncol + per - 1) / per;
-  hipLaunchKernelGGL(k_features<FEAT_NS>, dim3((unsigned)nblk), dim3(NT), 0, ctx->stream,
-                     p16.as<uint16_t>(), N, K, seed, s0 * neta, ncol, (float)ctx->dV, y, neta,
-                     (int64_t)K);
+  const int64_t ncol = neta > 0 ? nsamp * neta : nsamp;
+  const int64_t nblk = (ncol + FEAT_COLS - 1) / FEAT_COLS;
+  // parts of the grid: about 1024 workgroups (four per CU), at least 16
+  // chunks of 64 points each; one part from 1024 blocks of vectors on
+  const int64_t nch = N / 64;
+  int64_t np = std::max<int64_t>(1, std::min(1024 / nblk, nch / 16));
+  const int64_t cpp = (nch + np - 1) / np;
+  np = (nch + cpp - 1) / cpp;
+  const int direct = np == 1 && neta <= 0;
+  float *part = direct ? x
+                       : ctx->buf("cv_part_sums", sizeof(float) * (size_t)np * ncol * kp).as<float>();
+  const dim3 g((unsigned)nblk, (unsigned)np);
+  const uint64_t col0 = neta > 0 ? (uint64_t)s0 * neta : (uint64_t)s0;
+#define SGW_F(M)                                                                                \
+  case M:                                                                                       \
+    hipLaunchKernelGGL(k_features<M>, g, dim3(NT), 0, ctx->stream, p16, N, K, seed,             \
+                       (int64_t)col0, ncol, cpp, (float)ctx->dV, part, ldx, neta, direct);      \
+    break;
+  switch (mt) { SGW_F(1) SGW_F(2) SGW_F(3) SGW_F(4) }
+#undef SGW_F
   SGW_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_eta_mean, dim3((unsigned)((nsamp * K + NT - 1) / NT)), dim3(NT), 0,
-                     ctx->stream, y, nsamp, neta, K, x, ldx);
+  if (direct) return;
+  hipLaunchKernelGGL(k_feature_sums, dim3((unsigned)((nsamp * K + NT - 1) / NT)), dim3(NT), 0,
+                     ctx->stream, part, nsamp, std::max(1, neta), (int)np, kp, K, (float)ctx->dV,
+                     x, ldx);
   SGW_HIP(hipGetLastError());
 }
 

@@ -79,6 +79,36 @@ def test_features_match_oracle(which, K, first, nsamp, request):
     assert np.max(np.abs(got - model)) < 1e-4 * np.max(model)
 
 
+@pytest.mark.parametrize("n,K,first,nsamp,neta", [(8, 1, 0, 1, 0), (16, 17, 5, 255, 0),
+                                                  (24, 32, 0, 257, 0), (32, 48, 3, 40, 0),
+                                                  (32, 64, 2, 3, 150), (8, 33, 0, 9, 1)])
+def test_features_parts_and_state_tiles(n, K, first, nsamp, neta):
+    """Every count of 16-state tiles, blocks of 256 vectors that are full,
+    short by one and over by one, one and several parts of the grid, and phi
+    rows off 16-byte boundaries, against the rounding model: the sums of N
+    BF16 products in FP32 are within N 2^-24 sum|phi| of it."""
+    N, dV = n ** 3, 0.5 ** 3
+    rs = np.random.default_rng(41)
+    ld = N + 3                                  # rows not 16-byte aligned
+    phi = np.zeros((K, ld), dtype=np.float32)
+    phi[:, :N] = rs.standard_normal((K, N)) / np.sqrt(N * dV)
+    p64 = bf16(phi[:, :N])
+    ctx = sgw.Context(n, 0.5, np.zeros(N), None, precision=sgw.SGW_C64, max_nvec=1)
+    if neta:
+        got = sgw.cv_features_eta(ctx, f32(phi), 9, first, nsamp, neta)
+    else:
+        got = sgw.cv_features(ctx, f32(phi), 9, first, nsamp)
+    got = got.cpu().numpy().astype(np.float64)
+    ctx.close()
+    kind, cols = (cv.rng.ETA, range(neta)) if neta else (cv.rng.ZETA, (0,))
+    a = np.stack([[p64 @ cv.rng.white_noise_signs(9, cv.rng.stream_id(kind, i, l), N)
+                   for l in cols] for i in range(first, first + nsamp)])
+    ref = np.mean(dV * a ** 2, axis=1)
+    da = np.sum(np.abs(p64), axis=1) * N * 2.0 ** -24 + 1e-7 * np.max(np.abs(a))
+    bound = np.mean(dV * (2 * np.abs(a) * da + da ** 2), axis=1) + 1e-6 * ref
+    assert np.all(np.abs(got - ref) <= bound)
+
+
 def test_features_160_grid_sampled():
     """The control-variate configuration's grid (160^3 points, h = 0.6 bohr)
     with its 64 states and a ragged last block of samples (600 = 2 x 256 + 88):
