@@ -2,15 +2,16 @@
 // switch between the position representation, where V is diagonal, and the
 // momentum representation, where T is diagonal).
 //
-// Passes over a batch of vectors (x fastest):
-//   plane   one xy plane of one vector per workgroup, x then y transform in
-//           LDS, with fused epilogues on the inverse pass (V psi, Chebyshev
-//           update, Poisson outputs) -- used when the plane fits in LDS;
-//   pencil  TX neighbouring x columns along y or z per workgroup (coalesced
-//           rows of TX complex), optionally forward z -> k-space multiplier
-//           -> inverse z in one pass;
-//   xlines  whole x lines (fallback for planes too big for LDS).
-#include "fft_lds.h"
+// Passes over a batch of vectors (x fastest), the first and the last with a
+// whole xy plane per workgroup:
+//   plane   x and y transform of one xy plane of one vector, with fused
+//           epilogues on the inverse pass (V psi, Chebyshev update, Poisson
+//           outputs);
+//   pencil  TX neighbouring columns along z (coalesced rows of TX complex):
+//           forward z -> k-space multiplier -> inverse z;
+//   xlines, ypencil  x lines and y columns in two passes, where a plane does
+//           not fit in LDS (160^2 in complex FP64).
+#include "fft_reg.h"
 
 namespace sgw {
 
@@ -20,13 +21,12 @@ struct PassArgs {
   const void *src = nullptr;
   void *dst = nullptr;
   int64_t ld_src = 0, ld_dst = 0, ld_x = 0;
-  const void *tw0 = nullptr, *tw1 = nullptr;   // twiddles of the two axes used
+  const void *tw0 = nullptr;                   // twiddles of the pass's axis (x and y are equal)
   const void *k2x = nullptr, *k2y = nullptr, *k2z = nullptr;
   int nx = 0, ny = 0, nz = 0;
   int mode = 0;          // PlaneMode (inverse passes) / 0 forward
-  int inverse = 0;
-  int mul = 0;           // MulMode (pencil z)
-  int axis = 2;          // pencil: 1 = y, 2 = z
+  int inverse = 0;       // y pencils
+  int mul = 0;           // MulMode (z pencils)
   int rev = 0;           // 1: vectors in descending order of blockIdx.y
   double tau = 0, ecut = 0, invN = 0;
   int64_t N = 0;
@@ -103,37 +103,77 @@ __device__ __forceinline__ void epilogue(const PassArgs &a, int64_t v, int64_t r
 }
 
 // ----------------------------------------------------------------- plane
-template <typename R, int NX, int NY, int MODE>
-__global__ __launch_bounds__(NT_FFT) void k_plane(PassArgs a) {
+// One xy plane of one vector per workgroup: y transform, then x transform,
+// the points in registers throughout.  The first y stage loads rows of x, the
+// last x stage stores (and reads its epilogue operands) in runs of R1 points;
+// three exchanges through LDS connect the four stages.
+template <typename R, int N, int MODE = PLANE_FWD> struct PlaneShape {
+  static constexpr bool D = sizeof(R) == 8;
+  static constexpr int T = N == 128 ? (D ? 512 : 1024) : N == 112 ? 448 : N == 96 ? (D ? 384 : 768)
+                         : N == 80 ? 448 : N == 64 ? 512 : N == 56 ? 448 : N == 48 ? 192
+                         : N == 40 ? 320 : N == 32 ? 256 : N == 24 ? 192 : 64;
+  // waves per SIMD to fit the registers for: two workgroups per CU
+  static constexpr int WPE = !D && N == 128 && MODE != PLANE_INV_CHEB && MODE != PLANE_INV_SPLIT ? 8
+                           : !D && N == 112 ? 4 : 1;
+  // odd pitch: lanes on successive lines fall on distinct banks; at 128 and
+  // 64 also wide enough that the runs of R1 points of neighbouring lines do
+  static constexpr int P = N == 128 ? 145 : N == 64 ? 73 : N + 1;
+  static constexpr bool SPLIT = true;
+  static constexpr size_t lds = (size_t)N * P * sizeof(R) * (SPLIT ? 1 : 2) + N * sizeof(cplx<R>);
+  static constexpr bool fits = lds <= 160 * 1024 && !(D && N == 112) && !(!D && N == 160);
+};
+
+template <typename R, int N, int MODE>
+__global__ __launch_bounds__((PlaneShape<R, N>::T), (PlaneShape<R, N, MODE>::WPE)) void k_plane(PassArgs a) {
   constexpr bool INV = MODE != PLANE_FWD;
   using C = cplx<R>;
-  constexpr int P = NX + 1;
-  constexpr int E = NX * NY;
-  __shared__ C s[NY * P];
-  __shared__ C twx[NX], twy[NY];
+  using Sh = PlaneShape<R, N, MODE>;
+  constexpr int R1 = Radix<N>::R1, R2 = Radix<N>::R2, P = Sh::P, T = Sh::T;
+  __shared__ R s[N * P * (Sh::SPLIT ? 1 : 2)];
+  __shared__ C tw[N];
   const int tid = threadIdx.x;
-  const int z = blockIdx.x;
   const int64_t v = a.rev ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
-  for (int i = tid; i < NX; i += NT_FFT) twx[i] = static_cast<const C *>(a.tw0)[i];
-  for (int i = tid; i < NY; i += NT_FFT) twy[i] = static_cast<const C *>(a.tw1)[i];
-  const int64_t plane = (int64_t)z * E;
+  const int64_t plane = (int64_t)blockIdx.x * (N * N);
   const C *src = static_cast<const C *>(a.src) + v * a.ld_src + plane;
+  Stage<C, R1, N * R2, T> s1;
+  Stage<C, R2, N * R1, T> s2;
+  // x: butterflies b = (j fast, line)
+  s1.each(tid, [&](int q, int b) {
 #pragma unroll
-  for (int q = 0; q < (E + NT_FFT - 1) / NT_FFT; ++q) {
-    const int e = tid + q * NT_FFT;
-    if (E % NT_FFT == 0 || e < E) {
-      C val = src[e];
-      if (INV) val = cconj(val);
-      s[(e / NX) * P + (e % NX)] = val;
-    }
-  }
-  __syncthreads();
-  lds_fft<C, NX, NY, P, 1, true, NT_FFT>(s, twx, tid);
-  lds_fft<C, NY, NX, 1, P, true, NT_FFT>(s, twy, tid);
-  constexpr int Q = (E + NT_FFT - 1) / NT_FFT;
-  if constexpr (MODE == PLANE_INV_CHEB && E % NT_FFT == 0) {
-    // all operand loads of this thread in flight at once, then the updates
-    // (the stores to vold / acc would otherwise order every later load)
+    for (int i = 0; i < R1; ++i) s1.v[q][i] = src[(b / R2) * N + b % R2 + i * R2];
+  });
+  for (int i = tid; i < N; i += T) tw[i] = static_cast<const C *>(a.tw0)[i];
+  if (INV)
+    s1.each(tid, [&](int q, int) {
+#pragma unroll
+      for (int i = 0; i < R1; ++i) s1.v[q][i] = cconj(s1.v[q][i]);
+    });
+  s1.dft(tid);
+  exchange<Sh::SPLIT, C>(
+      s, tid, s1, s2, true, [](int b, int i) { return (b / R2) * P + (b % R2) * R1 + i; },
+      [](int b, int i) { return (b % N) * P + b / N + i * R1; });
+  twiddle<C>(s2, tw, tid, [](int b) { return b / N; });
+  s2.dft(tid);
+  // to y columns, butterflies b = (x fast, j)
+  exchange<Sh::SPLIT, C>(
+      s, tid, s2, s1, true, [](int b, int i) { return (b % N) * P + b / N + i * R1; },
+      [](int b, int i) { return (b / N + i * R2) * P + b % N; });
+  s1.dft(tid);
+  exchange<Sh::SPLIT, C>(
+      s, tid, s1, s2, false, [](int b, int i) { return ((b / N) * R1 + i) * P + b % N; },
+      [](int b, int i) { return (b / N + i * R1) * P + b % N; });
+  twiddle<C>(s2, tw, tid, [](int b) { return b / N; });
+  s2.dft(tid);
+  constexpr int STEP = R1 * N;           // butterfly b's output i is at point b + i STEP
+  if (INV)
+    s2.each(tid, [&](int q, int) {
+#pragma unroll
+      for (int i = 0; i < R2; ++i) s2.v[q][i] = cconj(s2.v[q][i]);
+    });
+  // epilogue operands are loaded CH points at a time before their stores (the
+  // stores would otherwise order every later load)
+  constexpr int CH = R2 % 4 == 0 ? 4 : R2;
+  if constexpr (MODE == PLANE_INV_CHEB) {
     const C *xp = static_cast<const C *>(a.e.x) + v * a.ld_x + plane;
     C *vp = static_cast<C *>(a.e.vold) + v * a.ld_x + plane;
     C *wp = (a.e.vout ? static_cast<C *>(a.e.vout) : static_cast<C *>(a.e.vold)) + v * a.ld_x + plane;
@@ -141,7 +181,7 @@ __global__ __launch_bounds__(NT_FFT) void k_plane(PassArgs a) {
     const R *Vp = static_cast<const R *>(a.e.vloc) + plane;
     const bool first = a.e.first != 0;
     const int am = a.e.acc_mode;
-    const R c = (R)a.e.c, iR = (R)a.e.invR, s2 = (R)a.e.scale2;
+    const R c = (R)a.e.c, iR = (R)a.e.invR, s2c = (R)a.e.scale2;
     R b0r = (R)a.e.cprev_re, b0i = (R)a.e.cprev_im, b1r = (R)a.e.coef_re, b1i = (R)a.e.coef_im;
     if (am && a.e.coef_dev) {
       const int k = a.e.term_dev[0];
@@ -150,73 +190,76 @@ __global__ __launch_bounds__(NT_FFT) void k_plane(PassArgs a) {
       b1r = (R)a.e.coef_dev[2 * k];
       b1i = (R)a.e.coef_dev[2 * k + 1];
     }
-    // two halves keep the operands within the 4-waves-per-SIMD register budget
-    constexpr int QH = Q % 2 == 0 ? Q / 2 : Q;
+    s2.each(tid, [&](int q, int b) {
+      const int e0 = b;
 #pragma unroll
-    for (int h = 0; h < Q / QH; ++h) {
-      C xs[QH], ps[QH], ss[QH];
-      R Vs[QH];
+      for (int h = 0; h < R2 / CH; ++h) {
+        C xs[CH], ps[CH], ss[CH];
+        R Vs[CH];
 #pragma unroll
-      for (int q = 0; q < QH; ++q) {
-        const int e = tid + (h * QH + q) * NT_FFT;
-        xs[q] = xp[e];
-        Vs[q] = Vp[e];
-        ps[q].x = ps[q].y = 0;
-        ss[q].x = ss[q].y = 0;
-        if (!first) ps[q] = vp[e];
-        if (am == 2) ss[q] = ap[e];
-      }
+        for (int i = 0; i < CH; ++i) {
+          const int e = e0 + (h * CH + i) * STEP;
+          xs[i] = xp[e];
+          Vs[i] = Vp[e];
+          ps[i].x = ps[i].y = 0;
+          ss[i].x = ss[i].y = 0;
+          if (!first) ps[i] = vp[e];
+          if (am == 2) ss[i] = ap[e];
+        }
 #pragma unroll
-      for (int q = 0; q < QH; ++q) {
-        const int e = tid + (h * QH + q) * NT_FFT;
-        const C val = cconj(s[(e / NX) * P + (e % NX)]);
-        const C x = xs[q], pv = ps[q];
-        // w = (H x - c x)/R; v_{n+1} = s2 w - v_{n-1}; on odd n
-        // acc (+)= b_{n-1} v_{n-1} + b_n v_n
-        C nv;
-        nv.x = s2 * ((val.x + (Vs[q] - c) * x.x) * iR) - pv.x;
-        nv.y = s2 * ((val.y + (Vs[q] - c) * x.y) * iR) - pv.y;
-        wp[e] = nv;
-        if (am) {
-          C sm = ss[q];
-          sm.x += b0r * pv.x - b0i * pv.y;
-          sm.y += b0r * pv.y + b0i * pv.x;
-          sm.x += b1r * x.x - b1i * x.y;
-          sm.y += b1r * x.y + b1i * x.x;
-          ap[e] = sm;
+        for (int i = 0; i < CH; ++i) {
+          const int e = e0 + (h * CH + i) * STEP;
+          const C val = s2.v[q][h * CH + i], x = xs[i], pv = ps[i];
+          // w = (H x - c x)/R; v_{n+1} = s2 w - v_{n-1}; on odd n
+          // acc (+)= b_{n-1} v_{n-1} + b_n v_n.  The projector part of H x is
+          // added to v_{n+1} afterwards, so v_{n-1} and v_n are complete here.
+          C nv;
+          nv.x = s2c * ((val.x + (Vs[i] - c) * x.x) * iR) - pv.x;
+          nv.y = s2c * ((val.y + (Vs[i] - c) * x.y) * iR) - pv.y;
+          wp[e] = nv;
+          if (am) {
+            C sm = ss[i];
+            sm.x += b0r * pv.x - b0i * pv.y;
+            sm.y += b0r * pv.y + b0i * pv.x;
+            sm.x += b1r * x.x - b1i * x.y;
+            sm.y += b1r * x.y + b1i * x.x;
+            ap[e] = sm;
+          }
         }
       }
-    }
-  } else if constexpr (MODE == PLANE_INV_HPSI && E % NT_FFT == 0) {
-    // H psi = (T psi) + V psi: loads first, then the stores
+    });
+  } else if constexpr (MODE == PLANE_INV_HPSI) {
+    // H psi = (T psi) + V psi
     const C *xp = static_cast<const C *>(a.e.x) + v * a.ld_x + plane;
     const R *Vp = static_cast<const R *>(a.e.vloc) + plane;
     C *dp = static_cast<C *>(a.dst) + v * a.ld_dst + plane;
-    C xs[Q];
-    R Vs[Q];
+    s2.each(tid, [&](int q, int b) {
+      const int e0 = b;
+      constexpr int CX = R2 % 4 == 0 ? 4 : R2;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      xs[q] = xp[tid + q * NT_FFT];
-      Vs[q] = Vp[tid + q * NT_FFT];
-    }
+      for (int h = 0; h < R2 / CX; ++h) {
+        C xs[CX];
+        R Vs[CX];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int e = tid + q * NT_FFT;
-      C val = cconj(s[(e / NX) * P + (e % NX)]);
-      val.x += Vs[q] * xs[q].x;
-      val.y += Vs[q] * xs[q].y;
-      dp[e] = val;
-    }
-  } else {
+        for (int i = 0; i < CX; ++i) {
+          xs[i] = xp[e0 + (h * CX + i) * STEP];
+          Vs[i] = Vp[e0 + (h * CX + i) * STEP];
+        }
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int e = tid + q * NT_FFT;
-      if (E % NT_FFT == 0 || e < E) {
-        C val = s[(e / NX) * P + (e % NX)];
-        if (INV) val = cconj(val);
-        epilogue<R, MODE>(a, v, plane + e, val);
+        for (int i = 0; i < CX; ++i) {
+          C val = s2.v[q][h * CX + i];
+          val.x += Vs[i] * xs[i].x;
+          val.y += Vs[i] * xs[i].y;
+          dp[e0 + (h * CX + i) * STEP] = val;
+        }
       }
-    }
+    });
+  } else {
+    s2.each(tid, [&](int q, int b) {
+      const int e0 = b;
+#pragma unroll
+      for (int i = 0; i < R2; ++i) epilogue<R, MODE>(a, v, plane + e0 + i * STEP, s2.v[q][i]);
+    });
   }
 }
 
@@ -283,9 +326,10 @@ __device__ __forceinline__ cplx<R> kmul(const PassArgs &a, int ix, int iy, int i
   return m;
 }
 
-// Columns x0..x0+TX-1 of one (y or z) line family; NLEN = length of the axis.
+// y lines of grids whose planes do not fit: columns x0..x0+TX-1 of one xy
+// plane, in LDS.
 template <typename R, int NLEN, int TX>
-__global__ __launch_bounds__(NT_FFT) void k_pencil(PassArgs a) {
+__global__ __launch_bounds__(NT_FFT) void k_ypencil(PassArgs a) {
   using C = cplx<R>;
   constexpr int P = TX + 1;
   constexpr int E = NLEN * TX;
@@ -294,122 +338,153 @@ __global__ __launch_bounds__(NT_FFT) void k_pencil(PassArgs a) {
   const int tid = threadIdx.x;
   const int nxb = a.nx / TX;
   const int xb = blockIdx.x % nxb;
-  const int w = blockIdx.x / nxb;       // z (axis y) or y (axis z)
+  const int z = blockIdx.x / nxb;
   const int64_t v = a.rev ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
-  const int x0 = xb * TX;
-  const int64_t stride = a.axis == 2 ? (int64_t)a.nx * a.ny : (int64_t)a.nx;
-  const int64_t base = a.axis == 2 ? x0 + (int64_t)w * a.nx : x0 + (int64_t)w * a.nx * a.ny;
+  const int64_t stride = a.nx;
+  C *data = static_cast<C *>(a.dst) + v * a.ld_dst + xb * TX + (int64_t)z * a.nx * a.ny;
   for (int i = tid; i < NLEN; i += NT_FFT) tw[i] = static_cast<const C *>(a.tw0)[i];
-  // in place on dst, or from src (ld_src) into dst when src is given
-  C *data = static_cast<C *>(a.dst) + v * a.ld_dst + base;
-  const C *in = a.src ? static_cast<const C *>(a.src) + v * a.ld_src + base : data;
 #pragma unroll
   for (int q = 0; q < (E + NT_FFT - 1) / NT_FFT; ++q) {
     const int e = tid + q * NT_FFT;
     if (E % NT_FFT == 0 || e < E) {
-      C val = in[(e / TX) * stride + (e % TX)];
+      C val = data[(e / TX) * stride + (e % TX)];
       if (a.inverse) val = cconj(val);
       s[(e / TX) * P + (e % TX)] = val;
     }
   }
   __syncthreads();
   lds_fft<C, NLEN, TX, 1, P, true, NT_FFT>(s, tw, tid);
-  bool conj_out = a.inverse;
-  if (a.mul != MUL_NONE) {
-    // multiply in k space, then inverse transform as conj(FFT(conj))
-#pragma unroll
-    for (int q = 0; q < (E + NT_FFT - 1) / NT_FFT; ++q) {
-      const int e = tid + q * NT_FFT;
-      if (E % NT_FFT == 0 || e < E) {
-        const int j = e / TX, c = e % TX;
-        C m = kmul<R>(a, x0 + c, w, j);
-        C val = cmul(s[j * P + c], m);
-        s[j * P + c] = cconj(val);
-      }
-    }
-    __syncthreads();
-    lds_fft<C, NLEN, TX, 1, P, true, NT_FFT>(s, tw, tid);
-    conj_out = true;
-  }
 #pragma unroll
   for (int q = 0; q < (E + NT_FFT - 1) / NT_FFT; ++q) {
     const int e = tid + q * NT_FFT;
     if (E % NT_FFT == 0 || e < E) {
       C val = s[(e / TX) * P + (e % TX)];
-      if (conj_out) val = cconj(val);
+      if (a.inverse) val = cconj(val);
       data[(e / TX) * stride + (e % TX)] = val;
     }
   }
 }
 
-// ----------------------------------------------------------------- dispatch
-template <typename R> constexpr int plane_max_bytes() { return 64 * 1024 - 4096; }
+// z lines of TX neighbouring columns x0..x0+TX-1: forward transform, k-space
+// multiplier, inverse transform, with the points in registers.  The forward
+// transform's last stage (radix R2) leaves thread (c, k) the points k + i R1,
+// which are the ones a radix-R2 FIRST stage of the inverse needs, so the
+// multiplier and the turn to the inverse need no exchange: two exchanges
+// through LDS in all, where stages that start and end in LDS take seven.
+template <typename R, int N, int TX> struct PencilShape {
+  static constexpr int R2 = Radix<N>::R2;
+  // threads for the smaller count of butterflies, or (short FP64 lines) the larger
+  static constexpr int T = (TX * (sizeof(R) == 8 && N <= 64 ? Radix<N>::R1 : R2) + 63) / 64 * 64;
+  static constexpr int P = TX + 1;
+  static constexpr bool SPLIT = sizeof(R) == 8 && N > 64;
+};
 
-template <typename R, int N> constexpr bool plane_fits() {
-  return (int64_t)N * (N + 1) * sizeof(cplx<R>) + 2 * N * sizeof(cplx<R>) <= plane_max_bytes<R>();
+template <typename R, int N, int TX>
+__global__ __launch_bounds__((PencilShape<R, N, TX>::T)) void k_pencil(PassArgs a) {
+  using C = cplx<R>;
+  using Sh = PencilShape<R, N, TX>;
+  constexpr int R1 = Radix<N>::R1, R2 = Radix<N>::R2, P = Sh::P, T = Sh::T;
+  __shared__ R s[N * P * (Sh::SPLIT ? 1 : 2)];
+  __shared__ C tw[N];
+  const int tid = threadIdx.x;
+  const int nxb = a.nx / TX;
+  const int x0 = (blockIdx.x % nxb) * TX, y = blockIdx.x / nxb;
+  const int64_t v = a.rev ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+  const int64_t stride = (int64_t)a.nx * a.ny;
+  const int64_t base = x0 + (int64_t)y * a.nx;
+  // in place on dst, or from src (ld_src) into dst when src is given
+  C *data = static_cast<C *>(a.dst) + v * a.ld_dst + base;
+  const C *in = a.src ? static_cast<const C *>(a.src) + v * a.ld_src + base : data;
+  Stage<C, R1, TX * R2, T> s1;
+  Stage<C, R2, TX * R1, T> s2;
+  s1.each(tid, [&](int q, int b) {
+#pragma unroll
+    for (int i = 0; i < R1; ++i) s1.v[q][i] = in[(b / TX + i * R2) * stride + b % TX];
+  });
+  for (int i = tid; i < N; i += T) tw[i] = static_cast<const C *>(a.tw0)[i];
+  s1.dft(tid);
+  exchange<Sh::SPLIT, C>(
+      s, tid, s1, s2, true, [](int b, int i) { return ((b / TX) * R1 + i) * P + b % TX; },
+      [](int b, int i) { return (b / TX + i * R1) * P + b % TX; });
+  twiddle<C>(s2, tw, tid, [](int b) { return b / TX; });
+  s2.dft(tid);
+  s2.each(tid, [&](int q, int b) {
+#pragma unroll
+    for (int i = 0; i < R2; ++i)
+      s2.v[q][i] = cconj(cmul(s2.v[q][i], kmul<R>(a, x0 + b % TX, y, b / TX + i * R1)));
+  });
+  s2.dft(tid);
+  exchange<Sh::SPLIT, C>(
+      s, tid, s2, s1, false, [](int b, int i) { return ((b / TX) * R2 + i) * P + b % TX; },
+      [](int b, int i) { return (b / TX + i * R2) * P + b % TX; });
+  twiddle<C>(s1, tw, tid, [](int b) { return b / TX; });
+  s1.dft(tid);
+  s1.each(tid, [&](int q, int b) {
+#pragma unroll
+    for (int i = 0; i < R1; ++i) data[(b / TX + i * R2) * stride + b % TX] = cconj(s1.v[q][i]);
+  });
 }
 
+// ----------------------------------------------------------------- dispatch
 template <int N> constexpr int pencil_tx() { return N % 16 == 0 ? 16 : N % 8 == 0 ? 8 : 4; }
 // wider pencils (rows of 32 complex) where the length allows them
-template <int N> constexpr int pencil_tx_wide() { return N % 32 == 0 ? 32 : pencil_tx<N>(); }
+// wider pencils where the length allows them (nx a multiple of the width)
+template <typename R, int N> constexpr int pencil_tx_wide() {
+  constexpr bool D = sizeof(R) == 8;
+  return N % 32 == 0 ? 32 : N == 24 ? 24 : N == 40 ? 40 : N == 48 ? (D ? 24 : 48) : N == 56 ? (D ? 28 : 56)
+         : N == 80 ? 40 : pencil_tx<N>();
+}
 template <int N> constexpr int xlines_nl() { return N >= 2048 ? 1 : 2048 / N; }
 
-template <typename R, int N, int MODE> static void launch_plane(dim3 g, hipStream_t st,
-                                                              const PassArgs &a) {
-  if constexpr (plane_fits<R, N>())
-    hipLaunchKernelGGL((k_plane<R, N, N, MODE>), g, dim3(NT_FFT), 0, st, a);
+// the xy transform of a forward or inverse pass: planes where they fit, else x lines
+template <typename R, int N, int MODE> static void launch_xy(dim3 g, hipStream_t st,
+                                                             const PassArgs &a) {
+  if constexpr (PlaneShape<R, N>::fits)
+    hipLaunchKernelGGL((k_plane<R, N, MODE>), g, dim3(PlaneShape<R, N>::T), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_xlines<R, N, xlines_nl<N>(), MODE>), g, dim3(NT_FFT), 0, st, a);
 }
-template <typename R, int N, int MODE> static void launch_xlines(dim3 g, hipStream_t st,
+template <typename R, int N, int TX> static void launch_pencil(dim3 g, hipStream_t st,
                                                                const PassArgs &a) {
-  hipLaunchKernelGGL((k_xlines<R, N, xlines_nl<N>(), MODE>), g, dim3(NT_FFT), 0, st, a);
+  hipLaunchKernelGGL((k_pencil<R, N, TX>), g, dim3(PencilShape<R, N, TX>::T), 0, st, a);
 }
 
 template <typename R, int N> struct Kernels {
-  static void plane(dim3 g, hipStream_t st, const PassArgs &a) {
+  static void xy(dim3 g, hipStream_t st, const PassArgs &a) {
     switch (a.mode) {
-      case PLANE_FWD: launch_plane<R, N, PLANE_FWD>(g, st, a); break;
-      case PLANE_INV_STORE: launch_plane<R, N, PLANE_INV_STORE>(g, st, a); break;
-      case PLANE_INV_HPSI: launch_plane<R, N, PLANE_INV_HPSI>(g, st, a); break;
-      case PLANE_INV_CHEB: launch_plane<R, N, PLANE_INV_CHEB>(g, st, a); break;
-      case PLANE_INV_POISSON: launch_plane<R, N, PLANE_INV_POISSON>(g, st, a); break;
-      case PLANE_INV_SPLIT: launch_plane<R, N, PLANE_INV_SPLIT>(g, st, a); break;
+      case PLANE_FWD: launch_xy<R, N, PLANE_FWD>(g, st, a); break;
+      case PLANE_INV_STORE: launch_xy<R, N, PLANE_INV_STORE>(g, st, a); break;
+      case PLANE_INV_HPSI: launch_xy<R, N, PLANE_INV_HPSI>(g, st, a); break;
+      case PLANE_INV_CHEB: launch_xy<R, N, PLANE_INV_CHEB>(g, st, a); break;
+      case PLANE_INV_POISSON: launch_xy<R, N, PLANE_INV_POISSON>(g, st, a); break;
+      case PLANE_INV_SPLIT: launch_xy<R, N, PLANE_INV_SPLIT>(g, st, a); break;
     }
+  }
+  static void ypencil(dim3 g, hipStream_t st, const PassArgs &a) {
+    if constexpr (!PlaneShape<R, N>::fits)
+      hipLaunchKernelGGL((k_ypencil<R, N, pencil_tx<N>()>), g, dim3(NT_FFT), 0, st, a);
   }
   static void pencil(dim3 g, hipStream_t st, const PassArgs &a) {
-    hipLaunchKernelGGL((k_pencil<R, N, pencil_tx<N>()>), g, dim3(NT_FFT), 0, st, a);
+    launch_pencil<R, N, pencil_tx<N>()>(g, st, a);
   }
   static void pencil_wide(dim3 g, hipStream_t st, const PassArgs &a) {
-    hipLaunchKernelGGL((k_pencil<R, N, pencil_tx_wide<N>()>), g, dim3(NT_FFT), 0, st, a);
+    launch_pencil<R, N, pencil_tx_wide<R, N>()>(g, st, a);
   }
-  static void xlines(dim3 g, hipStream_t st, const PassArgs &a) {
-    switch (a.mode) {
-      case PLANE_FWD: launch_xlines<R, N, PLANE_FWD>(g, st, a); break;
-      case PLANE_INV_STORE: launch_xlines<R, N, PLANE_INV_STORE>(g, st, a); break;
-      case PLANE_INV_HPSI: launch_xlines<R, N, PLANE_INV_HPSI>(g, st, a); break;
-      case PLANE_INV_CHEB: launch_xlines<R, N, PLANE_INV_CHEB>(g, st, a); break;
-      case PLANE_INV_POISSON: launch_xlines<R, N, PLANE_INV_POISSON>(g, st, a); break;
-      case PLANE_INV_SPLIT: launch_xlines<R, N, PLANE_INV_SPLIT>(g, st, a); break;
-    }
-  }
-  static constexpr bool has_plane = plane_fits<R, N>();
-  static constexpr int tx = pencil_tx<N>();
-  static constexpr int tx_wide = pencil_tx_wide<N>();
-  static constexpr int nl = xlines_nl<N>();
 };
 
 struct SizeOps {
-  void (*plane)(dim3, hipStream_t, const PassArgs &);
+  void (*xy)(dim3, hipStream_t, const PassArgs &);
+  void (*ypencil)(dim3, hipStream_t, const PassArgs &);
   void (*pencil)(dim3, hipStream_t, const PassArgs &);
-  void (*xlines)(dim3, hipStream_t, const PassArgs &);
   void (*pencil_wide)(dim3, hipStream_t, const PassArgs &);
   bool has_plane;
   int tx, nl, tx_wide;
 };
 
 template <typename R, int N> SizeOps make_ops() {
-  return SizeOps{&Kernels<R, N>::plane, &Kernels<R, N>::pencil, &Kernels<R, N>::xlines,
-                 &Kernels<R, N>::pencil_wide, Kernels<R, N>::has_plane, Kernels<R, N>::tx,
-                 Kernels<R, N>::nl, Kernels<R, N>::tx_wide};
+  using K = Kernels<R, N>;
+  return SizeOps{&K::xy, &K::ypencil, &K::pencil, &K::pencil_wide, PlaneShape<R, N>::fits,
+                 pencil_tx<N>(), xlines_nl<N>(), pencil_tx_wide<R, N>()};
 }
 
 template <typename R> bool get_ops(int n, SizeOps &o) {
@@ -460,7 +535,7 @@ void fft3d_apply_t(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t 
   base.e = epi;
   const C *twx = tw, *twy = tw + ctx->nx, *twz = tw + ctx->nx + ctx->ny;
   hipStream_t st = ctx->stream;
-  const bool use_plane = ctx->nx == ctx->ny && ox.has_plane;
+  const bool use_plane = ox.has_plane;   // nx == ny (sgw_create refuses others)
   for (int64_t v0 = 0; v0 < nvec; v0 += 65535) {
     const int64_t nv = std::min<int64_t>(65535, nvec - v0);
     const C *srcv = static_cast<const C *>(src) + v0 * ld;
@@ -482,24 +557,22 @@ void fft3d_apply_t(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t 
     // successive passes run the vectors in alternate directions, each starting
     // on those the pass before wrote last
     int dir = rev ? 1 : 0;
+    const dim3 gxy(use_plane ? ctx->nz : (ctx->ny * ctx->nz + ox.nl - 1) / ox.nl, nv);
     f.src = srcv; f.dst = tmpv; f.ld_src = ld; f.ld_dst = ldt; f.mode = PLANE_FWD; f.inverse = 0;
     f.rev = dir;
-    if (use_plane) {
-      f.tw0 = twx; f.tw1 = twy;
-      ox.plane(dim3(ctx->nz, nv), st, f);
-    } else {
-      f.tw0 = twx;
-      ox.xlines(dim3((ctx->ny * ctx->nz + ox.nl - 1) / ox.nl, nv), st, f);
+    f.tw0 = twx;
+    ox.xy(gxy, st, f);
+    if (!use_plane) {
       PassArgs py = a;
-      py.dst = tmpv; py.ld_dst = ldt; py.axis = 1; py.tw0 = twy; py.inverse = 0; py.mul = MUL_NONE;
+      py.dst = tmpv; py.ld_dst = ldt; py.tw0 = twy; py.inverse = 0;
       dir ^= 1;
       py.rev = dir;
-      oy.pencil(dim3((ctx->nx / oy.tx) * ctx->nz, nv), st, py);
+      oy.ypencil(dim3((ctx->nx / oy.tx) * ctx->nz, nv), st, py);
     }
     SGW_HIP(hipGetLastError());
     // z: forward, multiply, inverse
     PassArgs pz = a;
-    pz.dst = tmp2v; pz.ld_dst = ldt; pz.axis = 2; pz.tw0 = twz; pz.inverse = 0; pz.mul = mul;
+    pz.dst = tmp2v; pz.ld_dst = ldt; pz.tw0 = twz; pz.mul = mul;
     if (tmp2) { pz.src = tmpv; pz.ld_src = ldt; }
     dir ^= 1;
     pz.rev = dir;
@@ -519,21 +592,16 @@ void fft3d_apply_t(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t 
     const bool timed = (ctx->ktimer & 1) && inv_mode == PLANE_INV_CHEB && ctx->ns.empty();
     if (!use_plane) {
       PassArgs py = a;
-      py.dst = tmp2v; py.ld_dst = ldt; py.axis = 1; py.tw0 = twy; py.inverse = 1; py.mul = MUL_NONE;
+      py.dst = tmp2v; py.ld_dst = ldt; py.tw0 = twy; py.inverse = 1;
       dir ^= 1;
       py.rev = dir;
-      oy.pencil(dim3((ctx->nx / oy.tx) * ctx->nz, nv), st, py);
+      oy.ypencil(dim3((ctx->nx / oy.tx) * ctx->nz, nv), st, py);
     }
     dir ^= 1;
     b.rev = dir;
     if (timed) SGW_HIP(hipEventRecord(ctx->kt[0].event(0), st));
-    if (use_plane) {
-      b.tw0 = twx; b.tw1 = twy;
-      ox.plane(dim3(ctx->nz, nv), st, b);
-    } else {
-      b.tw0 = twx;
-      ox.xlines(dim3((ctx->ny * ctx->nz + ox.nl - 1) / ox.nl, nv), st, b);
-    }
+    b.tw0 = twx;
+    ox.xy(gxy, st, b);
     if (timed) {
       SGW_HIP(hipEventRecord(ctx->kt[0].event(1), st));
       ctx->kt[0].used++;

@@ -83,6 +83,34 @@ def test_hpsi_si35h36_64(si35, prec):
     assert rel_err(got, ref) < 10 * TOL[prec]
 
 
+@pytest.mark.parametrize("prec", [sgw.SGW_C128, sgw.SGW_C64])
+@pytest.mark.parametrize("n,nz", [(8, 8), (12, 12), (16, 24), (24, 24), (32, 48), (48, 48), (56, 40),
+                                  (56, 56), (80, 40), (64, 64), (80, 80), (96, 32), (112, 56),
+                                  (112, 112), (128, 160), (160, 96)])
+def test_local_h_every_plane_and_pencil_shape(n, nz, prec):
+    """Local H psi of every xy plane size and of wide and narrow z pencils
+    (wide ones need a width that divides nx) against the same operator by
+    FP64 FFTs of torch, on an odd batch; same bounds as above."""
+    rs = np.random.default_rng(n + nz)
+    N, h, ecut = n * n * nz, 0.55, 9.0
+    v = rs.standard_normal(N)
+    ctx = sgw.Context((n, n, nz), h, v, None, precision=prec, ecut=ecut, max_nvec=2)
+    x = torch.from_numpy(rs.standard_normal((3, N)) + 1j * rs.standard_normal((3, N))).cuda()
+    x = x.to(ctx.cdtype)
+    y = torch.empty_like(x)
+    ctx.apply_H(x, y)
+    k = [2 * np.pi * torch.fft.fftfreq(m, d=h, dtype=torch.float64, device="cuda")
+         for m in (nz, n, n)]
+    T = 0.5 * (k[0][:, None, None] ** 2 + k[1][None, :, None] ** 2 + k[2] ** 2)
+    xr = x.to(torch.complex128).view(3, nz, n, n)
+    ref = torch.fft.ifftn(torch.fft.fftn(xr, dim=(1, 2, 3)) * T.clamp(max=ecut), dim=(1, 2, 3))
+    ref = ref.reshape(3, N) + torch.from_numpy(v).cuda() * x
+    ctx.close()
+    got, ref = y.cpu().numpy().astype(np.complex128), ref.cpu().numpy()
+    assert norm_err(got, ref) < TOL[prec]
+    assert row_max_err(got, ref) < 10 * TOL[prec]
+
+
 def test_hpsi_errors_and_empty(tiny8):
     s, H = tiny8
     ctx = make_ctx(s, sgw.SGW_C128)
