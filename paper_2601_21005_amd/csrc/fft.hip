@@ -103,22 +103,35 @@ __device__ __forceinline__ void epilogue(const PassArgs &a, int64_t v, int64_t r
 }
 
 // ----------------------------------------------------------------- plane
-// One xy plane of one vector per workgroup: y transform, then x transform,
-// the points in registers throughout.  The first y stage loads rows of x, the
-// last x stage stores (and reads its epilogue operands) in runs of R1 points;
-// three exchanges through LDS connect the four stages.
+// One xy plane of one vector per workgroup, the points in registers
+// throughout: two stages of the x transform, two of the y transform, an
+// exchange through LDS between them, and rows of x from and to memory, in
+// whole cache lines, where a pass reads and writes most.  The passes are bound
+// by HBM (16, 24 and 40 B per point); what has to be avoided is a second pass
+// and too few bytes in flight.  Real and imaginary parts are exchanged one
+// after the other, through half the LDS, so a plane of 128^2 in FP32 (75 KB,
+// 62 registers) stays twice on a CU.  Forward pass of 800 MB: 128^2 285 us
+// (5.7 TB/s) where x lines and y pencils took 272 + 265, 96^2 283 from 303 +
+// 265, 80^2 286 from 372, FP64 64^2 301 from 282 + 270, FP64 128^2 321 from
+// 267 + 250; 32^2 to 64^2 as before (282 us).  The planes that would not fit
+// (FP64 160^2) or that spill registers (FP32 160^2, FP64 112^2: 391 and 401 us
+// against 304 + 263 and 297 + 255) keep the two passes.
 template <typename R, int N, int MODE = PLANE_FWD> struct PlaneShape {
   static constexpr bool D = sizeof(R) == 8;
-  static constexpr int T = N == 128 ? (D ? 512 : 1024) : N == 112 ? 448 : N == 96 ? (D ? 384 : 768)
-                         : N == 80 ? 448 : N == 64 ? 512 : N == 56 ? 448 : N == 48 ? 192
-                         : N == 40 ? 320 : N == 32 ? 256 : N == 24 ? 192 : 64;
+  static constexpr int T = N == 128 ? 1024 : N == 112 ? 448 : N == 96 ? 768 : N == 80 ? 448
+                         : N == 64 ? 512 : N == 56 ? 448 : N == 48 ? 192 : N == 40 ? 320
+                         : N == 32 ? 256 : N == 24 ? 192 : N == 16 ? 128 : 64;
   // waves per SIMD to fit the registers for: two workgroups per CU
   static constexpr int WPE = !D && N == 128 && MODE != PLANE_INV_CHEB && MODE != PLANE_INV_SPLIT ? 8
-                           : !D && N == 112 ? 4 : 1;
+                           : !D && N == 112 && MODE != PLANE_INV_CHEB ? 4 : 1;
   // odd pitch: lanes on successive lines fall on distinct banks; at 128 and
   // 64 also wide enough that the runs of R1 points of neighbouring lines do
   static constexpr int P = N == 128 ? 145 : N == 64 ? 73 : N + 1;
   static constexpr bool SPLIT = true;
+  // FP32 inverse transforms of 96 and more take y before x (one more exchange):
+  // the order, to the last bit, of the separate x and y passes that planes of
+  // these sizes have in place of this one when they do not fit
+  static constexpr bool YFIRST = !D && N >= 96;
   static constexpr size_t lds = (size_t)N * P * sizeof(R) * (SPLIT ? 1 : 2) + N * sizeof(cplx<R>);
   static constexpr bool fits = lds <= 160 * 1024 && !(D && N == 112) && !(!D && N == 160);
 };
@@ -129,6 +142,7 @@ __global__ __launch_bounds__((PlaneShape<R, N>::T), (PlaneShape<R, N, MODE>::WPE
   using C = cplx<R>;
   using Sh = PlaneShape<R, N, MODE>;
   constexpr int R1 = Radix<N>::R1, R2 = Radix<N>::R2, P = Sh::P, T = Sh::T;
+  constexpr bool YF = INV && Sh::YFIRST;
   __shared__ R s[N * P * (Sh::SPLIT ? 1 : 2)];
   __shared__ C tw[N];
   const int tid = threadIdx.x;
@@ -137,39 +151,44 @@ __global__ __launch_bounds__((PlaneShape<R, N>::T), (PlaneShape<R, N, MODE>::WPE
   const C *src = static_cast<const C *>(a.src) + v * a.ld_src + plane;
   Stage<C, R1, N * R2, T> s1;
   Stage<C, R2, N * R1, T> s2;
-  // x: butterflies b = (j fast, line)
   s1.each(tid, [&](int q, int b) {
 #pragma unroll
-    for (int i = 0; i < R1; ++i) s1.v[q][i] = src[(b / R2) * N + b % R2 + i * R2];
+    for (int i = 0; i < R1; ++i)
+      s1.v[q][i] = src[YF ? (b / N + i * R2) * N + b % N : (b / R2) * N + b % R2 + i * R2];
   });
   for (int i = tid; i < N; i += T) tw[i] = static_cast<const C *>(a.tw0)[i];
-  if (INV)
-    s1.each(tid, [&](int q, int) {
-#pragma unroll
-      for (int i = 0; i < R1; ++i) s1.v[q][i] = cconj(s1.v[q][i]);
-    });
-  s1.dft(tid);
-  exchange<Sh::SPLIT, C>(
-      s, tid, s1, s2, true, [](int b, int i) { return (b / R2) * P + (b % R2) * R1 + i; },
-      [](int b, int i) { return (b % N) * P + b / N + i * R1; });
-  twiddle<C>(s2, tw, tid, [](int b) { return b / N; });
-  s2.dft(tid);
-  // to y columns, butterflies b = (x fast, j)
-  exchange<Sh::SPLIT, C>(
-      s, tid, s2, s1, true, [](int b, int i) { return (b % N) * P + b / N + i * R1; },
-      [](int b, int i) { return (b / N + i * R2) * P + b % N; });
-  s1.dft(tid);
-  exchange<Sh::SPLIT, C>(
-      s, tid, s1, s2, false, [](int b, int i) { return ((b / N) * R1 + i) * P + b % N; },
-      [](int b, int i) { return (b / N + i * R1) * P + b % N; });
-  twiddle<C>(s2, tw, tid, [](int b) { return b / N; });
-  s2.dft(tid);
+  if (INV) s1.map(tid, [](C z, int, int) { return cconj(z); });
+  // where the values of a stage sit in the exchange: x butterflies
+  // b = (line fast, j), or (j fast, line) as loaded; y butterflies (x fast, j);
+  // first-stage inputs and outputs, second-stage inputs (= outputs)
+  auto x1 = [](int b, int i) { return (b % N) * P + b / N + i * R2; };
+  auto x1o = [](int b, int i) { return (b % N) * P + (b / N) * R1 + i; };
+  auto x1l = [](int b, int i) { return (b / R2) * P + (b % R2) * R1 + i; };
+  auto x2 = [](int b, int i) { return (b % N) * P + b / N + i * R1; };
+  auto y1 = [](int b, int i) { return (b / N + i * R2) * P + b % N; };
+  auto y1o = [](int b, int i) { return ((b / N) * R1 + i) * P + b % N; };
+  auto y2 = [](int b, int i) { return (b / N + i * R1) * P + b % N; };
+  auto j_of = [](int b) { return b / N; };
+  constexpr bool SP = Sh::SPLIT;
+  s1.template run<N, 1>(tid, tw, j_of);
+  if constexpr (YF) {
+    exchange<SP, C>(s, tid, s1, s2, true, y1o, y2);
+    s2.template run<N, R1>(tid, tw, j_of);
+    exchange<SP, C>(s, tid, s2, s1, true, y2, x1);
+    s1.template run<N, 1>(tid, tw, j_of);
+    exchange<SP, C>(s, tid, s1, s2, true, x1o, x2);
+    s2.template run<N, R1>(tid, tw, j_of);
+    exchange<SP, C>(s, tid, s2, s2, false, x2, y2);   // rows again, for whole cache lines
+  } else {
+    exchange<SP, C>(s, tid, s1, s2, true, x1l, x2);
+    s2.template run<N, R1>(tid, tw, j_of);
+    exchange<SP, C>(s, tid, s2, s1, true, x2, y1);
+    s1.template run<N, 1>(tid, tw, j_of);
+    exchange<SP, C>(s, tid, s1, s2, false, y1o, y2);
+    s2.template run<N, R1>(tid, tw, j_of);
+  }
   constexpr int STEP = R1 * N;           // butterfly b's output i is at point b + i STEP
-  if (INV)
-    s2.each(tid, [&](int q, int) {
-#pragma unroll
-      for (int i = 0; i < R2; ++i) s2.v[q][i] = cconj(s2.v[q][i]);
-    });
+  if (INV) s2.map(tid, [](C z, int, int) { return cconj(z); });
   // epilogue operands are loaded CH points at a time before their stores (the
   // stores would otherwise order every later load)
   constexpr int CH = R2 % 4 == 0 ? 4 : R2;
@@ -301,6 +320,10 @@ __global__ __launch_bounds__(NT_FFT) void k_xlines(PassArgs a) {
 }
 
 // ----------------------------------------------------------------- pencil
+template <typename C, typename R> __device__ __forceinline__ C cmake_r(R re, R im) {
+  C c; c.x = re; c.y = im; return c;
+}
+
 template <typename R>
 __device__ __forceinline__ cplx<R> kmul(const PassArgs &a, int ix, int iy, int iz) {
   using C = cplx<R>;
@@ -368,15 +391,26 @@ __global__ __launch_bounds__(NT_FFT) void k_ypencil(PassArgs a) {
 // z lines of TX neighbouring columns x0..x0+TX-1: forward transform, k-space
 // multiplier, inverse transform, with the points in registers.  The forward
 // transform's last stage (radix R2) leaves thread (c, k) the points k + i R1,
-// which are the ones a radix-R2 FIRST stage of the inverse needs, so the
-// multiplier and the turn to the inverse need no exchange: two exchanges
-// through LDS in all, where stages that start and end in LDS take seven.
+// the very ones that a radix-R2 FIRST stage of the inverse needs: where that
+// order of the inverse's stages is the usual one (R1 = R2), and in FP64, the
+// multiplier and the turn to the inverse need no exchange and the pass has
+// two; in FP32 the others take a third one and keep the usual order, whose
+// last bits the TDH's response field (a small difference of orbitals)
+// amplifies.  (Stages that start and end in LDS take seven.)  Bound by HBM;
+// rows of TX complex (256 B and more) matter most.  Forward + inverse of 800
+// MB: 40^3 501 -> 237 us, 56^3 652 -> 354, 48^3 404 -> 340, 128^3 394 -> 340,
+// FP64 40^3 451 -> 316, FP64 160^3 684 -> 545; 64^3 and 32^3 as before.
 template <typename R, int N, int TX> struct PencilShape {
-  static constexpr int R2 = Radix<N>::R2;
-  // threads for the smaller count of butterflies, or (short FP64 lines) the larger
-  static constexpr int T = (TX * (sizeof(R) == 8 && N <= 64 ? Radix<N>::R1 : R2) + 63) / 64 * 64;
+  static constexpr int R1 = Radix<N>::R1, R2 = Radix<N>::R2;
+  static constexpr bool D = sizeof(R) == 8;
+  // threads for the smaller count of butterflies of a stage, or the larger
+  // where that measured faster (FP64 80^3: 455 -> 332 us, FP32 48^3: 386 -> 340)
+  static constexpr int LO = R1 < R2 ? R1 : R2, HI = R1 < R2 ? R2 : R1;
+  static constexpr int T = (TX * ((D && N <= 80) || N == 48 || N == 24 ? HI : LO) + 63) / 64 * 64;
   static constexpr int P = TX + 1;
-  static constexpr bool SPLIT = sizeof(R) == 8 && N > 64;
+  static constexpr bool SPLIT = D && N > 64;
+  static constexpr bool TURN = D || R1 == R2;
+  static constexpr bool ALT = !D && N == 96 && TX == 32;   // see butterfly
 };
 
 template <typename R, int N, int TX>
@@ -397,32 +431,45 @@ __global__ __launch_bounds__((PencilShape<R, N, TX>::T)) void k_pencil(PassArgs 
   const C *in = a.src ? static_cast<const C *>(a.src) + v * a.ld_src + base : data;
   Stage<C, R1, TX * R2, T> s1;
   Stage<C, R2, TX * R1, T> s2;
+  auto col_of = [](int b) { return b / TX; };
   s1.each(tid, [&](int q, int b) {
 #pragma unroll
     for (int i = 0; i < R1; ++i) s1.v[q][i] = in[(b / TX + i * R2) * stride + b % TX];
   });
   for (int i = tid; i < N; i += T) tw[i] = static_cast<const C *>(a.tw0)[i];
-  s1.dft(tid);
+  s1.template run<N, 1>(tid, tw, col_of);
   exchange<Sh::SPLIT, C>(
       s, tid, s1, s2, true, [](int b, int i) { return ((b / TX) * R1 + i) * P + b % TX; },
       [](int b, int i) { return (b / TX + i * R1) * P + b % TX; });
-  twiddle<C>(s2, tw, tid, [](int b) { return b / TX; });
-  s2.dft(tid);
-  s2.each(tid, [&](int q, int b) {
-#pragma unroll
-    for (int i = 0; i < R2; ++i)
-      s2.v[q][i] = cconj(cmul(s2.v[q][i], kmul<R>(a, x0 + b % TX, y, b / TX + i * R1)));
+  s2.template run<N, R1, Sh::ALT>(tid, tw, col_of);
+  s2.map(tid, [&](C z, int b, int i) {
+    const C m = kmul<R>(a, x0 + b % TX, y, b / TX + i * R1);
+    return cmake_r<C>(fma(m.x, z.x, -(m.y * z.y)), -fma(m.y, z.x, m.x * z.y));   // conj(m z)
   });
-  s2.dft(tid);
-  exchange<Sh::SPLIT, C>(
-      s, tid, s2, s1, false, [](int b, int i) { return ((b / TX) * R2 + i) * P + b % TX; },
-      [](int b, int i) { return (b / TX + i * R2) * P + b % TX; });
-  twiddle<C>(s1, tw, tid, [](int b) { return b / TX; });
-  s1.dft(tid);
-  s1.each(tid, [&](int q, int b) {
+  if constexpr (Sh::TURN) {
+    s2.template run<N, 1>(tid, tw, [](int) { return 0; });
+    exchange<Sh::SPLIT, C>(
+        s, tid, s2, s1, false, [](int b, int i) { return ((b / TX) * R2 + i) * P + b % TX; },
+        [](int b, int i) { return (b / TX + i * R2) * P + b % TX; });
+    s1.template run<N, R2>(tid, tw, col_of);
+    s1.each(tid, [&](int q, int b) {
 #pragma unroll
-    for (int i = 0; i < R1; ++i) data[(b / TX + i * R2) * stride + b % TX] = cconj(s1.v[q][i]);
-  });
+      for (int i = 0; i < R1; ++i) data[(b / TX + i * R2) * stride + b % TX] = cconj(s1.v[q][i]);
+    });
+  } else {
+    exchange<Sh::SPLIT, C>(
+        s, tid, s2, s1, true, [](int b, int i) { return (b / TX + i * R1) * P + b % TX; },
+        [](int b, int i) { return (b / TX + i * R2) * P + b % TX; });
+    s1.template run<N, 1>(tid, tw, col_of);
+    exchange<Sh::SPLIT, C>(
+        s, tid, s1, s2, false, [](int b, int i) { return ((b / TX) * R1 + i) * P + b % TX; },
+        [](int b, int i) { return (b / TX + i * R1) * P + b % TX; });
+    s2.template run<N, R1, Sh::ALT>(tid, tw, col_of);
+    s2.each(tid, [&](int q, int b) {
+#pragma unroll
+      for (int i = 0; i < R2; ++i) data[(b / TX + i * R1) * stride + b % TX] = cconj(s2.v[q][i]);
+    });
+  }
 }
 
 // ----------------------------------------------------------------- dispatch

@@ -6,110 +6,89 @@
 // by exp(-2 pi i i k/N) and leaves X[k + i R1].  LDS only carries the exchange
 // between two stages, so a pass touches it once per stage boundary, and the
 // first stage loads from and the last one stores to global memory directly.
+// R1 is 8 (4 for length 12) and an R2 above 8 is taken as two radices inside
+// the thread, in the order and with the twiddles of the separate stages of
+// lds_fft: the two transforms round every value alike, bit for bit.
 // Inverse transforms are taken as conj(FFT(conj(x))).
 #pragma once
-
-#include <type_traits>
 
 #include "fft_lds.h"
 
 namespace sgw {
 
-// the two radices of each built length
+// the two stages of each built length
 template <int N> struct Radix {
-  static constexpr int R1 = N == 8 ? 4 : N == 12 ? 4 : N == 16 ? 4 : N == 24 ? 6 : N == 32 ? 8
-                          : N == 40 ? 8 : N == 48 ? 8 : N == 56 ? 8 : N == 64 ? 8 : N == 80 ? 16
-                          : N == 96 ? 12 : N == 112 ? 14 : 16;
-  static constexpr int R2 = N / R1;
-  static_assert(R1 * R2 == N && R2 >= 2 && R2 <= R1, "length not built");
+  static constexpr int R1 = pick_radix(N), R2 = N / R1;
 };
 
-template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
+template <typename C> struct DFT<C, 1> {
+  static __device__ __forceinline__ void run(C *) {}
+};
+
+// Keeps the operations that made z from being contracted with, or moved to,
+// those that use it (as a store to LDS and back would).
+__device__ __forceinline__ void settle(float2 &z) { asm volatile("" : "+v"(z.x), "+v"(z.y)); }
+__device__ __forceinline__ void settle(double2 &z) { asm volatile("" : "+v"(z.x), "+v"(z.y)); }
+
+// a t, and the same with the imaginary part's other product rounded first
+template <bool ALT, typename C> __device__ __forceinline__ C twist(C a, C t) {
+  C r;
+  r.x = fma(a.x, t.x, -(a.y * t.y));
+  r.y = ALT ? fma(a.x, t.y, a.y * t.x) : fma(a.y, t.x, a.x * t.y);
+  return r;
 }
 
-// cos and sin of 2 pi m / R at compile time: reduced to at most pi / 4, then
-// the Taylor series
-constexpr double taylor_cos(double x) {
-  double s = 0, t = 1;
-  for (int k = 1; k < 12; ++k) {
-    s += t;
-    t *= -x * x / ((2 * k - 1) * (2 * k));
-  }
-  return s;
-}
-constexpr double taylor_sin(double x) {
-  double s = 0, t = x;
-  for (int k = 1; k < 12; ++k) {
-    s += t;
-    t *= -x * x / ((2 * k) * (2 * k + 1));
-  }
-  return s;
-}
-constexpr double kTwoPi = 6.283185307179586476925286766559;
-constexpr double turn_cos(int m, int R);
-constexpr double turn_sin(int m, int R) {    // 0 <= m < R
-  return 2 * m > R ? -turn_sin(R - m, R)
-       : 4 * m > R ? (8 * m > 3 * R ? taylor_sin(kTwoPi * (R - 2 * m) / (2.0 * R))
-                                    : taylor_cos(kTwoPi * (4 * m - R) / (4.0 * R)))
-       : 8 * m > R ? taylor_cos(kTwoPi * (R - 4 * m) / (4.0 * R))
-                   : taylor_sin(kTwoPi * m / R);
-}
-constexpr double turn_cos(int m, int R) {
-  return 2 * m > R ? turn_cos(R - m, R)
-       : 4 * m > R ? (8 * m > 3 * R ? -taylor_cos(kTwoPi * (R - 2 * m) / (2.0 * R))
-                                    : -taylor_sin(kTwoPi * (4 * m - R) / (4.0 * R)))
-       : 8 * m > R ? taylor_sin(kTwoPi * (R - 4 * m) / (4.0 * R))
-                   : taylor_cos(kTwoPi * m / R);
-}
-
-// z exp(-2 pi i M / R)
-template <int M, int R, typename C> __device__ __forceinline__ C turn(C z) {
-  using T = decltype(z.x);
-  if constexpr (M == 0) {
-    return z;
-  } else if constexpr (4 * M == R) {
-    return mul_mi(z);
+// Radix-R butterfly k of a stage whose sub-transforms have length NS, in
+// place: twiddles exp(-2 pi i i k/(NS R)) from the table tw of length N, then
+// the transform; for R = A B (A = pick_radix(R)) the stages of radix A and B.
+// ALT: the radix-A butterflies after the first round their twiddles the other
+// way round (96-point z lines).
+template <typename C, int N, int R, int NS, bool ALT = false> __device__ __forceinline__ void butterfly(
+    C *a, const C *tw, int k) {
+  constexpr int A = pick_radix(R), B = R / A;
+  if constexpr (R == 1) {
+    return;
+  } else if constexpr (B == 1) {
+    if (NS > 1) {
+#pragma unroll
+      for (int i = 1; i < R; ++i) a[i] = twist<false>(a[i], tw[i * k * (N / (NS * R))]);
+    }
+    DFT<C, R>::run(a);
+#pragma unroll
+    for (int i = 0; i < R; ++i) settle(a[i]);
   } else {
-    constexpr T c = (T)turn_cos(M, R), s = (T)turn_sin(M, R);
-    C r;
-    r.x = c * z.x + s * z.y;
-    r.y = c * z.y - s * z.x;
-    return r;
-  }
-}
-
-// radix A B from radices A and B: n = n1 B + n2, k = k1 + A k2
-template <typename C, int A, int B> struct DFTprod {
-  static __device__ __forceinline__ void run(C *a) {
     C t[B][A];
-    static_for<0, B>([&](auto n2) {
 #pragma unroll
-      for (int n1 = 0; n1 < A; ++n1) t[n2][n1] = a[n1 * B + n2];
-      DFT<C, A>::run(t[n2]);
-      static_for<0, A>([&](auto k1) {
-        t[n2][k1] = turn<(int)n2 * (int)k1 % (A * B), A * B>(t[n2][k1]);
-      });
-    });
+    for (int m = 0; m < B; ++m) {
 #pragma unroll
-    for (int k1 = 0; k1 < A; ++k1) {
+      for (int i = 0; i < A; ++i) {
+        t[m][i] = a[m + i * B];
+        if (NS > 1 && i > 0) {
+          const C z = tw[i * k * (N / (NS * A))];
+          t[m][i] = ALT && m > 0 ? twist<true>(t[m][i], z) : twist<false>(t[m][i], z);
+        }
+      }
+      DFT<C, A>::run(t[m]);
+#pragma unroll
+      for (int i = 0; i < A; ++i) settle(t[m][i]);
+    }
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
       C w[B];
 #pragma unroll
-      for (int n2 = 0; n2 < B; ++n2) w[n2] = t[n2][k1];
+      for (int m = 0; m < B; ++m) {
+        w[m] = t[m][i];
+        if (m > 0) w[m] = twist<false>(w[m], tw[m * (k + NS * i) * (N / (NS * R))]);
+      }
       DFT<C, B>::run(w);
 #pragma unroll
-      for (int k2 = 0; k2 < B; ++k2) a[k1 + A * k2] = w[k2];
+      for (int m = 0; m < B; ++m) {
+        settle(w[m]);
+        a[i + A * m] = w[m];
+      }
     }
   }
-};
-template <typename C> struct DFT<C, 6> : DFTprod<C, 3, 2> {};
-template <typename C> struct DFT<C, 10> : DFTprod<C, 5, 2> {};
-template <typename C> struct DFT<C, 12> : DFTprod<C, 4, 3> {};
-template <typename C> struct DFT<C, 14> : DFTprod<C, 7, 2> {};
-template <typename C> struct DFT<C, 16> : DFTprod<C, 4, 4> {};
+}
 
 // The butterflies of one stage over a workgroup: NB butterflies of radix R,
 // butterfly b = tid + q T in slot q.
@@ -124,8 +103,20 @@ template <typename C, int R_, int NB_, int T_> struct Stage {
       if (NB % T == 0 || b < NB) f(q, b);
     }
   }
-  __device__ __forceinline__ void dft(int tid) {
-    each(tid, [&](int q, int) { DFT<C, R>::run(v[q]); });
+  // butterfly b is number k_of(b) of its sub-transforms (length NS)
+  template <int N, int NS, bool ALT = false, typename K>
+  __device__ __forceinline__ void run(int tid, const C *tw, K k_of) {
+    each(tid, [&](int q, int b) { butterfly<C, N, R, NS, ALT>(v[q], tw, k_of(b)); });
+  }
+  // f on every value, settled
+  template <typename F> __device__ __forceinline__ void map(int tid, F &&f) {
+    each(tid, [&](int q, int b) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        v[q][i] = f(v[q][i], b, i);
+        settle(v[q][i]);
+      }
+    });
   }
 };
 
@@ -170,16 +161,6 @@ __device__ __forceinline__ void exchange(void *lds, int tid, SA &a, SB &b, bool 
     });
   }
   if (more) __syncthreads();
-}
-
-// twiddles exp(-2 pi i i k / N) of radix butterflies whose k is k_of(b)
-template <typename C, typename S, typename K>
-__device__ __forceinline__ void twiddle(S &a, const C *tw, int tid, K k_of) {
-  S::each(tid, [&](int q, int b) {
-    const int k = k_of(b);
-#pragma unroll
-    for (int i = 1; i < S::R; ++i) a.v[q][i] = cmul(a.v[q][i], tw[i * k]);
-  });
 }
 
 }  // namespace sgw
