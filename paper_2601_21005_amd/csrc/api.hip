@@ -784,52 +784,39 @@ sgw_status sgw_lanczos_bounds(sgw_ctx *ctx, int32_t k, uint64_t seed, double pad
     const size_t cs = ctx->csize();
     void *v = ctx->buf("lz_v", cs * N).p, *vp = ctx->buf("lz_vp", cs * N).p;
     void *w = ctx->buf("lz_w", cs * N).p;
-    double *d = ctx->buf("lz_dot", sizeof(double)).as<double>();
-    auto fetch = [&]() {
-      double x = 0;
-      SGW_HIP(hipMemcpyAsync(&x, d, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-      SGW_HIP(hipStreamSynchronize(ctx->stream));
-      return x;
-    };
+    double *partial = ctx->buf("lz_partial", sizeof(double) * 2 * lanczos_blocks(ctx)).as<double>();
+    double *coef = ctx->buf("lz_coef", sizeof(double) * (2 * k + 1)).as<double>();
     // start: +-1 white noise of stream (BOUNDS, 0, 0), unit Euclidean norm
     const uint64_t key = rng_key(seed, rng_stream(RNG_BOUNDS, 0, 0));
     DevBuf &dk = ctx->buf("lz_key", sizeof(uint64_t));
     SGW_HIP(hipMemcpyAsync(dk.p, &key, sizeof key, hipMemcpyHostToDevice, ctx->stream));
-    launch_fill_noise(ctx, dk.as<uint64_t>(), 1, v);
-    launch_norm2(ctx, v, N, 1, d);
-    launch_scale_copy(ctx, v, N, v, N, 1, 1.0 / std::sqrt(fetch()), 0.0);
-    launch_scale_copy(ctx, v, N, vp, N, 1, 0.0, 0.0);
-    std::vector<double> alpha, beta;
-    double b = 0;
+    launch_fill_noise(ctx, dk.as<uint64_t>(), 1, w);
+    launch_lanczos_start(ctx, v, vp, w, coef + k, partial);
     for (int j = 0; j < k; ++j) {
       apply_h(ctx, v, w, 1, N);
-      launch_redot(ctx, v, w, N, 1, d);
-      const double a = fetch();
-      launch_axpy(ctx, v, N, w, N, 1, -a, 0.0);
-      launch_axpy(ctx, vp, N, w, N, 1, -b, 0.0);
-      launch_norm2(ctx, w, N, 1, d);
-      b = std::sqrt(fetch());
+      launch_lanczos_step(ctx, v, vp, w, coef + j, coef + k + j, partial);
+    }
+    std::vector<double> c(2 * k + 1);
+    SGW_HIP(hipMemcpyAsync(c.data(), coef, sizeof(double) * c.size(), hipMemcpyDeviceToHost,
+                           ctx->stream));
+    SGW_HIP(hipStreamSynchronize(ctx->stream));
+    std::vector<double> alpha, beta;
+    for (int j = 0; j < k; ++j) {
+      const double a = c[j], b = c[k + 1 + j];
       SGW_REQUIRE(std::isfinite(a) && std::isfinite(b), SGW_EDIVERGED, "Lanczos produced a non-finite value");
       alpha.push_back(a);
       beta.push_back(b);
       if (b == 0) break;
-      launch_copy(ctx, v, N, vp, N, 1);
-      launch_scale_copy(ctx, w, N, v, N, 1, 1.0 / b, 0.0);
     }
     const int n = (int)alpha.size();
-    std::vector<double> T((size_t)n * n, 0.0), vals, vecs;
-    for (int i = 0; i < n; ++i) {
-      T[(size_t)i * n + i] = alpha[i];
-      if (i + 1 < n) T[(size_t)i * n + i + 1] = T[(size_t)(i + 1) * n + i] = beta[i];
-    }
-    jacobi_eigen(n, T, vals, vecs);
-    const double r0 = beta[n - 1] * std::fabs(vecs[(size_t)(n - 1) * n + 0]);
-    const double r1 = beta[n - 1] * std::fabs(vecs[(size_t)(n - 1) * n + n - 1]);
-    const double width = vals[n - 1] - vals[0];
+    double th0, th1, y0, y1;              // extreme Ritz values, last eigenvector components
+    tridiagonal_extremes(alpha, beta, th0, th1, y0, y1);
+    const double r0 = beta[n - 1] * std::fabs(y0), r1 = beta[n - 1] * std::fabs(y1);
+    const double width = th1 - th0;
     double lo_w = 0, hi_w = 0;
     weyl_bounds(ctx, 0.0, lo_w, hi_w);
-    *emin = std::max(lo_w, vals[0] - r0 - pad * width);
-    *emax = std::min(hi_w, vals[n - 1] + r1 + pad * width);
+    *emin = std::max(lo_w, th0 - r0 - pad * width);
+    *emax = std::min(hi_w, th1 + r1 + pad * width);
   });
 }
 

@@ -332,9 +332,14 @@ void kb_upload_operands(sgw_ctx *ctx);
 
 // host utilities (host.cpp)
 // eigenvalues (ascending) and eigenvectors (columns, row-major) of a small
-// symmetric matrix (row-major, destroyed)
+// symmetric matrix (row-major, destroyed); the check of tridiagonal_extremes
 void jacobi_eigen(int n, std::vector<double> &a, std::vector<double> &vals,
                   std::vector<double> &vecs);
+// lowest and highest eigenvalue of the symmetric tridiagonal matrix with
+// diagonal a [n] and off-diagonal b[0 .. n - 2], and the last component of
+// their unit eigenvectors
+void tridiagonal_extremes(const std::vector<double> &a, const std::vector<double> &b, double &lo,
+                          double &hi, double &last_lo, double &last_hi);
 void build_kb(sgw_ctx *ctx, const sgw_projectors *p);
 // K (complex, [nproj][nproj] interleaved) with exp(-i tau V_NL) = I + dV B K B^T
 void kb_exponential_matrix(const sgw_ctx *ctx, double tau, std::vector<double> &K);

@@ -245,6 +245,123 @@ void launch_redot(sgw_ctx *ctx, const void *a, const void *b, int64_t ld, int64_
   reduce<RED_REDOT>(ctx, a, b, ld, nf, d_out);
 }
 
+// ============================================================ Lanczos
+// One Lanczos step after w = H v, its two scalars left on the device: every
+// workgroup sums the partial sums of the kernel before it (one wave, FP64),
+// so a step is three launches beside those of H and the host waits once at
+// the end.  (Fetching a = <v|w> and b = |w| to the host took two
+// synchronisations and ten launches a step: 60 steps at 64^3 10.7 ms, 3 of
+// them in an eigensolver for all Ritz pairs on the host; now 3.8.)
+
+// sum of partial[0 .. nblk - 1] on every thread
+__device__ __forceinline__ double partial_total(const double *partial, int nblk, double *sh) {
+  if (threadIdx.x < 64) {
+    double s = 0;
+    for (int i = threadIdx.x; i < nblk; i += 64) s += partial[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0) sh[0] = s;
+  }
+  __syncthreads();
+  const double t = sh[0];
+  __syncthreads();
+  return t;
+}
+
+// a = sum of dots; w <- w - a v - b vp (b: the norm of the step before);
+// norms[block] = |w|^2 of the block's points
+template <typename R>
+__global__ __launch_bounds__(NT) void k_lanczos_update(const cplx<R> *v, const cplx<R> *vp,
+                                                       cplx<R> *w, int64_t N, const double *dots,
+                                                       int nblk, double *alpha, const double *b,
+                                                       double *norms) {
+  __shared__ double sh[NT];
+  const double a = partial_total(dots, nblk, sh);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
+  const R ca = (R)-a, cb = (R)-*b;
+  const int64_t r0 = (int64_t)blockIdx.x * RCHUNK, r1 = std::min<int64_t>(N, r0 + RCHUNK);
+  double acc = 0;
+  for (int64_t r = r0 + threadIdx.x; r < r1; r += NT) {
+    const cplx<R> x = v[r], y = vp[r];
+    cplx<R> o = w[r];
+    o.x += ca * x.x;
+    o.y += ca * x.y;
+    o.x += cb * y.x;
+    o.y += cb * y.y;
+    w[r] = o;
+    acc += (double)o.x * o.x + (double)o.y * o.y;
+  }
+  const double s = block_sum(acc, sh);
+  if (threadIdx.x == 0) norms[blockIdx.x] = s;
+}
+
+// b = sqrt(sum of norms); vp <- v (0 on the first call), v <- w / b (0 where b = 0)
+template <typename R>
+__global__ __launch_bounds__(NT) void k_lanczos_next(cplx<R> *v, cplx<R> *vp, const cplx<R> *w,
+                                                     int64_t N, const double *norms, int nblk,
+                                                     double *beta, int first) {
+  __shared__ double sh[NT];
+  const double b = sqrt(partial_total(norms, nblk, sh));
+  if (blockIdx.x == 0 && threadIdx.x == 0) *beta = first ? 0.0 : b;
+  const R inv = b > 0 ? (R)(1.0 / b) : (R)0;
+  const int64_t r0 = (int64_t)blockIdx.x * RCHUNK, r1 = std::min<int64_t>(N, r0 + RCHUNK);
+  for (int64_t r = r0 + threadIdx.x; r < r1; r += NT) {
+    const cplx<R> x = w[r];
+    cplx<R> old;
+    old.x = old.y = 0;
+    if (!first) old = v[r];
+    vp[r] = old;
+    v[r] = cscale(x, inv);
+  }
+}
+
+template <typename R>
+static void lanczos_norm_t(sgw_ctx *ctx, const void *w, double *norms, int nblk) {
+  hipLaunchKernelGGL((k_reduce1<R, RED_NORM2>), dim3(nblk, 1), dim3(NT), 0, ctx->stream,
+                     static_cast<const cplx<R> *>(w), static_cast<const cplx<R> *>(nullptr),
+                     ctx->N, ctx->N, norms, nblk);
+}
+
+int lanczos_blocks(const sgw_ctx *ctx) { return (int)((ctx->N + RCHUNK - 1) / RCHUNK); }
+
+template <typename R>
+static void lanczos_start_t(sgw_ctx *ctx, void *v, void *vp, void *w, double *beta,
+                            double *partial) {
+  const int nblk = lanczos_blocks(ctx);
+  lanczos_norm_t<R>(ctx, w, partial + nblk, nblk);
+  hipLaunchKernelGGL(k_lanczos_next<R>, dim3(nblk), dim3(NT), 0, ctx->stream,
+                     static_cast<cplx<R> *>(v), static_cast<cplx<R> *>(vp),
+                     static_cast<const cplx<R> *>(w), ctx->N, partial + nblk, nblk, beta, 1);
+}
+
+template <typename R>
+static void lanczos_step_t(sgw_ctx *ctx, void *v, void *vp, void *w, double *alpha, double *beta,
+                           double *partial) {
+  const int nblk = lanczos_blocks(ctx);
+  cplx<R> *V = static_cast<cplx<R> *>(v), *P = static_cast<cplx<R> *>(vp);
+  cplx<R> *W = static_cast<cplx<R> *>(w);
+  hipLaunchKernelGGL((k_reduce1<R, RED_REDOT>), dim3(nblk, 1), dim3(NT), 0, ctx->stream, V, W,
+                     ctx->N, ctx->N, partial, nblk);
+  hipLaunchKernelGGL(k_lanczos_update<R>, dim3(nblk), dim3(NT), 0, ctx->stream, V, P, W, ctx->N,
+                     partial, nblk, alpha, beta, partial + nblk);
+  hipLaunchKernelGGL(k_lanczos_next<R>, dim3(nblk), dim3(NT), 0, ctx->stream, V, P, W, ctx->N,
+                     partial + nblk, nblk, beta + 1, 0);
+}
+
+void launch_lanczos_start(sgw_ctx *ctx, void *v, void *vp, void *w, double *beta,
+                          double *partial) {
+  if (ctx->dbl) lanczos_start_t<double>(ctx, v, vp, w, beta, partial);
+  else lanczos_start_t<float>(ctx, v, vp, w, beta, partial);
+  SGW_HIP(hipGetLastError());
+}
+
+void launch_lanczos_step(sgw_ctx *ctx, void *v, void *vp, void *w, double *alpha, double *beta,
+                         double *partial) {
+  if (ctx->dbl) lanczos_step_t<double>(ctx, v, vp, w, alpha, beta, partial);
+  else lanczos_step_t<float>(ctx, v, vp, w, alpha, beta, partial);
+  SGW_HIP(hipGetLastError());
+}
+
 // ============================================================ white noise
 template <typename R>
 __global__ void k_fill_noise(const uint64_t *keys, int64_t nr, int64_t N, R amp,

@@ -40,6 +40,17 @@ void launch_norm2(sgw_ctx *ctx, const void *x, int64_t ld, int64_t nvec, double 
 void launch_redot(sgw_ctx *ctx, const void *a, const void *b, int64_t ld, int64_t nf,
                   double *d_out);
 
+// ---- Lanczos (sgw_lanczos_bounds)
+// workgroups of the Lanczos kernels; `partial` holds twice as many doubles
+int lanczos_blocks(const sgw_ctx *ctx);
+// v = w / |w|, vp = 0, *beta = 0
+void launch_lanczos_start(sgw_ctx *ctx, void *v, void *vp, void *w, double *beta,
+                          double *partial);
+// with w = H v: *alpha = <v|w>, w -= alpha v + beta[0] vp, beta[1] = |w|,
+// vp = v, v = w / beta[1]
+void launch_lanczos_step(sgw_ctx *ctx, void *v, void *vp, void *w, double *alpha, double *beta,
+                         double *partial);
+
 // ---- white noise and unpacking (sgw_sigma_estimate)
 // Filter input: complex vector k carries real noise vectors 2k and 2k+1 of the
 // flat list keys[0..nr-1] (+-1/sqrt(dV)).
