@@ -90,22 +90,42 @@ __global__ __launch_bounds__(NTK) void k_kb_gather(const cplx<R> *psi, int64_t l
   }
 }
 
+// out[p][v] = sum of projector p's partial sums (times E_p), FP64.  A
+// workgroup holds 2^lv vectors of one projector and splits its entries (some
+// 60 to 90) over the 256 >> lv threads of each vector, whose sums are added
+// in order: with one thread per vector a batch of 1 left 255 threads idle
+// behind a chain of loads (64^3: 8.9 us, now 3.8; 16 vectors 15.6 -> 5.1).
 template <typename R>
-__global__ void k_kb_reduce(const cplx<R> *partial, const int *proj_off, const int *proj_entries,
-                            const double *ekb, int use_e, int64_t nvec, cplx<R> *out) {
-  const int64_t v = (int64_t)blockIdx.x * NTK + threadIdx.x;
+__global__ __launch_bounds__(NTK) void k_kb_reduce(const cplx<R> *partial, const int *proj_off,
+                                                   const int *proj_entries, const double *ekb,
+                                                   int use_e, int64_t nvec, int lv,
+                                                   cplx<R> *out) {
+  __shared__ double2 sh[NTK];
+  const int vl = threadIdx.x & ((1 << lv) - 1), part = threadIdx.x >> lv, np = NTK >> lv;
+  const int64_t v = ((int64_t)blockIdx.x << lv) + vl;
   const int p = blockIdx.y;
-  if (v >= nvec) return;
   double sr = 0, si = 0;
-  // unrolled so that several loads are in flight; the sum keeps its order
+  if (v < nvec) {
+    // unrolled so that several loads are in flight; the sum keeps its order
 #pragma unroll 8
-  for (int k = proj_off[p]; k < proj_off[p + 1]; ++k) {
-    const cplx<R> c = partial[(int64_t)proj_entries[k] * nvec + v];
-    sr += c.x;
-    si += c.y;
+    for (int k = proj_off[p] + part; k < proj_off[p + 1]; k += np) {
+      const cplx<R> c = partial[(int64_t)proj_entries[k] * nvec + v];
+      sr += c.x;
+      si += c.y;
+    }
   }
-  if (use_e) { sr *= ekb[p]; si *= ekb[p]; }
-  out[(int64_t)p * nvec + v] = cmake<cplx<R>>(sr, si);
+  sh[threadIdx.x] = make_double2(sr, si);
+  for (int h = np / 2; h > 0; h >>= 1) {
+    __syncthreads();
+    if (part < h) {
+      const double2 a = sh[threadIdx.x], b = sh[threadIdx.x + (h << lv)];
+      sh[threadIdx.x] = make_double2(a.x + b.x, a.y + b.y);
+    }
+  }
+  if (part > 0 || v >= nvec) return;
+  double2 s = sh[threadIdx.x];
+  if (use_e) { s.x *= ekb[p]; s.y *= ekb[p]; }
+  out[(int64_t)p * nvec + v] = cmake<cplx<R>>(s.x, s.y);
 }
 
 template <typename R>
@@ -326,6 +346,10 @@ __global__ __launch_bounds__(NTK) void k_kb_gather_mma(
   const int base = tile_base[t];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, col = lane & 15;
   const int off = tile_off[t], ne = tile_off[t + 1] - off;
+  // the passes over the tile's entries are split over gridDim.y workgroups
+  // where there are too few vectors to fill the device
+  const int mg0 = blockIdx.y * 16 * MT, mstep = gridDim.y * 16 * MT;
+  if (mg0 >= ne) return;
   // bit g of glive: some point of this wave's K group g (GK consecutive tile
   // points) lies in a projector's support.  A group without one holds only
   // zero beta values: its psi values are not loaded and its products (exact
@@ -401,10 +425,10 @@ __global__ __launch_bounds__(NTK) void k_kb_gather_mma(
   u32x4 a[RA][MT];
 #pragma unroll
   for (int g = 0; g < D; ++g)
-    if (live(g)) load_a(0, g, a[g]);
+    if (live(g)) load_a(mg0, g, a[g]);
   u32x4 b[NG][NTL], blo[NS][NSN];
   load_b(v0, b, blo);
-  for (int mg = 0; mg < ne; mg += 16 * MT) {
+  for (int mg = mg0; mg < ne; mg += mstep) {
     f32x4 acc[MT][NTL];
 #pragma unroll
     for (int j = 0; j < MT; ++j)
@@ -412,7 +436,7 @@ __global__ __launch_bounds__(NTK) void k_kb_gather_mma(
       for (int n = 0; n < NTL; ++n) acc[j][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-      if (live((g + D) % NG)) load_a(g + D < NG ? mg : mg + 16 * MT, (g + D) % NG, a[(g + D) % RA]);
+      if (live((g + D) % NG)) load_a(g + D < NG ? mg : mg + mstep, (g + D) % NG, a[(g + D) % RA]);
       if (!live(g)) continue;
 #pragma unroll
       for (int j = 0; j < MT; ++j)
@@ -765,7 +789,11 @@ static void gather_t(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, vo
       using Op = decltype(op);
       auto run = [&](int vi) {
         const int64_t nvb = (nvec + kGather[vi].nvb - 1) / kGather[vi].nvb;
-        launch_gather_variant<Op>(vi, tile_grid(ctx->kb_ntile, nvb), ctx->stream,
+        // fewer than four workgroups per CU: one pass over entries each (40^3, 1
+        // vector: 13.5 -> 7.0 us; 64^3, 16 vectors: 24.7 -> 18.5)
+        dim3 g = tile_grid(ctx->kb_ntile, nvb);
+        if (g.x < 1024) g.y = (ctx->kb_nek_max + 16 * kGather[vi].mt - 1) / (16 * kGather[vi].mt);
+        launch_gather_variant<Op>(vi, g, ctx->stream,
                                   static_cast<const float2 *>(psi), ld, nvec,
                                   ctx->d_kb_tile_base.as<int>(), ctx->d_kb_tile_off.as<int>(),
                                   beta, reinterpret_cast<float2 *>(partial), ctx->nx, ctx->ny,
@@ -796,10 +824,12 @@ static void gather_t(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, vo
                        ctx->ny, ctx->kb_lx, ctx->kb_ly, (R)ctx->dV);
   }
   SGW_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_kb_reduce<R>, dim3((nvec + NTK - 1) / NTK, ctx->kb.nproj), dim3(NTK), 0,
-                     ctx->stream, partial, ctx->d_kb_proj_off.as<int>(),
+  int lv = 0;                            // up to 64 vectors per workgroup
+  while (lv < 6 && (int64_t(1) << lv) < nvec) ++lv;
+  hipLaunchKernelGGL(k_kb_reduce<R>, dim3((nvec + (1 << lv) - 1) >> lv, ctx->kb.nproj), dim3(NTK),
+                     0, ctx->stream, partial, ctx->d_kb_proj_off.as<int>(),
                      ctx->d_kb_proj_entries.as<int>(), ctx->d_kb_ekb.as<double>(), use_e ? 1 : 0,
-                     nvec, static_cast<C *>(out));
+                     nvec, lv, static_cast<C *>(out));
   SGW_HIP(hipGetLastError());
 }
 
