@@ -215,7 +215,7 @@ void cheb_term(sgw_ctx *ctx, void *cur, void *old, void *acc, void *tmp, void *k
   e.term_dev = coef_dev ? ctx->d_counter.as<int>() : nullptr;
   fft3d_apply(ctx, cur, tmp, nullptr, nvec, N, MUL_KIN, 0.0, PLANE_INV_CHEB, e, 0, tmp2, rev);
   if (ctx->has_kb && ovl) join_gather(ctx);
-  if (ctx->has_kb) kb_scatter(ctx, kbC, nvec, out ? out : old, N, s2 * invR, 0.0, nullptr, 0.0, 0.0);
+  if (ctx->has_kb) kb_scatter(ctx, kbC, nvec, out ? out : old, N, s2 * invR);
 }
 
 constexpr int SHORT_SERIES = 64;   // up to this many terms a series is one graph
@@ -426,7 +426,7 @@ void kb_exp_apply(sgw_ctx *ctx, void *psi, int64_t ld, int64_t nvec, double tau)
   void *C2 = ctx->buf("kbC2", ctx->csize() * ctx->kb.nproj * nvec).p;
   kb_gather(ctx, psi, nvec, ld, C);
   kb_mix_dense(ctx, K, C, C2, nvec);
-  kb_scatter(ctx, C2, nvec, psi, ld, 1.0, 0.0, nullptr, 0.0, 0.0);
+  kb_scatter(ctx, C2, nvec, psi, ld, 1.0);
 }
 
 // Poisson of S complex fields rho (ld = N): POISSON -> v, u; SPLIT -> r0, r1
@@ -536,7 +536,7 @@ void apply_h(sgw_ctx *ctx, const void *psi, void *hpsi, int64_t nvec, int64_t ld
     e.x = x;
     e.vloc = ctx->d_vloc.p;
     fft3d_apply(ctx, x, tmp, y, nv, ld, MUL_KIN, 0.0, PLANE_INV_HPSI, e);
-    if (ctx->has_kb) kb_scatter(ctx, kbC, nv, y, ld, 1.0, 0.0, nullptr, 0.0, 0.0);
+    if (ctx->has_kb) kb_scatter(ctx, kbC, nv, y, ld, 1.0);
   }
 }
 
@@ -605,7 +605,7 @@ void apply_h_noalloc(sgw_ctx *ctx, const void *psi, void *hpsi, int64_t nvec, in
     e.x = x;
     e.vloc = ctx->d_vloc.p;
     fft3d_apply(ctx, x, y, y, nv, ld, MUL_KIN, 0.0, PLANE_INV_HPSI, e, ld);
-    if (ctx->has_kb) kb_scatter(ctx, kbC, nv, y, ld, 1.0, 0.0, nullptr, 0.0, 0.0);
+    if (ctx->has_kb) kb_scatter(ctx, kbC, nv, y, ld, 1.0);
   }
 }
 

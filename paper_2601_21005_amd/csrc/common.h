@@ -125,6 +125,7 @@ struct sgw_ctx {
   int kb_ntile = 0, kb_nentry = 0;
   int64_t kb_support_points = 0;     // grid points where some beta_p is nonzero
   int64_t kb_nnz = 0;                // nonzero beta values (point, projector)
+  int kb_ne_max = 0;                 // most projector entries of a tile
   int kb_nek_max = 0;                // largest padded entry count of a tile (scatter LDS)
   int kb_lx = 3, kb_ly = 3;          // tile extent log2 along x and y (512 points)
 
@@ -322,10 +323,8 @@ size_t kb_partial_bytes_per_vec(const sgw_ctx *ctx);
 // C' = K C  (K complex [nproj][nproj] in the working precision)
 void kb_mix_dense(sgw_ctx *ctx, const void *K, const void *coef_in, void *coef_out,
                   int64_t nvec);
-// dst[v] += s1 * B C[v];  if dst2: dst2[v] += s2 * B C[v]  (s1, s2 complex)
-// (the MFMA kernels of the complex FP32 precisions take s1 real and no dst2)
-void kb_scatter(sgw_ctx *ctx, const void *coef, int64_t nvec, void *dst, int64_t ld,
-                double s1re, double s1im, void *dst2, double s2re, double s2im);
+// dst[v] += s1 * B C[v]
+void kb_scatter(sgw_ctx *ctx, const void *coef, int64_t nvec, void *dst, int64_t ld, double s1);
 
 // operand arrays of the MFMA kernels (after build_kb and the upload of beta)
 void kb_upload_operands(sgw_ctx *ctx);

@@ -164,6 +164,7 @@ void build_kb(sgw_ctx *ctx, const sgw_projectors *P) {
         if (p != q) kb.gram[(size_t)q * np + p] += s;
       }
   ctx->kb_ntile = ntile;
+  ctx->kb_ne_max = maxe;
   ctx->kb_nentry = nentry;
   // grid points inside some projector's support, and nonzero beta values
   ctx->kb_support_points = 0;

@@ -3,7 +3,7 @@
 // spheres overlap, Sec. 3).  Here the work is owned by 512-point grid tiles
 // (16 x 8 x 4 where the grid allows it, else 8 x 8 x 8):
 //   gather   partial[e][v] = dV sum_{r in tile} beta_e(r) psi_v(r)   per
-//            (tile, projector) entry e -- the tile of NV vectors sits in LDS;
+//            (tile, projector) entry e;
 //   reduce   C[p][v] = sum of the partials of projector p, in a fixed order
 //            (optionally times E_p);
 //   mix      C'[p][v] = sum_q K[p][q] C[q][v]  (dense, for exp(-i tau V_NL));
@@ -16,78 +16,13 @@
 namespace sgw {
 
 constexpr int NTK = 256;
-constexpr int KB_MAXE = 256;   // max projector entries per tile
 
-template <typename R> struct KBV;
-template <> struct KBV<float> { static constexpr int NV = 8; };
-template <> struct KBV<double> { static constexpr int NV = 4; };
-
-// flat grid index of point p of a tile whose x and y extents are 2^lx, 2^ly
-__device__ __forceinline__ int64_t tile_point(int base, int p, int nx, int ny, int lx, int ly) {
-  const int x = p & ((1 << lx) - 1), y = (p >> lx) & ((1 << ly) - 1), z = p >> (lx + ly);
-  return (int64_t)base + x + (int64_t)nx * (y + (int64_t)ny * z);
-}
-
-// the same with the x extent 2^LX known at compile time (y extent 8), in
+// flat grid index of point p of a tile of x extent 2^LX (y extent 8), in
 // 32-bit arithmetic (grids below 2^31 points)
 template <int LX>
 __device__ __forceinline__ int tile_point_c(int base, int p, int nx, int ny) {
   const int x = p & ((1 << LX) - 1), y = (p >> LX) & 7, z = p >> (LX + 3);
   return base + x + nx * (y + ny * z);
-}
-
-template <typename T> __device__ __forceinline__ T wsum(T v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-  return v;
-}
-
-template <typename R>
-__global__ __launch_bounds__(NTK) void k_kb_gather(const cplx<R> *psi, int64_t ld, int64_t nvec,
-                                                   const int *tile_base, const int *tile_off,
-                                                   const R *beta, cplx<R> *partial, int nx,
-                                                   int ny, int lx, int ly, R dV) {
-  constexpr int NV = KBV<R>::NV;
-  using C = cplx<R>;
-  __shared__ C s[KB_TP * NV];
-  const int t = blockIdx.y;
-  const int64_t v0 = (int64_t)blockIdx.x * NV;
-  const int base = tile_base[t];
-  for (int idx = threadIdx.x; idx < KB_TP * NV; idx += NTK) {
-    const int vl = idx / KB_TP, p = idx % KB_TP;
-    C val = cmake<C>(0, 0);
-    if (v0 + vl < nvec) val = psi[(v0 + vl) * ld + tile_point(base, p, nx, ny, lx, ly)];
-    s[p * NV + vl] = val;
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int e1 = tile_off[t + 1];
-  for (int e = tile_off[t] + w; e < e1; e += NTK / 64) {
-    R ar[NV], ai[NV];
-#pragma unroll
-    for (int vl = 0; vl < NV; ++vl) { ar[vl] = 0; ai[vl] = 0; }
-    const R *b = beta + (int64_t)e * KB_TP;
-#pragma unroll
-    for (int q = 0; q < KB_TP / 64; ++q) {
-      const int p = lane + 64 * q;
-      const R bv = b[p];
-#pragma unroll
-      for (int vl = 0; vl < NV; ++vl) {
-        const C x = s[p * NV + vl];
-        ar[vl] += bv * x.x;
-        ai[vl] += bv * x.y;
-      }
-    }
-#pragma unroll
-    for (int vl = 0; vl < NV; ++vl) {
-      ar[vl] = wsum(ar[vl]);
-      ai[vl] = wsum(ai[vl]);
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int vl = 0; vl < NV; ++vl)
-        if (v0 + vl < nvec) partial[(int64_t)e * nvec + v0 + vl] = cmake<C>(dV * ar[vl], dV * ai[vl]);
-    }
-  }
 }
 
 // out[p][v] = sum of projector p's partial sums (times E_p), FP64.  A
@@ -151,60 +86,6 @@ __global__ void k_kb_mix(const cplx<R> *K, const cplx<R> *in, cplx<R> *out, int 
   }
   for (; q < np; ++q) add(k[q], in[(int64_t)q * nvec + v]);
   out[(int64_t)p * nvec + v] = cmake<cplx<R>>(sr, si);
-}
-
-template <typename R>
-__global__ __launch_bounds__(NTK) void k_kb_scatter(const cplx<R> *coef, int64_t nvec,
-                                                    const int *tile_base, const int *tile_off,
-                                                    const int *entry_proj, const R *beta,
-                                                    cplx<R> *dst, int64_t ld, R s1r, R s1i,
-                                                    cplx<R> *dst2, R s2r, R s2i, int nx,
-                                                    int ny, int lx, int ly) {
-  constexpr int NV = KBV<R>::NV;
-  using C = cplx<R>;
-  __shared__ C c[KB_MAXE * NV];
-  const int t = blockIdx.y;
-  const int64_t v0 = (int64_t)blockIdx.x * NV;
-  const int off = tile_off[t], ne = tile_off[t + 1] - off;
-  const int base = tile_base[t];
-  for (int idx = threadIdx.x; idx < ne * NV; idx += NTK) {
-    const int el = idx / NV, vl = idx % NV;
-    C val = cmake<C>(0, 0);
-    if (v0 + vl < nvec) val = coef[(int64_t)entry_proj[off + el] * nvec + v0 + vl];
-    c[idx] = val;
-  }
-  __syncthreads();
-  for (int p = threadIdx.x; p < KB_TP; p += NTK) {
-    R ar[NV], ai[NV];
-#pragma unroll
-    for (int vl = 0; vl < NV; ++vl) { ar[vl] = 0; ai[vl] = 0; }
-    for (int el = 0; el < ne; ++el) {
-      const R bv = beta[(int64_t)(off + el) * KB_TP + p];
-#pragma unroll
-      for (int vl = 0; vl < NV; ++vl) {
-        const C x = c[el * NV + vl];
-        ar[vl] += bv * x.x;
-        ai[vl] += bv * x.y;
-      }
-    }
-    const int64_t r = tile_point(base, p, nx, ny, lx, ly);
-#pragma unroll
-    for (int vl = 0; vl < NV; ++vl) {
-      if (v0 + vl >= nvec) break;
-      C *d = dst + (v0 + vl) * ld + r;
-      C o = *d;
-      o.x += s1r * ar[vl] - s1i * ai[vl];
-      o.y += s1r * ai[vl] + s1i * ar[vl];
-      *d = o;
-      if (dst2) {
-        C *d2 = dst2 + (v0 + vl) * ld + r;
-        C o2 = *d2;
-        o2.x += s2r * ar[vl] - s2i * ai[vl];
-        o2.y += s2r * ai[vl] + s2i * ar[vl];
-        *d2 = o2;
-      }
-    }
-  }
 }
 
 // ---------------------------------------------------------------- MFMA
@@ -672,6 +553,191 @@ k_kb_scatter_mma_w8(
   scatter_mma<Op, NVB, MJ, LX, PF>(coef, nvec, tile_base, tile_off, tile_offT, entry_proj, betaT, dst, ld, s1, nx, ny, ntile, nvb, pe, tile_mask);
 }
 
+// ---------------------------------------------------------------- FP64
+// The same two products in FP64 on v_mfma_f64_16x16x4: lane l supplies A[l %
+// 16][l / 16] and B[l / 16][l % 16] and holds D[l / 16 + 4 r][l % 16], r =
+// 0..3.  Blocks of 8 vectors (16 real columns).  They are bound by reading
+// beta once per vector block and by psi; on the vector ALU the gather's
+// cross-lane sums and LDS reads took more time than either.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int NVB64 = 8;
+
+// As k_kb_gather_mma: a wave's quarter of the tile in 16 K groups of 8 points,
+// of which lane (q, col) feeds points 2 q and 2 q + 1, two MFMAs per group;
+// column 2 v + part is the real or imaginary part of vector v, the lane pair
+// reads one complex value each and swaps halves.  H on 20 vectors of 96^3
+// (688 projectors): 265 us on the
+// vector ALU, now 94.
+template <int MT, int LX>
+__global__ __launch_bounds__(NTK) void k_kb_gather_f64(
+    const double2 *psi, int64_t ld, int64_t nvec, const int *tile_base, const int *tile_off,
+    const double *beta, double2 *partial, int nx, int ny, double dV, int ntile, int nvb,
+    const uint32_t *__restrict__ tile_mask) {
+  constexpr int NG = 16;
+  __shared__ __align__(16) double red[4 * MT * 256];
+  int t;
+  int64_t vb;
+  if (!tile_block(ntile, nvb, t, vb)) return;
+  const int64_t v0 = vb * NVB64;
+  const int base = tile_base[t];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, col = lane & 15;
+  const int off = tile_off[t], ne = tile_off[t + 1] - off;
+  const int mg0 = blockIdx.y * 16 * MT, mstep = gridDim.y * 16 * MT;
+  if (mg0 >= ne) return;
+  // bit g: K group g of this wave holds some point of a projector's support
+  uint32_t glive = 0;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t word = tile_mask[(int64_t)t * (KB_TP / 32) + 4 * wu + i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) glive |= ((word >> (8 * j)) & 0xffu ? 1u : 0u) << (4 * i + j);
+  }
+  glive = __builtin_amdgcn_readfirstlane(glive);
+  auto live = [&](int g) { return (glive >> g) & 1u; };
+  const double *bw = beta + 128 * w + 2 * q;
+  auto load_a = [&](int mg, int g, double2 *a) {
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+      const int e = min(mg + 16 * j + col, ne - 1);   // rows past ne: never stored
+      a[j] = *reinterpret_cast<const double2 *>(bw + (int64_t)(off + e) * KB_TP + 8 * g);
+    }
+  };
+  double2 a[2][MT], b[NG];
+  if (live(0)) load_a(mg0, 0, a[0]);
+  const int od = col & 1;
+  const double2 *src = psi + min(v0 + (col >> 1), nvec - 1) * ld + od;
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+    b[g] = live(g) ? src[tile_point_c<LX>(base, 128 * w + 8 * g + 2 * q, nx, ny)]
+                   : make_double2(0, 0);
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const double got = __shfl_xor(od ? b[g].x : b[g].y, 1, 64);
+    b[g] = od ? make_double2(got, b[g].y) : make_double2(b[g].x, got);
+  }
+  for (int mg = mg0; mg < ne; mg += mstep) {
+    f64x4 acc[MT];
+#pragma unroll
+    for (int j = 0; j < MT; ++j) acc[j] = f64x4{0, 0, 0, 0};
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      if (live((g + 1) % NG)) load_a(g + 1 < NG ? mg : mg + mstep, (g + 1) % NG, a[(g + 1) % 2]);
+      if (!live(g)) continue;
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+        if (mg + 16 * j < ne) {
+          acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g % 2][j].x, b[g].x, acc[j], 0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g % 2][j].y, b[g].y, acc[j], 0, 0, 0);
+        }
+    }
+    __syncthreads();                    // the sums of the pass before are read
+#pragma unroll
+    for (int j = 0; j < MT; ++j)
+      *reinterpret_cast<f64x4 *>(red + ((w * MT + j) * 64 + lane) * 4) = acc[j];
+    __syncthreads();
+    for (int o = tid; o < MT * 16 * NVB64; o += NTK) {
+      const int j = o / (16 * NVB64), er = (o / NVB64) % 16, vl = o % NVB64;
+      const int e = mg + 16 * j + er, at = (16 * (er & 3) + 2 * vl) * 4 + (er >> 2);
+      double re = 0, im = 0;
+#pragma unroll
+      for (int ww = 0; ww < 4; ++ww) {
+        const double *s = red + (ww * MT + j) * 256 + at;
+        re += s[0];
+        im += s[4];
+      }
+      if (e < ne && v0 + vl < nvec)
+        partial[(int64_t)(off + e) * nvec + v0 + vl] = make_double2(dV * re, dV * im);
+    }
+  }
+}
+
+// dst_v(r) += s1 sum_e beta_e(r) C'[p(e)][v].  A wave owns NP runs of 32 tile
+// points: lane column c holds points 2 c and 2 c + 1, one MFMA each per group
+// of 4 entries, so beta is read where it lies, 16 bytes a lane, and a lane
+// updates two neighbouring complex values.  C' rows are ordered in LDS so that
+// the accumulators r = 0, 1 of lane group q are the parts of vector q and r =
+// 2, 3 those of vector q + 4.  Runs outside every support are skipped.  Same
+// case: 147 us, now 91.
+template <int NP, int LX>
+__global__ __launch_bounds__(NTK) void k_kb_scatter_f64(
+    const double2 *coef, int64_t nvec, const int *tile_base, const int *tile_off,
+    const int *entry_proj, const double *beta, double2 *dst, int64_t ld, double s1, int nx,
+    int ny, int ntile, int nvb, const uint32_t *tile_mask) {
+  constexpr int NH = KB_TP / (128 * NP);            // workgroups per tile and vector block
+  extern __shared__ __align__(16) unsigned char kb_lds[];
+  double *sc = reinterpret_cast<double *>(kb_lds);  // [entry][16]
+  int t;
+  int64_t vbh;
+  if (!tile_block(ntile, nvb * NH, t, vbh)) return;
+  const int64_t v0 = vbh / NH * NVB64;
+  const int off = tile_off[t], ne = tile_off[t + 1] - off, nek = (ne + 3) / 4 * 4;
+  const int base = tile_base[t];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, col = lane & 15;
+  const int p0 = (int)(vbh % NH) * 128 * NP + 32 * NP * w;
+  bool live[NP];
+#pragma unroll
+  for (int j = 0; j < NP; ++j)
+    live[j] = __builtin_amdgcn_readfirstlane(tile_mask[(int64_t)t * (KB_TP / 32) + p0 / 32 + j]) != 0;
+  const double *bt = beta + (int64_t)off * KB_TP + p0 + 2 * col;
+  double2 b[2][NP];
+  auto load_b = [&](int e0, double2 *x) {
+    const double *r = bt + (int64_t)min(e0 + q, ne - 1) * KB_TP;   // past ne: times C' = 0
+#pragma unroll
+    for (int j = 0; j < NP; ++j)
+      if (live[j]) x[j] = *reinterpret_cast<const double2 *>(r + 32 * j);
+  };
+  load_b(0, b[0]);
+  for (int i = tid; i < nek * NVB64; i += NTK) {
+    const int el = i / NVB64, vl = i % NVB64;
+    double2 c = make_double2(0, 0);
+    if (el < ne && v0 + vl < nvec) c = coef[(int64_t)entry_proj[off + el] * nvec + v0 + vl];
+    double *d = sc + el * 16 + (vl & 3) + 8 * (vl >> 2);
+    d[0] = c.x;
+    d[4] = c.y;
+  }
+  __syncthreads();
+  f64x4 acc[NP][2];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) acc[j][0] = acc[j][1] = f64x4{0, 0, 0, 0};
+  auto group = [&](int e0, const double2 *x) {
+    const double a = sc[(e0 + q) * 16 + col];
+#pragma unroll
+    for (int j = 0; j < NP; ++j)
+      if (live[j]) {
+        acc[j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x[j].x, acc[j][0], 0, 0, 0);
+        acc[j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x[j].y, acc[j][1], 0, 0, 0);
+      }
+  };
+  for (int e0 = 0; e0 < nek; e0 += 8) {
+    if (e0 + 4 < nek) load_b(e0 + 4, b[1]);
+    group(e0, b[0]);
+    if (e0 + 8 < nek) load_b(e0 + 8, b[0]);
+    if (e0 + 4 < nek) group(e0 + 4, b[1]);
+  }
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    if (!live[j]) continue;
+    const int r = tile_point_c<LX>(base, p0 + 32 * j + 2 * col, nx, ny);
+    double2 o[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double2 *d = dst + min(v0 + q + 4 * h, nvec - 1) * ld + r;
+      o[h][0] = d[0];
+      o[h][1] = d[1];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t v = v0 + q + 4 * h;
+      if (v >= nvec) continue;
+      double2 *d = dst + v * ld + r;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        d[u] = make_double2(o[h][u].x + s1 * acc[j][u][2 * h], o[h][u].y + s1 * acc[j][u][2 * h + 1]);
+    }
+  }
+}
+
 // variants (autotuned per context, operand type and batch width)
 // (w: the instance held to that many waves per SIMD, 0: the compiler's
 // choice; the tuner keeps the first variant within 3 % of the fastest, so a
@@ -772,27 +838,31 @@ void kb_upload_operands(sgw_ctx *ctx) {
 }
 
 // ---------------------------------------------------------------- launchers
+// grid rows over which a gather's passes over entries are split: one pass
+// each while there are fewer than four workgroups per CU (40^3, 1 vector:
+// 13.5 -> 7.0 us; 64^3, 16 vectors: 24.7 -> 18.5)
+static int entry_split(const sgw_ctx *ctx, const dim3 &g, int mt) {
+  return g.x < 1024 ? (ctx->kb_ne_max + 16 * mt - 1) / (16 * mt) : 1;
+}
+
 template <typename R>
 static void gather_t(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, void *out,
                      bool use_e, void *partial_ext) {
-  constexpr int NV = KBV<R>::NV;
   using C = cplx<R>;
   C *partial = partial_ext ? static_cast<C *>(partial_ext)
                            : ctx->buf("kb_partial", sizeof(C) * (size_t)ctx->kb_nentry * nvec).as<C>();
   SGW_REQUIRE(ctx->kb_ntile <= 65535, SGW_EUNSUPPORTED, "KB gather: too many tiles");
+  SGW_REQUIRE(ctx->kb_ly == 3 && (ctx->kb_lx == 3 || ctx->kb_lx == 4), SGW_EUNSUPPORTED,
+              "KB tile shape not built");
   if constexpr (sizeof(R) == 4) {
     SGW_REQUIRE(ld % 2 == 0, SGW_EUNSUPPORTED,
                 "projectors in complex FP32 need an even leading dimension");
-    SGW_REQUIRE(ctx->kb_ly == 3 && (ctx->kb_lx == 3 || ctx->kb_lx == 4), SGW_EUNSUPPORTED,
-                "KB tile shape not built");
     auto go = [&](auto op, const char *name, const auto *beta) {
       using Op = decltype(op);
       auto run = [&](int vi) {
         const int64_t nvb = (nvec + kGather[vi].nvb - 1) / kGather[vi].nvb;
-        // fewer than four workgroups per CU: one pass over entries each (40^3, 1
-        // vector: 13.5 -> 7.0 us; 64^3, 16 vectors: 24.7 -> 18.5)
         dim3 g = tile_grid(ctx->kb_ntile, nvb);
-        if (g.x < 1024) g.y = (ctx->kb_nek_max + 16 * kGather[vi].mt - 1) / (16 * kGather[vi].mt);
+        g.y = entry_split(ctx, g, kGather[vi].mt);
         launch_gather_variant<Op>(vi, g, ctx->stream,
                                   static_cast<const float2 *>(psi), ld, nvec,
                                   ctx->d_kb_tile_base.as<int>(), ctx->d_kb_tile_off.as<int>(),
@@ -817,11 +887,14 @@ static void gather_t(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, vo
     else
       go(OpF32{}, "kb_gather", ctx->d_kb_beta.as<float>());
   } else {
-    const int64_t nvb = (nvec + NV - 1) / NV;
-    hipLaunchKernelGGL(k_kb_gather<R>, dim3(nvb, ctx->kb_ntile), dim3(NTK), 0, ctx->stream,
-                       static_cast<const C *>(psi), ld, nvec, ctx->d_kb_tile_base.as<int>(),
-                       ctx->d_kb_tile_off.as<int>(), ctx->d_kb_beta.as<R>(), partial, ctx->nx,
-                       ctx->ny, ctx->kb_lx, ctx->kb_ly, (R)ctx->dV);
+    const int64_t nvb = (nvec + NVB64 - 1) / NVB64;
+    dim3 g = tile_grid(ctx->kb_ntile, nvb);
+    g.y = entry_split(ctx, g, 2);
+    const auto k = ctx->kb_lx == 4 ? k_kb_gather_f64<2, 4> : k_kb_gather_f64<2, 3>;
+    hipLaunchKernelGGL(k, g, dim3(NTK), 0, ctx->stream, static_cast<const double2 *>(psi), ld,
+                       nvec, ctx->d_kb_tile_base.as<int>(), ctx->d_kb_tile_off.as<int>(),
+                       ctx->d_kb_beta.as<double>(), reinterpret_cast<double2 *>(partial), ctx->nx,
+                       ctx->ny, ctx->dV, ctx->kb_ntile, (int)nvb, ctx->d_kb_mask.as<uint32_t>());
   }
   SGW_HIP(hipGetLastError());
   int lv = 0;                            // up to 64 vectors per workgroup
@@ -864,15 +937,11 @@ void kb_mix_dense(sgw_ctx *ctx, const void *K, const void *coef_in, void *coef_o
 
 template <typename R>
 static void scatter_t(sgw_ctx *ctx, const void *coef, int64_t nvec, void *dst, int64_t ld,
-                      double s1re, double s1im, void *dst2, double s2re, double s2im) {
-  constexpr int NV = KBV<R>::NV;
-  using C = cplx<R>;
+                      double s1) {
   SGW_REQUIRE(ctx->kb_ntile <= 65535, SGW_EUNSUPPORTED, "KB scatter: too many tiles");
+  SGW_REQUIRE(ctx->kb_ly == 3 && (ctx->kb_lx == 3 || ctx->kb_lx == 4), SGW_EUNSUPPORTED,
+              "KB tile shape not built");
   if constexpr (sizeof(R) == 4) {
-    SGW_REQUIRE(dst2 == nullptr && s1im == 0.0, SGW_EUNSUPPORTED,
-                "KB scatter (FP32): complex scale or second output not built");
-    SGW_REQUIRE(ctx->kb_ly == 3 && (ctx->kb_lx == 3 || ctx->kb_lx == 4), SGW_EUNSUPPORTED,
-                "KB tile shape not built");
     auto go = [&](auto op, const char *name, const auto *betaT) {
       using Op = decltype(op);
       auto launch = [&](int vi, float s) {
@@ -891,7 +960,7 @@ static void scatter_t(sgw_ctx *ctx, const void *coef, int64_t nvec, void *dst, i
       const int vi = ctx->tune(name, nvec, NSCATTER, [&](int i) { launch(i, 0.0f); });
       const bool timed = (ctx->ktimer & 2) && ctx->ns.empty();
       if (timed) SGW_HIP(hipEventRecord(ctx->kt[1].event(0), ctx->stream));
-      launch(vi, (float)s1re);
+      launch(vi, (float)s1);
       if (timed) {
         SGW_HIP(hipEventRecord(ctx->kt[1].event(1), ctx->stream));
         ctx->kt[1].used++;
@@ -904,23 +973,23 @@ static void scatter_t(sgw_ctx *ctx, const void *coef, int64_t nvec, void *dst, i
       go(OpBF16x2{}, "kb_scatter_bf16x2", ctx->d_kb_betaT.as<uint16_t>());
     else
       go(OpF32{}, "kb_scatter", ctx->d_kb_betaT.as<float>());
-    SGW_HIP(hipGetLastError());
-    return;
+  } else {
+    const int64_t nvb = (nvec + NVB64 - 1) / NVB64;
+    constexpr int NP = 2, NH = KB_TP / (128 * NP);
+    const size_t lds = sizeof(double) * 16 * ((ctx->kb_ne_max + 3) / 4 * 4);
+    const auto k = ctx->kb_lx == 4 ? k_kb_scatter_f64<NP, 4> : k_kb_scatter_f64<NP, 3>;
+    hipLaunchKernelGGL(k, tile_grid(ctx->kb_ntile, nvb * NH), dim3(NTK), lds, ctx->stream,
+                       static_cast<const double2 *>(coef), nvec, ctx->d_kb_tile_base.as<int>(),
+                       ctx->d_kb_tile_off.as<int>(), ctx->d_kb_entry_proj.as<int>(),
+                       ctx->d_kb_beta.as<double>(), static_cast<double2 *>(dst), ld, s1, ctx->nx,
+                       ctx->ny, ctx->kb_ntile, (int)nvb, ctx->d_kb_mask.as<uint32_t>());
   }
-  const int64_t nvb = (nvec + NV - 1) / NV;
-  hipLaunchKernelGGL(k_kb_scatter<R>, dim3(nvb, ctx->kb_ntile), dim3(NTK), 0, ctx->stream,
-                     static_cast<const C *>(coef), nvec, ctx->d_kb_tile_base.as<int>(),
-                     ctx->d_kb_tile_off.as<int>(), ctx->d_kb_entry_proj.as<int>(),
-                     ctx->d_kb_beta.as<R>(), static_cast<C *>(dst), ld, (R)s1re, (R)s1im,
-                     static_cast<C *>(dst2), (R)s2re, (R)s2im, ctx->nx, ctx->ny, ctx->kb_lx,
-                     ctx->kb_ly);
   SGW_HIP(hipGetLastError());
 }
 
-void kb_scatter(sgw_ctx *ctx, const void *coef, int64_t nvec, void *dst, int64_t ld,
-                double s1re, double s1im, void *dst2, double s2re, double s2im) {
-  if (ctx->dbl) scatter_t<double>(ctx, coef, nvec, dst, ld, s1re, s1im, dst2, s2re, s2im);
-  else scatter_t<float>(ctx, coef, nvec, dst, ld, s1re, s1im, dst2, s2re, s2im);
+void kb_scatter(sgw_ctx *ctx, const void *coef, int64_t nvec, void *dst, int64_t ld, double s1) {
+  if (ctx->dbl) scatter_t<double>(ctx, coef, nvec, dst, ld, s1);
+  else scatter_t<float>(ctx, coef, nvec, dst, ld, s1);
 }
 
 }  // namespace sgw

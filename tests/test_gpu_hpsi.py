@@ -111,6 +111,36 @@ def test_local_h_every_plane_and_pencil_shape(n, nz, prec):
     assert row_max_err(got, ref) < 10 * TOL[prec]
 
 
+@pytest.mark.parametrize("which", ["si35", "si17_40"])
+def test_hpsi_c128_vector_blocks(which, request):
+    """The FP64 projector kernels on batches below, at and past their blocks
+    of 8 vectors, on 16 x 8 x 4 tiles (64^3) and 8 x 8 x 8 tiles (40^3),
+    with an odd leading dimension, against the oracle."""
+    from conftest import build_oracle_h
+    from paper_2601_21005_amd import systems
+    if which == "si35":
+        s, H = request.getfixturevalue("si35")
+    else:
+        species, pos = systems.si_cluster(17, seed=3)
+        s = systems.cluster_model(species, pos, n=40, h=0.6, ecut=28.0)
+        H = build_oracle_h(s)
+    N = s.grid.N
+    rs = np.random.default_rng(21)
+    x = rs.standard_normal((17, N)) + 1j * rs.standard_normal((17, N))
+    ref = H.apply(x)
+    ctx = make_ctx(s, sgw.SGW_C128, max_nvec=32)
+    for nv in (1, 8, 17):
+        xd = torch.zeros((nv, N + 3), dtype=torch.complex128, device="cuda")
+        xd[:, :N] = torch.from_numpy(x[:nv]).cuda()
+        yd = torch.zeros_like(xd)
+        ctx.apply_H(xd, yd)
+        got = yd[:, :N].cpu().numpy()
+        assert torch.all(yd[:, N:] == 0)
+        assert norm_err(got, ref[:nv]) < TOL[sgw.SGW_C128]
+        assert row_max_err(got, ref[:nv]) < 10 * TOL[sgw.SGW_C128]
+    ctx.close()
+
+
 def test_hpsi_errors_and_empty(tiny8):
     s, H = tiny8
     ctx = make_ctx(s, sgw.SGW_C128)
