@@ -782,20 +782,26 @@ sgw_status sgw_lanczos_bounds(sgw_ctx *ctx, int32_t k, uint64_t seed, double pad
     SGW_REQUIRE(pad >= 0 && std::isfinite(pad), SGW_EINVAL, "pad must be >= 0");
     const int64_t N = ctx->N;
     const size_t cs = ctx->csize();
-    void *v = ctx->buf("lz_v", cs * N).p, *vp = ctx->buf("lz_vp", cs * N).p;
+    void *u = ctx->buf("lz_u", cs * N).p, *up = ctx->buf("lz_up", cs * N).p;
     void *w = ctx->buf("lz_w", cs * N).p;
-    double *partial = ctx->buf("lz_partial", sizeof(double) * 2 * lanczos_blocks(ctx)).as<double>();
+    const int nblk = lanczos_blocks(ctx);
+    double *dots = ctx->buf("lz_partial", sizeof(double) * 3 * nblk).as<double>();
+    double *unorm = dots + nblk, *norms = unorm + nblk;
     double *coef = ctx->buf("lz_coef", sizeof(double) * (2 * k + 1)).as<double>();
-    // start: +-1 white noise of stream (BOUNDS, 0, 0), unit Euclidean norm
+    // start: +-1 white noise of stream (BOUNDS, 0, 0)
     const uint64_t key = rng_key(seed, rng_stream(RNG_BOUNDS, 0, 0));
     DevBuf &dk = ctx->buf("lz_key", sizeof(uint64_t));
     SGW_HIP(hipMemcpyAsync(dk.p, &key, sizeof key, hipMemcpyHostToDevice, ctx->stream));
-    launch_fill_noise(ctx, dk.as<uint64_t>(), 1, w);
-    launch_lanczos_start(ctx, v, vp, w, coef + k, partial);
+    launch_fill_noise(ctx, dk.as<uint64_t>(), 1, u);
+    launch_lanczos_start(ctx, u, unorm);
     for (int j = 0; j < k; ++j) {
-      apply_h(ctx, v, w, 1, N);
-      launch_lanczos_step(ctx, v, vp, w, coef + j, coef + k + j, partial);
+      apply_h(ctx, u, w, 1, N);
+      launch_lanczos_step(ctx, u, up, w, coef + j, coef + k + j, j == 0, dots, unorm, norms);
+      std::swap(unorm, norms);
+      std::swap(u, up);                   // the vector before
+      std::swap(u, w);                    // the new one; the oldest takes the next product
     }
+    launch_lanczos_end(ctx, unorm, coef + 2 * k);
     std::vector<double> c(2 * k + 1);
     SGW_HIP(hipMemcpyAsync(c.data(), coef, sizeof(double) * c.size(), hipMemcpyDeviceToHost,
                            ctx->stream));

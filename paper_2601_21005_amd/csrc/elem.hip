@@ -246,119 +246,161 @@ void launch_redot(sgw_ctx *ctx, const void *a, const void *b, int64_t ld, int64_
 }
 
 // ============================================================ Lanczos
-// One Lanczos step after w = H v, its two scalars left on the device: every
-// workgroup sums the partial sums of the kernel before it (one wave, FP64),
-// so a step is three launches beside those of H and the host waits once at
-// the end.  (Fetching a = <v|w> and b = |w| to the host took two
-// synchronisations and ten launches a step: 60 steps at 64^3 10.7 ms, 3 of
-// them in an eigensolver for all Ritz pairs on the host; now 3.8.)
+// The Lanczos vectors are kept unnormalised: u_j = b_j v_j with b_j = |u_j|,
+//   a_j = <u_j|H u_j> / b_j^2,
+//   u_{j+1} = (H u_j - a_j u_j) / b_j - (b_j / b_{j-1}) u_{j-1},
+// so a step is two launches beside those of H (the dot products, then the new
+// vector with its norm), its scalars stay on the device and the host waits
+// once at the end.  Both are bound by latency (2 MB a vector at 64^3): every
+// workgroup sums the partial sums of the kernel before it, one wave each, in
+// FP64, and there are up to LZ_BLOCKS of them (one a CU at 64^3).
+// Lanczos interval of 60 steps at 64^3: 10.7 ms with the scalars fetched to
+// the host (two synchronisations and ten launches a step), 3.8 with them on
+// the device, 64 workgroups and a third launch for v_{j+1}, 3.2 now.
+constexpr int LZ_BLOCKS = 512;
 
-// sum of partial[0 .. nblk - 1] on every thread
-__device__ __forceinline__ double partial_total(const double *partial, int nblk, double *sh) {
-  if (threadIdx.x < 64) {
-    double s = 0;
-    for (int i = threadIdx.x; i < nblk; i += 64) s += partial[i];
+// points of a workgroup: a multiple of 4 NT
+static int lanczos_chunk(const sgw_ctx *ctx) {
+  const int64_t rows = (ctx->N + 4 * NT - 1) / (4 * NT);
+  return (int)((rows + LZ_BLOCKS - 1) / LZ_BLOCKS) * 4 * NT;
+}
+
+int lanczos_blocks(const sgw_ctx *ctx) {
+  const int chunk = lanczos_chunk(ctx);
+  return (int)((ctx->N + chunk - 1) / chunk);
+}
+
+__device__ __forceinline__ double wave_total(double s) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (threadIdx.x == 0) sh[0] = s;
-  }
-  __syncthreads();
-  const double t = sh[0];
-  __syncthreads();
-  return t;
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  return s;
 }
 
-// a = sum of dots; w <- w - a v - b vp (b: the norm of the step before);
-// norms[block] = |w|^2 of the block's points
+// sum over the workgroup, on thread 0
+__device__ __forceinline__ double lanczos_block_sum(double s, double *sh) {
+  s = wave_total(s);
+  if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = s;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < NT / 64; ++w) s += sh[w];
+  return s;
+}
+
+// out[block] = Re <a|b> over the block's points
 template <typename R>
-__global__ __launch_bounds__(NT) void k_lanczos_update(const cplx<R> *v, const cplx<R> *vp,
-                                                       cplx<R> *w, int64_t N, const double *dots,
-                                                       int nblk, double *alpha, const double *b,
-                                                       double *norms) {
-  __shared__ double sh[NT];
-  const double a = partial_total(dots, nblk, sh);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
-  const R ca = (R)-a, cb = (R)-*b;
-  const int64_t r0 = (int64_t)blockIdx.x * RCHUNK, r1 = std::min<int64_t>(N, r0 + RCHUNK);
+__global__ __launch_bounds__(NT) void k_lanczos_dot(const cplx<R> *a, const cplx<R> *b, int64_t N,
+                                                    int chunk, double *out) {
+  __shared__ double sh[NT / 64];
+  const int64_t r0 = (int64_t)blockIdx.x * chunk, r1 = std::min<int64_t>(N, r0 + chunk);
   double acc = 0;
-  for (int64_t r = r0 + threadIdx.x; r < r1; r += NT) {
-    const cplx<R> x = v[r], y = vp[r];
-    cplx<R> o = w[r];
-    o.x += ca * x.x;
-    o.y += ca * x.y;
-    o.x += cb * y.x;
-    o.y += cb * y.y;
-    w[r] = o;
-    acc += (double)o.x * o.x + (double)o.y * o.y;
+  for (int64_t r = r0 + threadIdx.x; r < r1; r += 4 * NT) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (r + u * NT < r1) {
+        const cplx<R> x = a[r + u * NT], y = b[r + u * NT];
+        acc += (double)x.x * y.x + (double)x.y * y.y;
+      }
   }
-  const double s = block_sum(acc, sh);
-  if (threadIdx.x == 0) norms[blockIdx.x] = s;
+  acc = lanczos_block_sum(acc, sh);
+  if (threadIdx.x == 0) out[blockIdx.x] = acc;
 }
 
-// b = sqrt(sum of norms); vp <- v (0 on the first call), v <- w / b (0 where b = 0)
+// w = H u becomes the next vector; norms[block] = |w|^2 of the block's points.
+// dots, unorm: partial sums of <u|w> and |u|^2.  beta[j] = |u| is written,
+// beta[j - 1] is the one before (up = u_{j-1}, not read on the first step).
 template <typename R>
-__global__ __launch_bounds__(NT) void k_lanczos_next(cplx<R> *v, cplx<R> *vp, const cplx<R> *w,
-                                                     int64_t N, const double *norms, int nblk,
-                                                     double *beta, int first) {
-  __shared__ double sh[NT];
-  const double b = sqrt(partial_total(norms, nblk, sh));
-  if (blockIdx.x == 0 && threadIdx.x == 0) *beta = first ? 0.0 : b;
-  const R inv = b > 0 ? (R)(1.0 / b) : (R)0;
-  const int64_t r0 = (int64_t)blockIdx.x * RCHUNK, r1 = std::min<int64_t>(N, r0 + RCHUNK);
-  for (int64_t r = r0 + threadIdx.x; r < r1; r += NT) {
-    const cplx<R> x = w[r];
-    cplx<R> old;
-    old.x = old.y = 0;
-    if (!first) old = v[r];
-    vp[r] = old;
-    v[r] = cscale(x, inv);
+__global__ __launch_bounds__(NT) void k_lanczos_update(const cplx<R> *u, const cplx<R> *up,
+                                                       cplx<R> *w, int64_t N, int chunk,
+                                                       const double *dots, const double *unorm,
+                                                       int nblk, double *alpha, double *beta,
+                                                       int first, double *norms) {
+  __shared__ double sh[NT / 64], tot[2];
+  const int wave = threadIdx.x / 64;
+  if (wave < 2) {
+    const double *p = wave == 0 ? dots : unorm;
+    double s = 0;
+    for (int i = threadIdx.x % 64; i < nblk; i += 64) s += p[i];
+    s = wave_total(s);
+    if (threadIdx.x % 64 == 0) tot[wave] = s;
   }
+  __syncthreads();
+  const double b2 = tot[1], b = sqrt(b2), ib = b > 0 ? 1.0 / b : 0.0;
+  const double a = b > 0 ? tot[0] / b2 : 0.0;
+  const double bp = first ? 0.0 : beta[-1];
+  const R ca = (R)-a, ci = (R)ib, cb = (R)(bp > 0 ? -b / bp : 0.0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *alpha = a;
+    *beta = b;
+  }
+  const int64_t r0 = (int64_t)blockIdx.x * chunk, r1 = std::min<int64_t>(N, r0 + chunk);
+  double acc = 0;
+  for (int64_t r = r0 + threadIdx.x; r < r1; r += 4 * NT) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (r + q * NT < r1) {
+        const cplx<R> x = u[r + q * NT];
+        cplx<R> o = w[r + q * NT];
+        o.x = (o.x + ca * x.x) * ci;
+        o.y = (o.y + ca * x.y) * ci;
+        if (!first) {
+          const cplx<R> y = up[r + q * NT];
+          o.x += cb * y.x;
+          o.y += cb * y.y;
+        }
+        w[r + q * NT] = o;
+        acc += (double)o.x * o.x + (double)o.y * o.y;
+      }
+  }
+  acc = lanczos_block_sum(acc, sh);
+  if (threadIdx.x == 0) norms[blockIdx.x] = acc;
+}
+
+// *b = sqrt(sum of norms); one wave
+__global__ __launch_bounds__(64) void k_lanczos_norm(const double *norms, int nblk, double *b) {
+  double s = 0;
+  for (int i = threadIdx.x; i < nblk; i += 64) s += norms[i];
+  s = wave_total(s);
+  if (threadIdx.x == 0) *b = sqrt(s);
 }
 
 template <typename R>
-static void lanczos_norm_t(sgw_ctx *ctx, const void *w, double *norms, int nblk) {
-  hipLaunchKernelGGL((k_reduce1<R, RED_NORM2>), dim3(nblk, 1), dim3(NT), 0, ctx->stream,
-                     static_cast<const cplx<R> *>(w), static_cast<const cplx<R> *>(nullptr),
-                     ctx->N, ctx->N, norms, nblk);
+static void lanczos_dot_t(sgw_ctx *ctx, const void *a, const void *b, double *out) {
+  hipLaunchKernelGGL(k_lanczos_dot<R>, dim3(lanczos_blocks(ctx)), dim3(NT), 0, ctx->stream,
+                     static_cast<const cplx<R> *>(a), static_cast<const cplx<R> *>(b), ctx->N,
+                     lanczos_chunk(ctx), out);
 }
 
-int lanczos_blocks(const sgw_ctx *ctx) { return (int)((ctx->N + RCHUNK - 1) / RCHUNK); }
-
 template <typename R>
-static void lanczos_start_t(sgw_ctx *ctx, void *v, void *vp, void *w, double *beta,
-                            double *partial) {
+static void lanczos_step_t(sgw_ctx *ctx, const void *u, const void *up, void *w, double *alpha,
+                           double *beta, bool first, double *dots, const double *unorm,
+                           double *norms) {
   const int nblk = lanczos_blocks(ctx);
-  lanczos_norm_t<R>(ctx, w, partial + nblk, nblk);
-  hipLaunchKernelGGL(k_lanczos_next<R>, dim3(nblk), dim3(NT), 0, ctx->stream,
-                     static_cast<cplx<R> *>(v), static_cast<cplx<R> *>(vp),
-                     static_cast<const cplx<R> *>(w), ctx->N, partial + nblk, nblk, beta, 1);
+  lanczos_dot_t<R>(ctx, u, w, dots);
+  hipLaunchKernelGGL(k_lanczos_update<R>, dim3(nblk), dim3(NT), 0, ctx->stream,
+                     static_cast<const cplx<R> *>(u), static_cast<const cplx<R> *>(up),
+                     static_cast<cplx<R> *>(w), ctx->N, lanczos_chunk(ctx), dots, unorm, nblk,
+                     alpha, beta, first ? 1 : 0, norms);
 }
 
-template <typename R>
-static void lanczos_step_t(sgw_ctx *ctx, void *v, void *vp, void *w, double *alpha, double *beta,
-                           double *partial) {
-  const int nblk = lanczos_blocks(ctx);
-  cplx<R> *V = static_cast<cplx<R> *>(v), *P = static_cast<cplx<R> *>(vp);
-  cplx<R> *W = static_cast<cplx<R> *>(w);
-  hipLaunchKernelGGL((k_reduce1<R, RED_REDOT>), dim3(nblk, 1), dim3(NT), 0, ctx->stream, V, W,
-                     ctx->N, ctx->N, partial, nblk);
-  hipLaunchKernelGGL(k_lanczos_update<R>, dim3(nblk), dim3(NT), 0, ctx->stream, V, P, W, ctx->N,
-                     partial, nblk, alpha, beta, partial + nblk);
-  hipLaunchKernelGGL(k_lanczos_next<R>, dim3(nblk), dim3(NT), 0, ctx->stream, V, P, W, ctx->N,
-                     partial + nblk, nblk, beta + 1, 0);
-}
-
-void launch_lanczos_start(sgw_ctx *ctx, void *v, void *vp, void *w, double *beta,
-                          double *partial) {
-  if (ctx->dbl) lanczos_start_t<double>(ctx, v, vp, w, beta, partial);
-  else lanczos_start_t<float>(ctx, v, vp, w, beta, partial);
+void launch_lanczos_start(sgw_ctx *ctx, const void *u, double *norms) {
+  if (ctx->dbl) lanczos_dot_t<double>(ctx, u, u, norms);
+  else lanczos_dot_t<float>(ctx, u, u, norms);
   SGW_HIP(hipGetLastError());
 }
 
-void launch_lanczos_step(sgw_ctx *ctx, void *v, void *vp, void *w, double *alpha, double *beta,
-                         double *partial) {
-  if (ctx->dbl) lanczos_step_t<double>(ctx, v, vp, w, alpha, beta, partial);
-  else lanczos_step_t<float>(ctx, v, vp, w, alpha, beta, partial);
+void launch_lanczos_step(sgw_ctx *ctx, const void *u, const void *up, void *w, double *alpha,
+                         double *beta, bool first, double *dots, const double *unorm,
+                         double *norms) {
+  if (ctx->dbl)
+    lanczos_step_t<double>(ctx, u, up, w, alpha, beta, first, dots, unorm, norms);
+  else
+    lanczos_step_t<float>(ctx, u, up, w, alpha, beta, first, dots, unorm, norms);
+  SGW_HIP(hipGetLastError());
+}
+
+void launch_lanczos_end(sgw_ctx *ctx, const double *norms, double *beta) {
+  hipLaunchKernelGGL(k_lanczos_norm, dim3(1), dim3(64), 0, ctx->stream, norms,
+                     lanczos_blocks(ctx), beta);
   SGW_HIP(hipGetLastError());
 }
 

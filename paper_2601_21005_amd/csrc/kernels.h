@@ -41,15 +41,17 @@ void launch_redot(sgw_ctx *ctx, const void *a, const void *b, int64_t ld, int64_
                   double *d_out);
 
 // ---- Lanczos (sgw_lanczos_bounds)
-// workgroups of the Lanczos kernels; `partial` holds twice as many doubles
+// partial sums (one a workgroup) of the arrays dots, unorm and norms below
 int lanczos_blocks(const sgw_ctx *ctx);
-// v = w / |w|, vp = 0, *beta = 0
-void launch_lanczos_start(sgw_ctx *ctx, void *v, void *vp, void *w, double *beta,
-                          double *partial);
-// with w = H v: *alpha = <v|w>, w -= alpha v + beta[0] vp, beta[1] = |w|,
-// vp = v, v = w / beta[1]
-void launch_lanczos_step(sgw_ctx *ctx, void *v, void *vp, void *w, double *alpha, double *beta,
-                         double *partial);
+// norms = |u|^2
+void launch_lanczos_start(sgw_ctx *ctx, const void *u, double *norms);
+// with w = H u and unorm = |u|^2: *alpha = <u|w> / |u|^2, *beta = |u|, w = (w -
+// alpha u) / beta[0] - beta[0] / beta[-1] up (first: without up), norms = |w|^2
+void launch_lanczos_step(sgw_ctx *ctx, const void *u, const void *up, void *w, double *alpha,
+                         double *beta, bool first, double *dots, const double *unorm,
+                         double *norms);
+// *beta = sqrt(sum of norms)
+void launch_lanczos_end(sgw_ctx *ctx, const double *norms, double *beta);
 
 // ---- white noise and unpacking (sgw_sigma_estimate)
 // Filter input: complex vector k carries real noise vectors 2k and 2k+1 of the

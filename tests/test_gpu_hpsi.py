@@ -250,6 +250,28 @@ def test_lanczos_bounds_match_oracle(tiny8, tiny8_eig):
     assert lo <= e[0] and hi >= e[-1]
 
 
+@pytest.mark.parametrize("prec", [sgw.SGW_C128, sgw.SGW_C64])
+@pytest.mark.parametrize("n, steps", [(8, 2), (12, 3), (40, 13), (96, 7)])
+def test_lanczos_vector_rotation_and_block_edges(n, steps, prec):
+    """Short Lanczos runs on grids below one workgroup's points, with a part
+    of one at the end, and with two rows a workgroup (96^3), after step
+    counts that leave the three vectors in each order, against the oracle.
+    The oracle's vectors are normalised, the device's are not.  Each product
+    is within TOL of the exact one, so `steps` of them move the ends by less
+    than 10 steps TOL of the width (10: residuals and last components)."""
+    from conftest import build_oracle_h
+    from oracle import eigen
+    from paper_2601_21005_amd import systems
+    s = systems.gaussian_wells(seed=5, n=n, h=0.6, nwell=4)
+    H = build_oracle_h(s, workers=8)
+    ctx = make_ctx(s, prec)
+    lo, hi = ctx.lanczos_bounds(steps, seed=4, pad=0.02)
+    ctx.close()
+    lo_o, hi_o = eigen.lanczos_bounds(H, steps, seed=4, pad=0.02)
+    tol = 10 * steps * TOL[prec] * (hi_o - lo_o)
+    assert abs(lo - lo_o) < tol and abs(hi - hi_o) < tol
+
+
 def test_lanczos_bounds_si35h36_fp32(si35):
     """On the 64^3 cluster in complex FP32 the Lanczos interval encloses the
     extreme eigenvalues that the oracle's ARPACK eigensolvers give
