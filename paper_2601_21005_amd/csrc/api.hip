@@ -194,10 +194,13 @@ void cheb_term(sgw_ctx *ctx, void *cur, void *old, void *acc, void *tmp, void *k
                void *tmp2 = nullptr, bool rev = false, bool ovl = false) {
   const int64_t N = ctx->N;
   const double s2 = first ? 1.0 : 2.0;
-  // with ovl the projections of v_n go on the second stream, beside the FFT
-  // passes (both only read v_n), and the scatter waits for them
+  // the projections of v_n: in small batches in the FFT passes themselves, with
+  // ovl on the second stream beside them (all only read v_n; the scatter waits)
+  const bool ride = kb_rides(ctx, nvec, N);
+  const KbRide kb{cur, N, kbC};
+  ovl = ovl && !ride;
   if (ctx->has_kb && ovl) fork_gather(ctx, cur, nvec, N, kbC);
-  else if (ctx->has_kb) kb_gather_e(ctx, cur, nvec, N, kbC);
+  else if (ctx->has_kb && !ride) kb_gather_e(ctx, cur, nvec, N, kbC);
   EpiArgs e;
   e.x = cur;
   e.vold = old;
@@ -213,7 +216,8 @@ void cheb_term(sgw_ctx *ctx, void *cur, void *old, void *acc, void *tmp, void *k
   e.scale2 = s2;
   e.coef_dev = coef_dev;
   e.term_dev = coef_dev ? ctx->d_counter.as<int>() : nullptr;
-  fft3d_apply(ctx, cur, tmp, nullptr, nvec, N, MUL_KIN, 0.0, PLANE_INV_CHEB, e, 0, tmp2, rev);
+  fft3d_apply(ctx, cur, tmp, nullptr, nvec, N, MUL_KIN, 0.0, PLANE_INV_CHEB, e, 0, tmp2, rev,
+              ride ? &kb : nullptr);
   if (ctx->has_kb && ovl) join_gather(ctx);
   if (ctx->has_kb) kb_scatter(ctx, kbC, nvec, out ? out : old, N, s2 * invR);
 }
@@ -528,14 +532,17 @@ void apply_h(sgw_ctx *ctx, const void *psi, void *hpsi, int64_t nvec, int64_t ld
     const char *x = static_cast<const char *>(psi) + v0 * ld * ctx->csize();
     char *y = static_cast<char *>(hpsi) + v0 * ld * ctx->csize();
     void *kbC = nullptr;
+    const bool ride = kb_rides(ctx, nv, ld);
+    KbRide kb{x, ld};
     if (ctx->has_kb) {
-      kbC = ctx->buf("kbC", ctx->csize() * ctx->kb.nproj * nv).p;
-      kb_gather_e(ctx, x, nv, ld, kbC);
+      kb.out = kbC = ctx->buf("kbC", ctx->csize() * ctx->kb.nproj * nv).p;
+      if (!ride) kb_gather_e(ctx, x, nv, ld, kbC);
     }
     EpiArgs e;
     e.x = x;
     e.vloc = ctx->d_vloc.p;
-    fft3d_apply(ctx, x, tmp, y, nv, ld, MUL_KIN, 0.0, PLANE_INV_HPSI, e);
+    fft3d_apply(ctx, x, tmp, y, nv, ld, MUL_KIN, 0.0, PLANE_INV_HPSI, e, 0, nullptr, false,
+                ride ? &kb : nullptr);
     if (ctx->has_kb) kb_scatter(ctx, kbC, nv, y, ld, 1.0);
   }
 }
@@ -596,15 +603,18 @@ void apply_h_noalloc(sgw_ctx *ctx, const void *psi, void *hpsi, int64_t nvec, in
     const char *x = static_cast<const char *>(psi) + v0 * ld * ctx->csize();
     char *y = static_cast<char *>(hpsi) + v0 * ld * ctx->csize();
     void *kbC = nullptr;
+    const bool ride = kb_rides(ctx, nv, ld);
+    KbRide kb{x, ld};
     if (ctx->has_kb) {
-      void *partial = scr;
-      kbC = static_cast<char *>(scr) + align256(part_per * nv);
-      kb_gather_e(ctx, x, nv, ld, kbC, partial);
+      kb.partial = scr;
+      kb.out = kbC = static_cast<char *>(scr) + align256(part_per * nv);
+      if (!ride) kb_gather_e(ctx, x, nv, ld, kbC, scr);
     }
     EpiArgs e;
     e.x = x;
     e.vloc = ctx->d_vloc.p;
-    fft3d_apply(ctx, x, y, y, nv, ld, MUL_KIN, 0.0, PLANE_INV_HPSI, e, ld);
+    fft3d_apply(ctx, x, y, y, nv, ld, MUL_KIN, 0.0, PLANE_INV_HPSI, e, ld, nullptr, false,
+                ride ? &kb : nullptr);
     if (ctx->has_kb) kb_scatter(ctx, kbC, nv, y, ld, 1.0);
   }
 }

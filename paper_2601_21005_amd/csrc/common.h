@@ -300,6 +300,16 @@ struct EpiArgs {
   const int *term_dev = nullptr;
 };
 
+// Projections out[p][v] = E_p <beta_p|psi_v> that the passes of fft3d_apply
+// carry along where kb_rides says so (partial: kb_partial_bytes_per_vec per
+// vector, nullptr: the context's scratch); `out` is ready when they have run
+struct KbRide {
+  const void *psi = nullptr;
+  int64_t ld = 0;
+  void *out = nullptr;
+  void *partial = nullptr;
+};
+
 // Full forward+multiply+inverse 3D transform of nvec vectors of `src` (ld),
 // result written through the inverse pass mode into dst / epilogue outputs.
 // tmp holds nvec vectors ld_tmp apart (0: N); it may be dst itself when
@@ -311,13 +321,20 @@ struct EpiArgs {
 void fft3d_apply(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t nvec,
                  int64_t ld, MulMode mul, double tau, PlaneMode inv_mode,
                  const EpiArgs &epi, int64_t ld_tmp = 0, void *tmp2 = nullptr,
-                 bool rev = false);
+                 bool rev = false, const KbRide *kb = nullptr);
+
+// whether the forward plane pass of this grid is built with a gather beside it
+bool fft_carries_kb(const sgw_ctx *ctx);
 
 // KB (kb.hip)
 // C[p][v] = <beta_p|psi_v>  (kb_gather_e: times E_p)
 void kb_gather(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, void *coef_out);
 void kb_gather_e(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, void *coef_out,
                  void *partial = nullptr);
+// small batches in complex FP32: the gather has fewer than four workgroups per
+// CU, so the FFT passes that read the same vectors carry it (KbRide; the same
+// bits as kb_gather_e)
+bool kb_rides(const sgw_ctx *ctx, int64_t nvec, int64_t ld);
 // bytes of per-(tile, projector) partial sums the gather needs per vector
 size_t kb_partial_bytes_per_vec(const sgw_ctx *ctx);
 // C' = K C  (K complex [nproj][nproj] in the working precision)

@@ -256,7 +256,8 @@ void launch_redot(sgw_ctx *ctx, const void *a, const void *b, int64_t ld, int64_
 // FP64, and there are up to LZ_BLOCKS of them (one a CU at 64^3).
 // Lanczos interval of 60 steps at 64^3: 10.7 ms with the scalars fetched to
 // the host (two synchronisations and ten launches a step), 3.8 with them on
-// the device, 64 workgroups and a third launch for v_{j+1}, 3.2 now.
+// the device, 64 workgroups and a third launch for v_{j+1}, 3.2 with two, 2.7 now that
+// the gather rides with the FFT passes.
 constexpr int LZ_BLOCKS = 512;
 
 // points of a workgroup: a multiple of 4 NT

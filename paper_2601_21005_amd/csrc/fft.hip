@@ -12,6 +12,7 @@
 //   xlines, ypencil  x lines and y columns in two passes, where a plane does
 //           not fit in LDS (160^2 in complex FP64).
 #include "fft_reg.h"
+#include "kb_gather.h"
 
 namespace sgw {
 
@@ -136,18 +137,17 @@ template <typename R, int N, int MODE = PLANE_FWD> struct PlaneShape {
   static constexpr bool fits = lds <= 160 * 1024 && !(D && N == 112) && !(!D && N == 160);
 };
 
+// plane z of vector v; s: N P values (twice as many unless SPLIT), tw: N
 template <typename R, int N, int MODE>
-__global__ __launch_bounds__((PlaneShape<R, N>::T), (PlaneShape<R, N, MODE>::WPE)) void k_plane(PassArgs a) {
+__device__ __forceinline__ void plane_pass(const PassArgs &a, int z, int64_t v, R *s,
+                                           cplx<R> *tw) {
   constexpr bool INV = MODE != PLANE_FWD;
   using C = cplx<R>;
   using Sh = PlaneShape<R, N, MODE>;
   constexpr int R1 = Radix<N>::R1, R2 = Radix<N>::R2, P = Sh::P, T = Sh::T;
   constexpr bool YF = INV && Sh::YFIRST;
-  __shared__ R s[N * P * (Sh::SPLIT ? 1 : 2)];
-  __shared__ C tw[N];
   const int tid = threadIdx.x;
-  const int64_t v = a.rev ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
-  const int64_t plane = (int64_t)blockIdx.x * (N * N);
+  const int64_t plane = (int64_t)z * (N * N);
   const C *src = static_cast<const C *>(a.src) + v * a.ld_src + plane;
   Stage<C, R1, N * R2, T> s1;
   Stage<C, R2, N * R1, T> s2;
@@ -282,6 +282,44 @@ __global__ __launch_bounds__((PlaneShape<R, N>::T), (PlaneShape<R, N, MODE>::WPE
   }
 }
 
+// vector of a workgroup in the passes' order
+__device__ __forceinline__ int64_t vec_of(const PassArgs &a, int i, int nvec) {
+  return a.rev ? nvec - 1 - i : i;
+}
+
+template <typename R, int N, int MODE>
+__global__ __launch_bounds__((PlaneShape<R, N>::T), (PlaneShape<R, N, MODE>::WPE)) void k_plane(PassArgs a) {
+  using Sh = PlaneShape<R, N, MODE>;
+  __shared__ R s[N * Sh::P * (Sh::SPLIT ? 1 : 2)];
+  __shared__ cplx<R> tw[N];
+  plane_pass<R, N, MODE>(a, blockIdx.x, vec_of(a, blockIdx.y, gridDim.y), s, tw);
+}
+
+// The forward pass of a small batch with the projector gather of the same
+// vectors beside it, in the first workgroups (their waves past the gather's
+// four end at once).  A launch costs about as much as either does on one or a
+// few vectors, and neither fills the device.  H psi with the gather and the
+// reduction (k_pencil_reduce) in launches of their own and beside the passes:
+// 40^3 1 vector 29.2 -> 22.2 us, 8 vectors 38.8 -> 30.7, 48 vectors 78 -> 69;
+// 64^3 1 vector 40.5 -> 32.7, 16 vectors 82.6 -> 75.0; 96^3 8 vectors 125 ->
+// 117.  Registers are the larger of the two parts', which the planes of a
+// large batch would pay for in waves: kb_rides ends at 1024 gather workgroups,
+// from where (64^3, 32 vectors: 135 us either way) nothing is gained.
+template <int N>
+__global__ __launch_bounds__((PlaneShape<float, N>::T), (PlaneShape<float, N>::WPE)) void
+k_plane_gather(PassArgs a, KbGather<float> g, int nvec) {
+  using Sh = PlaneShape<float, N>;
+  __shared__ __align__(16) float s[N * Sh::P > RIDE_LDS ? N * Sh::P : RIDE_LDS];
+  __shared__ float2 tw[N];
+  const int ng = g.gx * g.gy, b = blockIdx.x;
+  if (b < ng) {
+    if (threadIdx.x < NTK)
+      gather_tile<OpF32, RIDE_NVB, RIDE_MT, N % 16 == 0 ? 4 : 3>(g, b % g.gx, b / g.gx, g.gy, s);
+    return;
+  }
+  plane_pass<float, N, PLANE_FWD>(a, (b - ng) % a.nz, vec_of(a, (b - ng) / a.nz, nvec), s, tw);
+}
+
 // ----------------------------------------------------------------- xlines
 template <typename R, int NX, int NL, int MODE>
 __global__ __launch_bounds__(NT_FFT) void k_xlines(PassArgs a) {
@@ -413,17 +451,16 @@ template <typename R, int N, int TX> struct PencilShape {
   static constexpr bool ALT = !D && N == 96 && TX == 32;   // see butterfly
 };
 
+// columns block bx of vector v; s: N P complex (N P values where SPLIT), tw: N
 template <typename R, int N, int TX>
-__global__ __launch_bounds__((PencilShape<R, N, TX>::T)) void k_pencil(PassArgs a) {
+__device__ __forceinline__ void pencil_pass(const PassArgs &a, int bx, int64_t v, R *s,
+                                            cplx<R> *tw) {
   using C = cplx<R>;
   using Sh = PencilShape<R, N, TX>;
   constexpr int R1 = Radix<N>::R1, R2 = Radix<N>::R2, P = Sh::P, T = Sh::T;
-  __shared__ R s[N * P * (Sh::SPLIT ? 1 : 2)];
-  __shared__ C tw[N];
   const int tid = threadIdx.x;
   const int nxb = a.nx / TX;
-  const int x0 = (blockIdx.x % nxb) * TX, y = blockIdx.x / nxb;
-  const int64_t v = a.rev ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+  const int x0 = (bx % nxb) * TX, y = bx / nxb;
   const int64_t stride = (int64_t)a.nx * a.ny;
   const int64_t base = x0 + (int64_t)y * a.nx;
   // in place on dst, or from src (ld_src) into dst when src is given
@@ -470,6 +507,33 @@ __global__ __launch_bounds__((PencilShape<R, N, TX>::T)) void k_pencil(PassArgs 
       for (int i = 0; i < R2; ++i) data[(b / TX + i * R1) * stride + b % TX] = cconj(s2.v[q][i]);
     });
   }
+}
+
+template <typename R, int N, int TX>
+__global__ __launch_bounds__((PencilShape<R, N, TX>::T)) void k_pencil(PassArgs a) {
+  using Sh = PencilShape<R, N, TX>;
+  __shared__ R s[N * Sh::P * (Sh::SPLIT ? 1 : 2)];
+  __shared__ cplx<R> tw[N];
+  pencil_pass<R, N, TX>(a, blockIdx.x, vec_of(a, blockIdx.y, gridDim.y), s, tw);
+}
+
+// the z pass with the reduction of the gather's partial sums beside it, as in
+// k_plane_gather (workgroups of four waves and more)
+template <int N, int TX>
+__global__ __launch_bounds__((PencilShape<float, N, TX>::T)) void k_pencil_reduce(
+    PassArgs a, KbReduce<float> r, int nvec) {
+  using Sh = PencilShape<float, N, TX>;
+  constexpr int E = N * Sh::P * (Sh::SPLIT ? 1 : 2);
+  __shared__ __align__(16) float s[E > 4 * NTK ? E : 4 * NTK];
+  __shared__ float2 tw[N];
+  const int nr = r.gx * r.nproj, b = blockIdx.x;
+  if (b < nr) {
+    if (threadIdx.x < NTK)
+      reduce_projector<float>(r, b % r.gx, b / r.gx, reinterpret_cast<double2 *>(s));
+    return;
+  }
+  const int npen = a.nx / TX * a.ny;
+  pencil_pass<float, N, TX>(a, (b - nr) % npen, vec_of(a, (b - nr) / npen, nvec), s, tw);
 }
 
 // ----------------------------------------------------------------- dispatch
@@ -519,6 +583,25 @@ template <typename R, int N> struct Kernels {
   }
 };
 
+// the passes that carry the projector gather and its reduction (FP32, planes
+// and pencils of at least the gather's four waves)
+template <int N> struct RideKernels {
+  static constexpr int TX = pencil_tx_wide<float, N>();
+  static constexpr bool plane_ok = PlaneShape<float, N>::fits && PlaneShape<float, N>::T >= NTK;
+  static constexpr bool pencil_ok = PencilShape<float, N, TX>::T >= NTK;
+  static void plane(int nvec, hipStream_t st, const PassArgs &a, const KbGather<float> &g) {
+    if constexpr (plane_ok)
+      hipLaunchKernelGGL(k_plane_gather<N>, dim3(g.gx * g.gy + a.nz * nvec),
+                         dim3(PlaneShape<float, N>::T), 0, st, a, g, nvec);
+  }
+  static void pencil(int nvec, hipStream_t st, const PassArgs &a, const KbReduce<float> &r) {
+    if constexpr (pencil_ok)
+      hipLaunchKernelGGL((k_pencil_reduce<N, TX>),
+                         dim3(r.gx * r.nproj + a.nx / TX * a.ny * nvec),
+                         dim3(PencilShape<float, N, TX>::T), 0, st, a, r, nvec);
+  }
+};
+
 struct SizeOps {
   void (*xy)(dim3, hipStream_t, const PassArgs &);
   void (*ypencil)(dim3, hipStream_t, const PassArgs &);
@@ -526,12 +609,20 @@ struct SizeOps {
   void (*pencil_wide)(dim3, hipStream_t, const PassArgs &);
   bool has_plane;
   int tx, nl, tx_wide;
+  // with projector work beside them; nullptr where not built
+  void (*plane_kb)(int, hipStream_t, const PassArgs &, const KbGather<float> &) = nullptr;
+  void (*pencil_kb)(int, hipStream_t, const PassArgs &, const KbReduce<float> &) = nullptr;
 };
 
 template <typename R, int N> SizeOps make_ops() {
   using K = Kernels<R, N>;
-  return SizeOps{&K::xy, &K::ypencil, &K::pencil, &K::pencil_wide, PlaneShape<R, N>::fits,
-                 pencil_tx<N>(), xlines_nl<N>(), pencil_tx_wide<R, N>()};
+  SizeOps o{&K::xy, &K::ypencil, &K::pencil, &K::pencil_wide, PlaneShape<R, N>::fits,
+            pencil_tx<N>(), xlines_nl<N>(), pencil_tx_wide<R, N>()};
+  if constexpr (sizeof(R) == 4 && N % 8 == 0) {      // projector grids
+    if (RideKernels<N>::plane_ok) o.plane_kb = &RideKernels<N>::plane;
+    if (RideKernels<N>::pencil_ok) o.pencil_kb = &RideKernels<N>::pencil;
+  }
+  return o;
 }
 
 template <typename R> bool get_ops(int n, SizeOps &o) {
@@ -561,10 +652,17 @@ bool fft_pencils_cover(int nx, int ny, int nz, bool dbl) {
   return ok && nx % oz.tx == 0 && nx % oy.tx == 0;
 }
 
+bool fft_carries_kb(const sgw_ctx *ctx) {
+  SizeOps o;
+  return !ctx->dbl && get_ops<float>(ctx->nx, o) && o.plane_kb && ctx->kb_ly == 3 &&
+         ctx->kb_lx == (ctx->nx % 16 == 0 ? 4 : 3);
+}
+
 template <typename R>
 void fft3d_apply_t(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t nvec,
                    int64_t ld, MulMode mul, double tau, PlaneMode inv_mode,
-                   const EpiArgs &epi, int64_t ldt, void *tmp2, bool rev) {
+                   const EpiArgs &epi, int64_t ldt, void *tmp2, bool rev,
+                   const KbRide *kb) {
   using C = cplx<R>;
   SizeOps ox, oy, oz;
   SGW_REQUIRE(get_ops<R>(ctx->nx, ox) && get_ops<R>(ctx->ny, oy) && get_ops<R>(ctx->nz, oz),
@@ -608,7 +706,8 @@ void fft3d_apply_t(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t 
     f.src = srcv; f.dst = tmpv; f.ld_src = ld; f.ld_dst = ldt; f.mode = PLANE_FWD; f.inverse = 0;
     f.rev = dir;
     f.tw0 = twx;
-    ox.xy(gxy, st, f);
+    if (kb) ox.plane_kb((int)nv, st, f, kb_ride_gather(ctx, *kb, nv));   // one chunk: kb_rides
+    else ox.xy(gxy, st, f);
     if (!use_plane) {
       PassArgs py = a;
       py.dst = tmpv; py.ld_dst = ldt; py.tw0 = twy; py.inverse = 0;
@@ -628,7 +727,11 @@ void fft3d_apply_t(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t 
     const auto fp = ctx->forced.find("pencil");
     const bool wide = oz.tx_wide != oz.tx && ctx->nx % oz.tx_wide == 0 &&
                       (fp == ctx->forced.end() || fp->second != 0);
-    if (wide)
+    const bool ride = kb && oz.pencil_kb && (wide || oz.tx_wide == oz.tx);
+    if (kb && !ride) kb_launch_reduce(ctx, kb_ride_reduce(ctx, *kb, nv));
+    if (ride)
+      oz.pencil_kb((int)nv, st, pz, kb_ride_reduce(ctx, *kb, nv));
+    else if (wide)
       oz.pencil_wide(dim3((ctx->nx / oz.tx_wide) * ctx->ny, nv), st, pz);
     else
       oz.pencil(dim3((ctx->nx / oz.tx) * ctx->ny, nv), st, pz);
@@ -660,13 +763,15 @@ void fft3d_apply_t(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t 
 
 void fft3d_apply(sgw_ctx *ctx, const void *src, void *tmp, void *dst, int64_t nvec,
                  int64_t ld, MulMode mul, double tau, PlaneMode inv_mode,
-                 const EpiArgs &epi, int64_t ld_tmp, void *tmp2, bool rev) {
+                 const EpiArgs &epi, int64_t ld_tmp, void *tmp2, bool rev, const KbRide *kb) {
   if (nvec <= 0) return;
   const int64_t ldt = ld_tmp > 0 ? ld_tmp : ctx->N;
   if (ctx->dbl)
-    fft3d_apply_t<double>(ctx, src, tmp, dst, nvec, ld, mul, tau, inv_mode, epi, ldt, tmp2, rev);
+    fft3d_apply_t<double>(ctx, src, tmp, dst, nvec, ld, mul, tau, inv_mode, epi, ldt, tmp2, rev,
+                          kb);
   else
-    fft3d_apply_t<float>(ctx, src, tmp, dst, nvec, ld, mul, tau, inv_mode, epi, ldt, tmp2, rev);
+    fft3d_apply_t<float>(ctx, src, tmp, dst, nvec, ld, mul, tau, inv_mode, epi, ldt, tmp2, rev,
+                         kb);
 }
 
 }  // namespace sgw

@@ -10,57 +10,14 @@
 //   scatter  dst_v(r) += s1 sum_e beta_e(r) C'[p(e)][v] on each tile's own
 //            points -- every point is written by exactly one workgroup, so
 //            no atomics and bitwise reproducible results.
-#include "common.h"
-#include "kernels.h"
+#include "kb_gather.h"
 
 namespace sgw {
 
-constexpr int NTK = 256;
-
-// flat grid index of point p of a tile of x extent 2^LX (y extent 8), in
-// 32-bit arithmetic (grids below 2^31 points)
-template <int LX>
-__device__ __forceinline__ int tile_point_c(int base, int p, int nx, int ny) {
-  const int x = p & ((1 << LX) - 1), y = (p >> LX) & 7, z = p >> (LX + 3);
-  return base + x + nx * (y + ny * z);
-}
-
-// out[p][v] = sum of projector p's partial sums (times E_p), FP64.  A
-// workgroup holds 2^lv vectors of one projector and splits its entries (some
-// 60 to 90) over the 256 >> lv threads of each vector, whose sums are added
-// in order: with one thread per vector a batch of 1 left 255 threads idle
-// behind a chain of loads (64^3: 8.9 us, now 3.8; 16 vectors 15.6 -> 5.1).
 template <typename R>
-__global__ __launch_bounds__(NTK) void k_kb_reduce(const cplx<R> *partial, const int *proj_off,
-                                                   const int *proj_entries, const double *ekb,
-                                                   int use_e, int64_t nvec, int lv,
-                                                   cplx<R> *out) {
+__global__ __launch_bounds__(NTK) void k_kb_reduce(KbReduce<R> a) {
   __shared__ double2 sh[NTK];
-  const int vl = threadIdx.x & ((1 << lv) - 1), part = threadIdx.x >> lv, np = NTK >> lv;
-  const int64_t v = ((int64_t)blockIdx.x << lv) + vl;
-  const int p = blockIdx.y;
-  double sr = 0, si = 0;
-  if (v < nvec) {
-    // unrolled so that several loads are in flight; the sum keeps its order
-#pragma unroll 8
-    for (int k = proj_off[p] + part; k < proj_off[p + 1]; k += np) {
-      const cplx<R> c = partial[(int64_t)proj_entries[k] * nvec + v];
-      sr += c.x;
-      si += c.y;
-    }
-  }
-  sh[threadIdx.x] = make_double2(sr, si);
-  for (int h = np / 2; h > 0; h >>= 1) {
-    __syncthreads();
-    if (part < h) {
-      const double2 a = sh[threadIdx.x], b = sh[threadIdx.x + (h << lv)];
-      sh[threadIdx.x] = make_double2(a.x + b.x, a.y + b.y);
-    }
-  }
-  if (part > 0 || v >= nvec) return;
-  double2 s = sh[threadIdx.x];
-  if (use_e) { s.x *= ekb[p]; s.y *= ekb[p]; }
-  out[(int64_t)p * nvec + v] = cmake<cplx<R>>(s.x, s.y);
+  reduce_projector<R>(a, blockIdx.x, blockIdx.y, sh);
 }
 
 template <typename R>
@@ -88,273 +45,10 @@ __global__ void k_kb_mix(const cplx<R> *K, const cplx<R> *in, cplx<R> *out, int 
   out[(int64_t)p * nvec + v] = cmake<cplx<R>>(sr, si);
 }
 
-// ---------------------------------------------------------------- MFMA
-// Per tile the gather is the GEMM  D[e][c] = sum_p beta[e][p] Psi[p][c]
-// (M = projector entries, K = 512 points, N = 2 NVB real columns = NVB
-// complex vectors) and the scatter  D[p][c] = sum_e beta[e][p] C'[e][c]
-// (M = 512 points, K = entries padded to the K group).  The operands are stored in
-// FP32 (SGW_C64) or in BF16 rounded to nearest even (SGW_C64_BF16KB; with
-// SGW_C64_BF16X2KB the psi / coefficient operand as two BF16 terms); the
-// accumulation is FP32 either way.  A lane feeds 16 contiguous bytes of A and
-// of B per group of K values:
-//   FP32: four v_mfma_f32_16x16x4f32, K group 16, lane l holds the K slots
-//         4 (l / 16) + s, s = 0..3, one per instruction;
-//   BF16: one v_mfma_f32_16x16x32_bf16, K group 32, lane l holds the K slots
-//         8 (l / 16) + s, s = 0..7;
-// lane l supplies row l % 16 of A and column l % 16 of B and receives
-// D[4 (l / 16) + r][l % 16] in accumulator register r.  Every variant below
-// (vectors per workgroup NVB, entry tiles per pass MT) computes each output
-// with the same instructions in the same order, so the choice changes the
-// speed, not a bit of the result.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-// float -> bfloat16 bits, round to nearest even (finite inputs)
-__host__ __device__ __forceinline__ uint32_t bf16_bits(float f) {
-  uint32_t u;
-  __builtin_memcpy(&u, &f, 4);
-  return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
-
-struct OpF32 {
-  using T = float;
-  static constexpr int GK = 16;
-  static constexpr bool SPLIT = false;
-  __device__ static void mma(f32x4 &acc, const u32x4 &a, const u32x4 &b) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[0]), __uint_as_float(b[0]), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[1]), __uint_as_float(b[1]), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[2]), __uint_as_float(b[2]), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[3]), __uint_as_float(b[3]), acc, 0, 0, 0);
-  }
-  __device__ static void put2(T *d, float x, float y) {
-    *reinterpret_cast<float2 *>(d) = make_float2(x, y);
-  }
-  __device__ static u32x4 pack(const float *e) {      // 4 values -> one operand
-    return u32x4{__float_as_uint(e[0]), __float_as_uint(e[1]), __float_as_uint(e[2]),
-                 __float_as_uint(e[3])};
-  }
-  __device__ static void put1(T *d, float x) { *d = x; }
-};
-
-struct OpBF16 {
-  using T = uint16_t;
-  static constexpr int GK = 32;
-  static constexpr bool SPLIT = false;
-  __device__ static void mma(f32x4 &acc, const u32x4 &a, const u32x4 &b) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                  __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-  }
-  __device__ static void put2(T *d, float x, float y) {
-    *reinterpret_cast<uint32_t *>(d) = bf16_bits(x) | (bf16_bits(y) << 16);
-  }
-  __device__ static void put1(T *d, float x) { *d = (uint16_t)bf16_bits(x); }
-  __device__ static u32x4 pack(const float *e) {      // 8 values -> one operand (RNE)
-    return u32x4{bf16_bits(e[0]) | (bf16_bits(e[1]) << 16), bf16_bits(e[2]) | (bf16_bits(e[3]) << 16),
-                 bf16_bits(e[4]) | (bf16_bits(e[5]) << 16), bf16_bits(e[6]) | (bf16_bits(e[7]) << 16)};
-  }
-};
-
-__device__ __forceinline__ float bf16_value(uint32_t b) { return __uint_as_float(b << 16); }
-
-// BF16 products with the state-vector operand (psi in the gather, the mixed
-// coefficients in the scatter) carried as two BF16 terms hi + lo, hi = RNE(x),
-// lo = RNE(x - hi): two MFMAs per operand pair, the split operand exact to
-// about 2^-17; beta stays one BF16 term.
-struct OpBF16x2 : OpBF16 {
-  static constexpr bool SPLIT = true;
-  __device__ static void pack2(const float *e, u32x4 &hi, u32x4 &lo) {
-    uint32_t h[8], l[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      h[i] = bf16_bits(e[i]);
-      l[i] = bf16_bits(e[i] - bf16_value(h[i]));
-    }
-    hi = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-    lo = u32x4{l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16)};
-  }
-  __device__ static void put1x2(T *dhi, T *dlo, float x) {
-    const uint32_t h = bf16_bits(x);
-    *dhi = (uint16_t)h;
-    *dlo = (uint16_t)bf16_bits(x - bf16_value(h));
-  }
-};
-
-// Workgroup -> (tile, vector block).  Consecutive workgroups go to the 8
-// XCDs in turn, so tile t is given to workgroups on XCD t % 8 only, and one
-// XCD walks all vector blocks of a tile in a row: the tile's beta rows are
-// read from memory once per XCD L2 instead of once per workgroup.
-__device__ __forceinline__ bool tile_block(int ntile, int nvb, int &t, int64_t &vb) {
-  const int b = blockIdx.x, xcd = b & 7, i = b >> 3;
-  t = xcd + 8 * (i / nvb);
-  vb = i % nvb;
-  return t < ntile;
-}
-
-inline dim3 tile_grid(int ntile, int64_t nvb) {
-  return dim3((unsigned)(8 * ((ntile + 7) / 8) * nvb));
-}
-
-template <class T> __device__ __forceinline__ u32x4 ld16(const T *p) {
-  return *reinterpret_cast<const u32x4 *>(p);
-}
-
-// partial[off + e][v] = dV sum_p beta_e(p) psi_v(p) for the entries e of tile t.
-// The B operand of lane (q, col) in K group g is EL consecutive tile points
-// (consecutive x, so EL consecutive complex values in memory) of the real
-// (col even) or imaginary (col odd) part of vector v0 + 8 n + col / 2: the
-// lane reads them straight from memory (lanes col and col ^ 1 read the same
-// bytes in the same instruction) -- no staging in LDS.  The tile's x extent
-// is 2^LX (y 8).  Lanes of vectors past nvec read the last vector and entry
-// rows past ne the last row: both only feed outputs that are never written,
-// so the loads need no branch.
 template <class Op, int NVB, int MT, int LX>
-__global__ __launch_bounds__(NTK) void k_kb_gather_mma(
-    const float2 *psi, int64_t ld, int64_t nvec, const int *tile_base, const int *tile_off,
-    const typename Op::T *beta, float2 *partial, int nx, int ny, float dV, int ntile,
-    int nvb, const uint32_t *__restrict__ tile_mask) {
-  using T = typename Op::T;
-  constexpr int NC = 2 * NVB, NTL = NC / 16;
-  constexpr int EL = 16 / (int)sizeof(T);           // operand elements per lane per group
-  constexpr int NG = 128 / Op::GK;                  // K groups of one wave (128 points)
-  static_assert(Op::GK == 16 || Op::GK == 32, "K group of 16 or 32 points");
-  constexpr int NS = Op::SPLIT ? NG : 1, NSN = Op::SPLIT ? NTL : 1;
-  __shared__ __align__(16) float red[4 * MT * NTL * 256];   // cross-wave sums
-  int t;
-  int64_t vb;
-  if (!tile_block(ntile, nvb, t, vb)) return;
-  const int64_t v0 = vb * NVB;
-  const int base = tile_base[t];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, col = lane & 15;
-  const int off = tile_off[t], ne = tile_off[t + 1] - off;
-  // the passes over the tile's entries are split over gridDim.y workgroups
-  // where there are too few vectors to fill the device
-  const int mg0 = blockIdx.y * 16 * MT, mstep = gridDim.y * 16 * MT;
-  if (mg0 >= ne) return;
-  // bit g of glive: some point of this wave's K group g (GK consecutive tile
-  // points) lies in a projector's support.  A group without one holds only
-  // zero beta values: its psi values are not loaded and its products (exact
-  // zeros) are not taken.  The condition is uniform over the wave.
-  uint32_t glive = 0;
-  const int wu = __builtin_amdgcn_readfirstlane(w);   // scalar loads of the four words
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t word = tile_mask[(int64_t)t * (KB_TP / 32) + 4 * wu + i];
-    if constexpr (Op::GK == 16)
-      glive |= ((word & 0xffffu) ? 1u : 0u) << (2 * i) | ((word >> 16) ? 1u : 0u) << (2 * i + 1);
-    else
-      glive |= (word ? 1u : 0u) << i;
-  }
-  glive = __builtin_amdgcn_readfirstlane(glive);
-  auto live = [&](int g) { return (glive >> g) & 1u; };
-  // B operands of this wave's quarter of K, kept in registers for all entries:
-  // every load of a live group is issued first, the lane exchanges follow
-  auto load_b = [&](int64_t v0, u32x4 (*b)[NTL], u32x4 (*blo)[NSN]) {
-    constexpr int NZ = EL / 4;
-    float4 z[NG][NTL][NZ];
-    // the lane pair (col, col ^ 1) reads each group of 4 complex values once:
-    // the even lane points 0, 1 and the odd lane points 2, 3
-    const int od = col & 1;
-#pragma unroll
-    for (int n = 0; n < NTL; ++n) {
-      const int64_t v = min(v0 + 8 * n + (col >> 1), nvec - 1);
-      const float2 *src = psi + v * ld;
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const int p = 128 * w + g * Op::GK + EL * q;  // EL consecutive points along x
-        const float4 *s4 = reinterpret_cast<const float4 *>(src + tile_point_c<LX>(base, p, nx, ny));
-#pragma unroll
-        for (int i = 0; i < NZ; ++i) z[g][n][i] = live(g) ? s4[2 * i + od] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    }
-    // then they swap the parts the other needs (real parts to the even lane,
-    // imaginary parts to the odd lane)
-#pragma unroll
-    for (int n = 0; n < NTL; ++n)
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        float e[EL];
-#pragma unroll
-        for (int i = 0; i < NZ; ++i) {
-          const float4 zz = z[g][n][i];
-          const float g0 = __shfl_xor(od ? zz.x : zz.y, 1, 64);
-          const float g1 = __shfl_xor(od ? zz.z : zz.w, 1, 64);
-          e[4 * i] = od ? g0 : zz.x;
-          e[4 * i + 1] = od ? g1 : zz.z;
-          e[4 * i + 2] = od ? zz.y : g0;
-          e[4 * i + 3] = od ? zz.w : g1;
-        }
-        if constexpr (Op::SPLIT) Op::pack2(e, b[g][n], blo[g][n]);
-        else b[g][n] = Op::pack(e);
-      }
-  };
-  // A operands (beta rows of MT entry tiles, one K group) alternate between
-  // two register sets: group g + 1 is requested before the products of group
-  // g (after the last group, the next pass's first one), so one group's loads
-  // are in flight behind the products (three in flight, with a ring of four,
-  // cost a wave per SIMD in registers and ran 5 % slower).  Entry rows past
-  // ne read row ne - 1: in bounds, and their products are never stored.
-  constexpr int D = 1, RA = 2;
-  static_assert(NG % RA == 0, "the A operands alternate with the K groups");
-  auto load_a = [&](int mg, int g, u32x4 *a) {
-#pragma unroll
-    for (int j = 0; j < MT; ++j) {
-      const int e = min(mg + 16 * j + col, ne - 1);   // A row = lane % 16
-      a[j] = ld16(beta + (int64_t)(off + e) * KB_TP + 128 * w + g * Op::GK + EL * q);
-    }
-  };
-  u32x4 a[RA][MT];
-#pragma unroll
-  for (int g = 0; g < D; ++g)
-    if (live(g)) load_a(mg0, g, a[g]);
-  u32x4 b[NG][NTL], blo[NS][NSN];
-  load_b(v0, b, blo);
-  for (int mg = mg0; mg < ne; mg += mstep) {
-    f32x4 acc[MT][NTL];
-#pragma unroll
-    for (int j = 0; j < MT; ++j)
-#pragma unroll
-      for (int n = 0; n < NTL; ++n) acc[j][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      if (live((g + D) % NG)) load_a(g + D < NG ? mg : mg + mstep, (g + D) % NG, a[(g + D) % RA]);
-      if (!live(g)) continue;
-#pragma unroll
-      for (int j = 0; j < MT; ++j)
-        if (mg + 16 * j < ne)
-#pragma unroll
-          for (int n = 0; n < NTL; ++n) {
-            Op::mma(acc[j][n], a[g % RA][j], b[g][n]);
-            if constexpr (Op::SPLIT) Op::mma(acc[j][n], a[g % RA][j], blo[g][n]);
-          }
-    }
-    // a barrier between the last products and the LDS writes of their
-    // accumulators (without it the <8, 2> instantiation read some
-    // accumulators before their last product had landed)
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < MT; ++j)
-#pragma unroll
-      for (int n = 0; n < NTL; ++n)
-        *reinterpret_cast<f32x4 *>(red + (((w * MT + j) * NTL + n) * 64 + lane) * 4) = acc[j][n];
-    __syncthreads();
-    // the four K quarters summed in wave order; one complex (entry, vector) per item
-    for (int o = tid; o < MT * 16 * NVB; o += NTK) {
-      const int j = o / (16 * NVB), er = (o / NVB) % 16, vl = o % NVB;
-      const int e = mg + 16 * j + er;
-      const int n = vl >> 3, lre = 16 * (er >> 2) + 2 * (vl & 7), r = er & 3;
-      float re = 0.f, im = 0.f;
-#pragma unroll
-      for (int ww = 0; ww < 4; ++ww) {
-        const float *s = red + (((ww * MT + j) * NTL + n) * 64) * 4;
-        re += s[lre * 4 + r];
-        im += s[(lre + 1) * 4 + r];
-      }
-      if (e < ne && v0 + vl < nvec)
-        partial[(int64_t)(off + e) * nvec + v0 + vl] = make_float2(dV * re, dV * im);
-    }
-    __syncthreads();
-  }
+__global__ __launch_bounds__(NTK) void k_kb_gather_mma(KbGather<typename Op::T> a) {
+  __shared__ __align__(16) float red[4 * MT * (2 * NVB / 16) * 256];   // cross-wave sums
+  gather_tile<Op, NVB, MT, LX>(a, blockIdx.x, blockIdx.y, gridDim.y, red);
 }
 
 // dst_v(r) += s1 sum_e beta_e(r) C'[p(e)][v] on the points r of tile t (s1 real).
@@ -382,7 +76,7 @@ __device__ __forceinline__ void scatter_mma(
   T *sc = reinterpret_cast<T *>(kb_lds);            // C' [column][entry] (hi, lo), pitch pe
   int t;
   int64_t vbh;
-  if (!tile_block(ntile, nvb * NH, t, vbh)) return;
+  if (!tile_block(blockIdx.x, ntile, nvb * NH, t, vbh)) return;
   const int64_t vb = vbh / NH;
   const int p0 = (int)(vbh % NH) * 64 * MJ;       // first point of this workgroup
   const int64_t v0 = vb * NVB;
@@ -577,7 +271,7 @@ __global__ __launch_bounds__(NTK) void k_kb_gather_f64(
   __shared__ __align__(16) double red[4 * MT * 256];
   int t;
   int64_t vb;
-  if (!tile_block(ntile, nvb, t, vb)) return;
+  if (!tile_block(blockIdx.x, ntile, nvb, t, vb)) return;
   const int64_t v0 = vb * NVB64;
   const int base = tile_base[t];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, col = lane & 15;
@@ -669,7 +363,7 @@ __global__ __launch_bounds__(NTK) void k_kb_scatter_f64(
   double *sc = reinterpret_cast<double *>(kb_lds);  // [entry][16]
   int t;
   int64_t vbh;
-  if (!tile_block(ntile, nvb * NH, t, vbh)) return;
+  if (!tile_block(blockIdx.x, ntile, nvb * NH, t, vbh)) return;
   const int64_t v0 = vbh / NH * NVB64;
   const int off = tile_off[t], ne = tile_off[t + 1] - off, nek = (ne + 3) / 4 * 4;
   const int base = tile_base[t];
@@ -751,15 +445,12 @@ static const ScatterVariant kScatter[] = {{8, 8, 0, 0}, {16, 8, 0, 0}, {8, 4, 0,
 constexpr int NGATHER = 4, NSCATTER = 9;
 
 template <class Op>
-static void launch_gather_variant(int vi, dim3 g, hipStream_t st, const float2 *psi, int64_t ld,
-                                  int64_t nvec, const int *tb, const int *to,
-                                  const typename Op::T *beta, float2 *partial, int nx, int ny,
-                                  int lx, float dV, int ntile, int nvb, const uint32_t *mask) {
-  const GatherVariant v = kGather[vi];
+static void launch_gather_variant(const GatherVariant &v, int lx, hipStream_t st,
+                                  const KbGather<typename Op::T> &a) {
+  const dim3 g(a.gx, a.gy);
 #define SGW_G(A, B, X)                                                                           \
   if (v.nvb == A && v.mt == B && lx == X)                                                        \
-    hipLaunchKernelGGL((k_kb_gather_mma<Op, A, B, X>), g, dim3(NTK), 0, st, psi, ld, nvec, tb,  \
-                       to, beta, partial, nx, ny, dV, ntile, nvb, mask);
+    hipLaunchKernelGGL((k_kb_gather_mma<Op, A, B, X>), g, dim3(NTK), 0, st, a);
   SGW_G(8, 2, 4) SGW_G(8, 4, 4) SGW_G(16, 2, 4) SGW_G(16, 4, 4)
   SGW_G(8, 2, 3) SGW_G(8, 4, 3) SGW_G(16, 2, 3) SGW_G(16, 4, 3)
 #undef SGW_G
@@ -845,12 +536,80 @@ static int entry_split(const sgw_ctx *ctx, const dim3 &g, int mt) {
   return g.x < 1024 ? (ctx->kb_ne_max + 16 * mt - 1) / (16 * mt) : 1;
 }
 
+// arguments and grid of a gather by blocks of v.nvb vectors
+template <typename T>
+static KbGather<T> gather_args(const sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld,
+                               const T *beta, void *partial, const GatherVariant &v) {
+  KbGather<T> a;
+  a.psi = static_cast<const float2 *>(psi);
+  a.ld = ld;
+  a.nvec = nvec;
+  a.tile_base = ctx->d_kb_tile_base.as<int>();
+  a.tile_off = ctx->d_kb_tile_off.as<int>();
+  a.beta = beta;
+  a.partial = static_cast<float2 *>(partial);
+  a.nx = ctx->nx;
+  a.ny = ctx->ny;
+  a.dV = (float)ctx->dV;
+  a.ntile = ctx->kb_ntile;
+  a.nvb = (int)((nvec + v.nvb - 1) / v.nvb);
+  a.tile_mask = ctx->d_kb_mask.as<uint32_t>();
+  const dim3 g = tile_grid(ctx->kb_ntile, a.nvb);
+  a.gx = g.x;
+  a.gy = entry_split(ctx, g, v.mt);
+  return a;
+}
+
+template <typename R>
+static KbReduce<R> reduce_args(const sgw_ctx *ctx, const void *partial, int64_t nvec, bool use_e,
+                               void *out) {
+  KbReduce<R> a;
+  a.partial = static_cast<const cplx<R> *>(partial);
+  a.proj_off = ctx->d_kb_proj_off.as<int>();
+  a.proj_entries = ctx->d_kb_proj_entries.as<int>();
+  a.ekb = ctx->d_kb_ekb.as<double>();
+  a.use_e = use_e ? 1 : 0;
+  a.nvec = nvec;
+  a.lv = 0;                              // up to 64 vectors per workgroup
+  while (a.lv < 6 && (int64_t(1) << a.lv) < nvec) ++a.lv;
+  a.out = static_cast<cplx<R> *>(out);
+  a.gx = (int)((nvec + (1 << a.lv) - 1) >> a.lv);
+  a.nproj = ctx->kb.nproj;
+  return a;
+}
+
+void kb_launch_reduce(sgw_ctx *ctx, const KbReduce<float> &r) {
+  hipLaunchKernelGGL(k_kb_reduce<float>, dim3(r.gx, r.nproj), dim3(NTK), 0, ctx->stream, r);
+  SGW_HIP(hipGetLastError());
+}
+
+bool kb_rides(const sgw_ctx *ctx, int64_t nvec, int64_t ld) {
+  if (!ctx->has_kb || ctx->prec != SGW_C64 || ld % 2 != 0 || ctx->kb_ntile > 65535) return false;
+  if ((ctx->ktimer & 4) || ctx->forced.count("kb_gather")) return false;
+  const int64_t nvb = (nvec + RIDE_NVB - 1) / RIDE_NVB;
+  return nvb <= 128 && tile_grid(ctx->kb_ntile, nvb).x < 1024 && fft_carries_kb(ctx);
+}
+
+static void *partial_buf(sgw_ctx *ctx, int64_t nvec) {
+  return ctx->buf("kb_partial", ctx->csize() * (size_t)ctx->kb_nentry * nvec).p;
+}
+
+KbGather<float> kb_ride_gather(sgw_ctx *ctx, const KbRide &k, int64_t nvec) {
+  return gather_args(ctx, k.psi, nvec, k.ld, ctx->d_kb_beta.as<float>(),
+                     k.partial ? k.partial : partial_buf(ctx, nvec),
+                     GatherVariant{RIDE_NVB, RIDE_MT});
+}
+
+KbReduce<float> kb_ride_reduce(sgw_ctx *ctx, const KbRide &k, int64_t nvec) {
+  return reduce_args<float>(ctx, k.partial ? k.partial : partial_buf(ctx, nvec), nvec, true,
+                            k.out);
+}
+
 template <typename R>
 static void gather_t(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, void *out,
                      bool use_e, void *partial_ext) {
   using C = cplx<R>;
-  C *partial = partial_ext ? static_cast<C *>(partial_ext)
-                           : ctx->buf("kb_partial", sizeof(C) * (size_t)ctx->kb_nentry * nvec).as<C>();
+  C *partial = static_cast<C *>(partial_ext ? partial_ext : partial_buf(ctx, nvec));
   SGW_REQUIRE(ctx->kb_ntile <= 65535, SGW_EUNSUPPORTED, "KB gather: too many tiles");
   SGW_REQUIRE(ctx->kb_ly == 3 && (ctx->kb_lx == 3 || ctx->kb_lx == 4), SGW_EUNSUPPORTED,
               "KB tile shape not built");
@@ -860,15 +619,8 @@ static void gather_t(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, vo
     auto go = [&](auto op, const char *name, const auto *beta) {
       using Op = decltype(op);
       auto run = [&](int vi) {
-        const int64_t nvb = (nvec + kGather[vi].nvb - 1) / kGather[vi].nvb;
-        dim3 g = tile_grid(ctx->kb_ntile, nvb);
-        g.y = entry_split(ctx, g, kGather[vi].mt);
-        launch_gather_variant<Op>(vi, g, ctx->stream,
-                                  static_cast<const float2 *>(psi), ld, nvec,
-                                  ctx->d_kb_tile_base.as<int>(), ctx->d_kb_tile_off.as<int>(),
-                                  beta, reinterpret_cast<float2 *>(partial), ctx->nx, ctx->ny,
-                                  ctx->kb_lx, (float)ctx->dV, ctx->kb_ntile,
-                                  (int)nvb, ctx->d_kb_mask.as<uint32_t>());
+        launch_gather_variant<Op>(kGather[vi], ctx->kb_lx, ctx->stream,
+                                  gather_args(ctx, psi, nvec, ld, beta, partial, kGather[vi]));
       };
       const int vi = ctx->tune(name, nvec, NGATHER, run);   // the gather overwrites: trials are harmless
       const bool timed = (ctx->ktimer & 4) && ctx->ns.empty();
@@ -897,12 +649,8 @@ static void gather_t(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, vo
                        ctx->ny, ctx->dV, ctx->kb_ntile, (int)nvb, ctx->d_kb_mask.as<uint32_t>());
   }
   SGW_HIP(hipGetLastError());
-  int lv = 0;                            // up to 64 vectors per workgroup
-  while (lv < 6 && (int64_t(1) << lv) < nvec) ++lv;
-  hipLaunchKernelGGL(k_kb_reduce<R>, dim3((nvec + (1 << lv) - 1) >> lv, ctx->kb.nproj), dim3(NTK),
-                     0, ctx->stream, partial, ctx->d_kb_proj_off.as<int>(),
-                     ctx->d_kb_proj_entries.as<int>(), ctx->d_kb_ekb.as<double>(), use_e ? 1 : 0,
-                     nvec, lv, static_cast<C *>(out));
+  const KbReduce<R> r = reduce_args<R>(ctx, partial, nvec, use_e, out);
+  hipLaunchKernelGGL(k_kb_reduce<R>, dim3(r.gx, r.nproj), dim3(NTK), 0, ctx->stream, r);
   SGW_HIP(hipGetLastError());
 }
 

@@ -207,6 +207,44 @@ def test_kb_variants_bit_identical(si35, monkeypatch, prec, names):
     assert np.array_equal(ref[20], ref[100][:20])
 
 
+@pytest.mark.parametrize("n", [24, 32, 40, 48, 56, 64, 80, 96, 112, 128, 160])
+def test_small_batch_gather_beside_fft_passes(n, monkeypatch):
+    """In small batches the FFT passes carry the projector gather and its
+    reduction (the forward planes where they have four waves or more, the z
+    pencils likewise): H psi through both entry points and a short Chebyshev
+    series are bitwise the same as with the gather in a launch of its own
+    (which pinning its variant keeps), on one vector, on a block of 8 and on
+    a ragged batch, with padded vectors."""
+    from paper_2601_21005_amd import systems
+    species, pos = systems.si_cluster(5, seed=3)
+    s = systems.cluster_model(species, pos, n=n, h=0.6, ecut=28.0)
+    N = s.grid.N
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((11, N + 64), dtype=torch.complex64, device="cuda", generator=g)
+    out = {}
+    for pin in (False, True):
+        if pin:
+            monkeypatch.setenv("SGW_FORCE_VARIANT", "kb_gather=1")
+        ctx = make_ctx(s, sgw.SGW_C64, max_nvec=11)
+        lo, hi = ctx.bounds(0.0)
+        res = []
+        for nv in (1, 8, 11):
+            y = torch.zeros_like(x[:nv])
+            ctx.apply_H(x[:nv], y)
+            res.append(y[:, :N].clone())
+            y.zero_()
+            ctx.apply_H_noalloc(x[:nv], y)
+            res.append(y[:, :N].clone())
+            w = x[:nv, :N].clone(memory_format=torch.contiguous_format)
+            ctx.fermi_filter(w, np.array([0.3, -0.2, 0.5, 0.1, -0.4]), lo, hi)
+            res.append(w)
+        torch.cuda.synchronize()
+        ctx.close()
+        out[pin] = [r.cpu() for r in res]
+    for a, b in zip(out[False], out[True]):
+        assert torch.isfinite(torch.view_as_real(a)).all() and torch.equal(a, b)
+
+
 @pytest.mark.parametrize("prec", [sgw.SGW_C64, sgw.SGW_C64_BF16KB, sgw.SGW_C64_BF16X2KB])
 def test_kb_support_masks_change_no_value(si35, monkeypatch, prec):
     """The KB kernels skip the 16-point rows (gather: K groups) that no
