@@ -52,7 +52,7 @@ HPSI_ALGO_BYTES = 16.0
 # FETCH_SIZE + WRITE_SIZE hardware counters on the 260-vector filter launch,
 # scaled by the counters' reading for a plain 256 MiB device copy.  Valid only
 # for the kernel source it was measured on; None once that kernel changes.
-CHEB_MEASURED_BYTES = 36.68
+CHEB_MEASURED_BYTES = 36.67
 # The dominant kernel by time, the projector scatter psi += s B C' (the TDH's
 # KB exponential twice per substep at 1024 vectors, every filter term at 260):
 # algorithmic bytes per (grid point inside some projector's support x complex
@@ -1054,7 +1054,7 @@ def main():
         "hbm_ceilings": ceilings,
         "filter_coefficients": fcoef,
         "kb_layout": kbs,
-        "roofline_cheb": {"bound": "hbm", "kernel": "k_plane<float,64,64,PLANE_INV_CHEB>",
+        "roofline_cheb": {"bound": "hbm", "kernel": "k_plane<float,64,PLANE_INV_CHEB>",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS if achieved else None,
                      "traffic": (CHEB_MEASURED_BYTES * k_pts / k_launch

@@ -66,8 +66,8 @@ typedef enum {
  * 128, 160), with nx == ny and nx a multiple of the z pencils' width (16 when
  * nz % 16 == 0, else 8 when nz % 8 == 0, else 4); otherwise SGW_EUNSUPPORTED.
  * The x and y transforms run on whole xy planes in LDS when a plane fits
- * (n <= 80 in complex FP32, n <= 56 in complex FP64), else on x lines and y
- * pencils (one more pass over the batch, same results). */
+ * (n <= 128, but not 112 in complex FP64), else on x lines and y pencils (two
+ * more passes over the batch). */
 typedef struct {
   int32_t nx, ny, nz;
   double h;               /* grid spacing, bohr */
