@@ -191,7 +191,9 @@ __device__ __forceinline__ void plane_pass(const PassArgs &a, int z, int64_t v, 
   if (INV) s2.map(tid, [](C z, int, int) { return cconj(z); });
   // epilogue operands are loaded CH points at a time before their stores (the
   // stores would otherwise order every later load)
-  constexpr int CH = R2 % 4 == 0 ? 4 : R2;
+  // (10 at once hold 132 registers: 80^2 filter terms of 24 vectors 255 us
+  // against 240 with 5, and 250 with the points in LDS)
+  constexpr int CH = R2 % 4 == 0 ? 4 : R2 % 5 == 0 ? 5 : R2;
   if constexpr (MODE == PLANE_INV_CHEB) {
     const C *xp = static_cast<const C *>(a.e.x) + v * a.ld_x + plane;
     C *vp = static_cast<C *>(a.e.vold) + v * a.ld_x + plane;
@@ -584,10 +586,13 @@ template <typename R, int N> struct Kernels {
 };
 
 // the passes that carry the projector gather and its reduction (FP32, planes
-// and pencils of at least the gather's four waves)
+// and pencils of at least the gather's four waves; not the planes held to a
+// register budget, where the gather spills: 128^3, 4 vectors, 30 filter terms
+// 6.15 ms against 5.86 with launches of its own)
 template <int N> struct RideKernels {
   static constexpr int TX = pencil_tx_wide<float, N>();
-  static constexpr bool plane_ok = PlaneShape<float, N>::fits && PlaneShape<float, N>::T >= NTK;
+  static constexpr bool plane_ok = PlaneShape<float, N>::fits && PlaneShape<float, N>::T >= NTK &&
+                                   PlaneShape<float, N>::WPE == 1;
   static constexpr bool pencil_ok = PencilShape<float, N, TX>::T >= NTK;
   static void plane(int nvec, hipStream_t st, const PassArgs &a, const KbGather<float> &g) {
     if constexpr (plane_ok)
