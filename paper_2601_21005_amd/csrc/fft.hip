@@ -10,7 +10,8 @@
 //   pencil  TX neighbouring columns along z (coalesced rows of TX complex):
 //           forward z -> k-space multiplier -> inverse z;
 //   xlines, ypencil  x lines and y columns in two passes, where a plane does
-//           not fit in LDS (160^2 in complex FP64).
+//           not fit in LDS or spills registers (160^2, and 112^2 in FP64).
+// Small batches carry the projector gather in the same launches.
 #include "fft_reg.h"
 #include "kb_gather.h"
 
