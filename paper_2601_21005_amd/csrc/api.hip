@@ -171,9 +171,14 @@ void join_gather(sgw_ctx *ctx) {
 
 // whether the projector gathers of a batch of nvec vectors go beside the FFT
 // passes (on the context's stream, with projectors, for batches that fill
-// more than a sliver of the device); creates the second stream on first use
+// more than a sliver of the device); creates the second stream on first use.
+// The two events of a term cost about 10 us: with fewer than some 320 gather
+// workgroups the term is too short for them (24^3 in complex FP32, 32 vectors,
+// 26 terms: 1084 us with them, 953 without; 40^3 split BF16, 24 vectors, 360
+// workgroups: 1439 and 1466)
 bool gather_beside(sgw_ctx *ctx, int64_t nvec) {
-  const bool ovl = ctx->has_kb && ctx->kb_overlap && ctx->ns.empty() && nvec >= 16;
+  const bool ovl = ctx->has_kb && ctx->kb_overlap && ctx->ns.empty() && nvec >= 16 &&
+                   kb_gather_blocks(ctx, nvec) >= 320;
   if (ovl) ctx->make_aux();
   return ovl;
 }

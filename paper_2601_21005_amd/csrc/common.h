@@ -331,6 +331,8 @@ bool fft_carries_kb(const sgw_ctx *ctx);
 void kb_gather(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, void *coef_out);
 void kb_gather_e(sgw_ctx *ctx, const void *psi, int64_t nvec, int64_t ld, void *coef_out,
                  void *partial = nullptr);
+// workgroups of a gather by blocks of 8 vectors
+int64_t kb_gather_blocks(const sgw_ctx *ctx, int64_t nvec);
 // small batches in complex FP32: the gather has fewer than four workgroups per
 // CU, so the FFT passes that read the same vectors carry it (KbRide; the same
 // bits as kb_gather_e)

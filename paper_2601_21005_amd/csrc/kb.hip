@@ -583,11 +583,14 @@ void kb_launch_reduce(sgw_ctx *ctx, const KbReduce<float> &r) {
   SGW_HIP(hipGetLastError());
 }
 
+int64_t kb_gather_blocks(const sgw_ctx *ctx, int64_t nvec) {
+  return 8 * ((ctx->kb_ntile + 7) / 8) * ((nvec + RIDE_NVB - 1) / RIDE_NVB);
+}
+
 bool kb_rides(const sgw_ctx *ctx, int64_t nvec, int64_t ld) {
   if (!ctx->has_kb || ctx->prec != SGW_C64 || ld % 2 != 0 || ctx->kb_ntile > 65535) return false;
   if (((ctx->ktimer & 4) && ctx->ns.empty()) || ctx->forced.count("kb_gather")) return false;
-  const int64_t nvb = (nvec + RIDE_NVB - 1) / RIDE_NVB;
-  return nvb <= 128 && tile_grid(ctx->kb_ntile, nvb).x < 1024 && fft_carries_kb(ctx);
+  return kb_gather_blocks(ctx, nvec) < 1024 && fft_carries_kb(ctx);
 }
 
 static void *partial_buf(sgw_ctx *ctx, int64_t nvec) {
