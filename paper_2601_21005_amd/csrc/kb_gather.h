@@ -30,6 +30,8 @@ template <typename T> struct KbGather {
   const uint32_t *tile_mask;
   int gx, gy;
 };
+// vectors of a reduction workgroup (log2): rows of 16, or of 64 for wide batches
+constexpr int KB_LV_FEW = 4, KB_LV_MANY = 6;
 template <typename R> struct KbReduce {
   const cplx<R> *partial;
   const int *proj_off, *proj_entries;
@@ -41,38 +43,72 @@ template <typename R> struct KbReduce {
   int gx, nproj;
 };
 
-// out[p][v] = sum of projector p's partial sums (times E_p), FP64.  A
-// workgroup holds 2^lv vectors of one projector and splits its entries (some
-// 60 to 90) over the 256 >> lv threads of each vector, whose sums are added
-// in order: with one thread per vector a batch of 1 left 255 threads idle
-// behind a chain of loads (64^3: 8.9 us, now 3.8; 16 vectors 15.6 -> 5.1).
-template <typename R>
-__device__ __forceinline__ void reduce_projector(const KbReduce<R> &a, int bx, int p, double2 *sh) {
-  const auto [partial, proj_off, proj_entries, ekb, use_e, nvec, lv, out, gx, nproj] = a;
-  const int vl = threadIdx.x & ((1 << lv) - 1), part = threadIdx.x >> lv, np = NTK >> lv;
-  const int64_t v = ((int64_t)bx << lv) + vl;
-  double sr = 0, si = 0;
-  if (v < nvec) {
-    // unrolled so that several loads are in flight; the sum keeps its order
-#pragma unroll 8
-    for (int k = proj_off[p] + part; k < proj_off[p + 1]; k += np) {
-      const cplx<R> c = partial[(int64_t)proj_entries[k] * nvec + v];
-      sr += c.x;
-      si += c.y;
+// out[p][v] = sum of projector p's partial sums (times E_p), FP64.  The
+// entries (some 60 to 90) are dealt to KB_SLOTS sums in turn, which are added
+// in a tree: an order of the projector alone, so that a vector's result does
+// not depend on how many vectors share its launch.  A workgroup holds 2^LV
+// vectors of one projector; its threads of a vector share the slots.  Bound by
+// the latency of the entry list and the sums behind it: eight loads of a
+// thread are in flight (64^3, 260 vectors beside the FFT passes: 22 us, 26
+// with one thread's loads in a loop and an order that followed the batch).
+constexpr int KB_SLOTS = 16;
+
+template <int LV, typename R>
+__device__ __forceinline__ void reduce_slots(const KbReduce<R> &a, int bx, int p, double2 *sh) {
+  constexpr int NP = NTK >> LV, SL = KB_SLOTS / NP;   // threads of a vector, slots of a thread
+  static_assert(NP * SL == KB_SLOTS, "the threads of a vector share the slots evenly");
+  const int vl = threadIdx.x & ((1 << LV) - 1);
+  const int part = LV == 6 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> LV) : threadIdx.x >> LV;
+  const int64_t v = ((int64_t)bx << LV) + vl;
+  double2 s[SL];
+#pragma unroll
+  for (int j = 0; j < SL; ++j) s[j] = make_double2(0, 0);
+  if (v < a.nvec) {
+    // IN rounds of the slots are requested before they are added, those past
+    // the last entry (a zero then) at the last
+    constexpr int IN = 8 / SL;
+    const int k1 = a.proj_off[p + 1];
+    for (int k = a.proj_off[p] + part; k < k1; k += KB_SLOTS * IN) {
+      cplx<R> c[IN][SL];
+#pragma unroll
+      for (int i = 0; i < IN; ++i)
+#pragma unroll
+        for (int j = 0; j < SL; ++j) {
+          const int e = min(k + KB_SLOTS * i + NP * j, k1 - 1);
+          c[i][j] = a.partial[(int64_t)a.proj_entries[e] * a.nvec + v];
+        }
+#pragma unroll
+      for (int i = 0; i < IN; ++i)
+#pragma unroll
+        for (int j = 0; j < SL; ++j) {
+          const bool in = k + KB_SLOTS * i + NP * j < k1;
+          s[j].x += in ? c[i][j].x : 0;
+          s[j].y += in ? c[i][j].y : 0;
+        }
     }
   }
-  sh[threadIdx.x] = make_double2(sr, si);
-  for (int h = np / 2; h > 0; h >>= 1) {
+#pragma unroll
+  for (int h = SL / 2; h > 0; h >>= 1)
+#pragma unroll
+    for (int j = 0; j < h; ++j) s[j] = make_double2(s[j].x + s[j + h].x, s[j].y + s[j + h].y);
+  sh[threadIdx.x] = s[0];
+  for (int h = NP / 2; h > 0; h >>= 1) {
     __syncthreads();
     if (part < h) {
-      const double2 a = sh[threadIdx.x], b = sh[threadIdx.x + (h << lv)];
-      sh[threadIdx.x] = make_double2(a.x + b.x, a.y + b.y);
+      const double2 x = sh[threadIdx.x], y = sh[threadIdx.x + (h << LV)];
+      sh[threadIdx.x] = make_double2(x.x + y.x, x.y + y.y);
     }
   }
-  if (part > 0 || v >= nvec) return;
-  double2 s = sh[threadIdx.x];
-  if (use_e) { s.x *= ekb[p]; s.y *= ekb[p]; }
-  out[(int64_t)p * nvec + v] = cmake<cplx<R>>(s.x, s.y);
+  if (part > 0 || v >= a.nvec) return;
+  double2 t = sh[threadIdx.x];
+  if (a.use_e) { t.x *= a.ekb[p]; t.y *= a.ekb[p]; }
+  a.out[(int64_t)p * a.nvec + v] = cmake<cplx<R>>(t.x, t.y);
+}
+
+template <typename R>
+__device__ __forceinline__ void reduce_projector(const KbReduce<R> &a, int bx, int p, double2 *sh) {
+  if (a.lv == KB_LV_FEW) reduce_slots<KB_LV_FEW>(a, bx, p, sh);
+  else reduce_slots<KB_LV_MANY>(a, bx, p, sh);
 }
 
 // ---------------------------------------------------------------- MFMA
