@@ -489,7 +489,7 @@ sgw_status sgw_mlp_train(sgw_mlp *mlp, const float *x, const float *y, int64_t n
 /* Mean and sample variance (FP64) of g over the cheap samples first_sample
  * .. first_sample + count - 1: features and network in chunks of `chunk`
  * samples on the context's stream, which must be the network's stream.
- * K must equal the network's din. Synchronous. */
+ * K must equal the network's din and lie in 1..64, ld_phi >= N.  Synchronous. */
 sgw_status sgw_cv_cheap_moments(sgw_ctx *ctx, sgw_mlp *mlp, const float *phi, int32_t K,
                                 int64_t ld_phi, uint64_t seed, int64_t first_sample,
                                 int64_t count, int64_t chunk, double *mean, double *var);

@@ -296,7 +296,10 @@ void features(sgw_ctx *ctx, const float *phi, int K, int64_t ld, uint64_t seed, 
     hipLaunchKernelGGL(k_features<M>, g, dim3(NT), 0, ctx->stream, p16, N, K, seed,             \
                        (int64_t)col0, ncol, cpp, (float)ctx->dV, part, ldx, neta, direct);      \
     break;
-  switch (mt) { SGW_F(1) SGW_F(2) SGW_F(3) SGW_F(4) }
+  switch (mt) {
+    SGW_F(1) SGW_F(2) SGW_F(3) SGW_F(4)
+    default: throw Error{SGW_EUNSUPPORTED, "features: K must be in 1..64"};
+  }
 #undef SGW_F
   SGW_HIP(hipGetLastError());
   if (direct) return;
@@ -1046,8 +1049,10 @@ sgw_status sgw_cv_cheap_moments(sgw_ctx *ctx, sgw_mlp *M, const float *phi, int3
   if (!ctx || !M) return SGW_EINVAL;
   return guard_ctx(ctx, [&] {
     SGW_REQUIRE(phi && mean && var, SGW_EINVAL, "NULL argument");
+    SGW_REQUIRE(K >= 1 && K <= 64, SGW_EINVAL, "K must be in 1..64");
     SGW_REQUIRE(K == M->din, SGW_EINVAL, "K must equal the network's input size");
     SGW_REQUIRE(count >= 2 && chunk >= 1, SGW_EINVAL, "count >= 2 and chunk >= 1 required");
+    SGW_REQUIRE(ld_phi >= ctx->N, SGW_EINVAL, "ld_phi < number of grid points");
     SGW_REQUIRE(first_sample >= 0 && first_sample + count <= ((int64_t)1 << 20), SGW_EINVAL,
                 "sample indices must lie in [0, 2^20)");
     SGW_REQUIRE(ctx->N % 64 == 0, SGW_EUNSUPPORTED, "features need N divisible by 64");

@@ -356,6 +356,20 @@ def test_cheap_moments_match_model(tiny8, net_case):
     assert abs(var / go.var(ddof=1) - 1) < 0.05
 
 
+@pytest.mark.parametrize("states,short", [(65, 0), (64, 64)])
+def test_cheap_moments_reject_bad_sizes(tiny8, states, short):
+    """More states than the feature kernels take, and rows shorter than the
+    grid, are refused as in the feature calls."""
+    s, _ = tiny8
+    ctx = sgw.Context(s.grid.n, s.grid.h, s.v_loc, None, precision=sgw.SGW_C64, max_nvec=4)
+    m = sgw.Mlp(systems.mlp_init(3, din=states, h1=16, h2=16), din=states, h1=16, h2=16)
+    phi = torch.zeros((states, ctx.N - short), device="cuda")
+    with pytest.raises(sgw.SgwError) as e:
+        sgw.cv_cheap_moments(ctx, m, phi, 9, 0, 100)
+    assert e.value.code == sgw.SGW_EINVAL
+    ctx.close()
+
+
 def test_cheap_moments_mixed_match_model(tiny8):
     """Mean and variance of g over 3000 cheap samples whose input rows are
     [16 zeta-bar features, 48 eta-bar features (N_eta = 6)], device chunks of
