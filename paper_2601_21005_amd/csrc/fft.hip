@@ -451,6 +451,7 @@ template <typename R, int N, int TX> struct PencilShape {
   static constexpr int P = TX + 1;
   static constexpr bool SPLIT = D && N > 64;
   static constexpr bool TURN = D || R1 == R2;
+  static constexpr bool ALT = !D && N == 96 && TX == 32;   // see butterfly
 };
 
 // columns block bx of vector v; s: N P complex (N P values where SPLIT), tw: N
@@ -480,7 +481,7 @@ __device__ __forceinline__ void pencil_pass(const PassArgs &a, int bx, int64_t v
   exchange<Sh::SPLIT, C>(
       s, tid, s1, s2, true, [](int b, int i) { return ((b / TX) * R1 + i) * P + b % TX; },
       [](int b, int i) { return (b / TX + i * R1) * P + b % TX; });
-  s2.template run<N, R1>(tid, tw, col_of);
+  s2.template run<N, R1, Sh::ALT>(tid, tw, col_of);
   s2.map(tid, [&](C z, int b, int i) {
     const C m = kmul<R>(a, x0 + b % TX, y, b / TX + i * R1);
     return cmake_r<C>(fma(m.x, z.x, -(m.y * z.y)), -fma(m.y, z.x, m.x * z.y));   // conj(m z)
@@ -503,7 +504,7 @@ __device__ __forceinline__ void pencil_pass(const PassArgs &a, int bx, int64_t v
     exchange<Sh::SPLIT, C>(
         s, tid, s1, s2, false, [](int b, int i) { return ((b / TX) * R1 + i) * P + b % TX; },
         [](int b, int i) { return (b / TX + i * R1) * P + b % TX; });
-    s2.template run<N, R1>(tid, tw, col_of);
+    s2.template run<N, R1, Sh::ALT>(tid, tw, col_of);
     s2.each(tid, [&](int q, int b) {
 #pragma unroll
       for (int i = 0; i < R2; ++i) data[(b / TX + i * R1) * stride + b % TX] = cconj(s2.v[q][i]);

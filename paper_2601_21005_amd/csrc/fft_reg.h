@@ -30,27 +30,28 @@ template <typename C> struct DFT<C, 1> {
 __device__ __forceinline__ void settle(float2 &z) { asm volatile("" : "+v"(z.x), "+v"(z.y)); }
 __device__ __forceinline__ void settle(double2 &z) { asm volatile("" : "+v"(z.x), "+v"(z.y)); }
 
-// a t
-template <typename C> __device__ __forceinline__ C twist(C a, C t) {
+// a t, and the same with the imaginary part's other product rounded first
+template <bool ALT, typename C> __device__ __forceinline__ C twist(C a, C t) {
   C r;
   r.x = fma(a.x, t.x, -(a.y * t.y));
-  r.y = fma(a.y, t.x, a.x * t.y);
+  r.y = ALT ? fma(a.x, t.y, a.y * t.x) : fma(a.y, t.x, a.x * t.y);
   return r;
 }
 
 // Radix-R butterfly k of a stage whose sub-transforms have length NS, in
 // place: twiddles exp(-2 pi i i k/(NS R)) from the table tw of length N, then
 // the transform; for R = A B (A = pick_radix(R)) the stages of radix A and B.
-template <typename C, int N, int R, int NS> __device__ __forceinline__ void butterfly(C *a,
-                                                                                      const C *tw,
-                                                                                      int k) {
+// ALT: the radix-A butterflies after the first round their twiddles the other
+// way round (96-point z lines).
+template <typename C, int N, int R, int NS, bool ALT = false> __device__ __forceinline__ void butterfly(
+    C *a, const C *tw, int k) {
   constexpr int A = pick_radix(R), B = R / A;
   if constexpr (R == 1) {
     return;
   } else if constexpr (B == 1) {
     if (NS > 1) {
 #pragma unroll
-      for (int i = 1; i < R; ++i) a[i] = twist(a[i], tw[i * k * (N / (NS * R))]);
+      for (int i = 1; i < R; ++i) a[i] = twist<false>(a[i], tw[i * k * (N / (NS * R))]);
     }
     DFT<C, R>::run(a);
 #pragma unroll
@@ -62,7 +63,10 @@ template <typename C, int N, int R, int NS> __device__ __forceinline__ void butt
 #pragma unroll
       for (int i = 0; i < A; ++i) {
         t[m][i] = a[m + i * B];
-        if (NS > 1 && i > 0) t[m][i] = twist(t[m][i], tw[i * k * (N / (NS * A))]);
+        if (NS > 1 && i > 0) {
+          const C z = tw[i * k * (N / (NS * A))];
+          t[m][i] = ALT && m > 0 ? twist<true>(t[m][i], z) : twist<false>(t[m][i], z);
+        }
       }
       DFT<C, A>::run(t[m]);
 #pragma unroll
@@ -74,7 +78,7 @@ template <typename C, int N, int R, int NS> __device__ __forceinline__ void butt
 #pragma unroll
       for (int m = 0; m < B; ++m) {
         w[m] = t[m][i];
-        if (m > 0) w[m] = twist(w[m], tw[m * (k + NS * i) * (N / (NS * R))]);
+        if (m > 0) w[m] = twist<false>(w[m], tw[m * (k + NS * i) * (N / (NS * R))]);
       }
       DFT<C, B>::run(w);
 #pragma unroll
@@ -100,9 +104,9 @@ template <typename C, int R_, int NB_, int T_> struct Stage {
     }
   }
   // butterfly b is number k_of(b) of its sub-transforms (length NS)
-  template <int N, int NS, typename K>
+  template <int N, int NS, bool ALT = false, typename K>
   __device__ __forceinline__ void run(int tid, const C *tw, K k_of) {
-    each(tid, [&](int q, int b) { butterfly<C, N, R, NS>(v[q], tw, k_of(b)); });
+    each(tid, [&](int q, int b) { butterfly<C, N, R, NS, ALT>(v[q], tw, k_of(b)); });
   }
   // f on every value, settled
   template <typename F> __device__ __forceinline__ void map(int tid, F &&f) {
