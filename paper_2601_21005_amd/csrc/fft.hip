@@ -130,9 +130,12 @@ template <typename R, int N, int MODE = PLANE_FWD> struct PlaneShape {
   // 64 also wide enough that the runs of R1 points of neighbouring lines do
   static constexpr int P = N == 128 ? 145 : N == 64 ? 73 : N + 1;
   static constexpr bool SPLIT = true;
-  // FP32 inverse transforms of 96 and more take y before x (one more exchange):
-  // the order, to the last bit, of the separate x and y passes that planes of
-  // these sizes have in place of this one when they do not fit
+  // FP32 inverse transforms of 96 and more take y before x, at one exchange
+  // more: the order in which x lines and y pencils round.  The TDH's response
+  // field, a small difference of orbitals, amplifies another rounding to some
+  // 2e-5 of itself (96^3), so results recorded with that order stay what they
+  // are (x before y: H psi on 24 vectors of 96^3 300 us against 304, 112^3 498
+  // against 506, 128^3 669 against 672, as accurate)
   static constexpr bool YFIRST = !D && N >= 96;
   static constexpr size_t lds = (size_t)N * P * sizeof(R) * (SPLIT ? 1 : 2) + N * sizeof(cplx<R>);
   static constexpr bool fits = lds <= 160 * 1024 && !(D && N == 112) && !(!D && N == 160);
@@ -451,7 +454,11 @@ template <typename R, int N, int TX> struct PencilShape {
   static constexpr int P = TX + 1;
   static constexpr bool SPLIT = D && N > 64;
   static constexpr bool TURN = D || R1 == R2;
-  static constexpr bool ALT = !D && N == 96 && TX == 32;   // see butterfly
+  // FP32 lines of 96 points round a twiddle product the other way round (see
+  // butterfly), at every width: without it the TDH's response field at 96^3
+  // moves by 2e-5 to 6e-5 of itself, as accurate and no faster; results
+  // recorded with it stay what they are
+  static constexpr bool ALT = !D && N == 96;
 };
 
 // columns block bx of vector v; s: N P complex (N P values where SPLIT), tw: N

@@ -8,7 +8,8 @@
 // first stage loads from and the last one stores to global memory directly.
 // R1 is 8 (4 for length 12) and an R2 above 8 is taken as two radices inside
 // the thread, in the order and with the twiddles of the separate stages of
-// lds_fft: the two transforms round every value alike, bit for bit.
+// lds_fft: the two transforms round every value alike, bit for bit (but for
+// the 96-point z lines, see ALT).
 // Inverse transforms are taken as conj(FFT(conj(x))).
 #pragma once
 
