@@ -1,0 +1,79 @@
+"""Which small batches carry the projector gather in their FFT passes, and that
+they give the bits of a gather in launches of its own: on cubic grids of every
+length and on flat and tall ones, where the z pencils are too narrow or too
+small for the reduction and only the planes carry their part."""
+import json
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_21005_amd import sgw, systems
+
+pytestmark = pytest.mark.gpu
+H = 0.6
+# grid -> whether its forward planes carry the gather (four waves or more, no
+# register budget)
+GRIDS = {(24, 24, 24): False, (32, 32, 32): True, (40, 40, 40): True, (48, 48, 48): False,
+         (56, 56, 56): True, (64, 64, 64): True, (80, 80, 80): True, (96, 96, 96): True,
+         (112, 112, 112): False, (128, 128, 128): False,
+         (64, 64, 32): True, (32, 32, 64): True, (96, 96, 48): True, (80, 80, 40): True,
+         (80, 80, 96): True, (64, 64, 40): True, (64, 64, 24): True, (96, 96, 24): True,
+         (64, 64, 12): True, (48, 48, 64): False}
+
+
+def model(n):
+    """A 5-Si cluster's projectors in the middle of an n box."""
+    species, pos = systems.si_cluster(5, seed=3)
+    p = systems.cluster_model(species, pos, n=40, h=H, ecut=28.0).projectors
+    p.pos = np.asarray(p.pos) + 0.5 * H * (np.array(n) - 40.0)
+    v = -np.random.default_rng(n[2]).random(n[0] * n[1] * n[2])
+    return v, p
+
+
+@pytest.mark.parametrize("n", sorted(GRIDS))
+def test_gather_rides_where_it_is_built(n, tmp_path, monkeypatch):
+    """A gather in a launch of its own times its variants and writes the choice
+    to SGW_TUNE_CACHE; one carried by the planes has none to choose."""
+    v, p = model(n)
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("SGW_TUNE_CACHE", str(cache))
+    monkeypatch.setenv("SGW_FORCE_VARIANT", "kb_scatter=0")
+    ctx = sgw.Context(n, H, v, p, precision=sgw.SGW_C64, ecut=28.0, max_nvec=6)
+    x = torch.zeros((6, ctx.N), dtype=torch.complex64, device="cuda")
+    ctx.apply_H(x, torch.empty_like(x))
+    torch.cuda.synchronize()
+    ctx.close()
+    keys = json.loads(cache.read_text()) if cache.exists() else {}
+    tuned = any("/kb_gather/%dx%dx%d/" % n in k and k.endswith("/6") for k in keys)
+    assert tuned != GRIDS[n]
+
+
+@pytest.mark.parametrize("pencil", ["", ",pencil=0"])
+@pytest.mark.parametrize("n", sorted(GRIDS))
+def test_riding_gather_changes_no_bit(n, pencil, monkeypatch):
+    v, p = model(n)
+    N = n[0] * n[1] * n[2]
+    g = torch.Generator(device="cuda").manual_seed(n[0] + n[2])
+    x = torch.randn((11, N + 64), dtype=torch.complex64, device="cuda", generator=g)
+    out = []
+    for pin in ("kb_scatter=0", "kb_scatter=0,kb_gather=1"):
+        monkeypatch.setenv("SGW_FORCE_VARIANT", pin + pencil)
+        ctx = sgw.Context(n, H, v, p, precision=sgw.SGW_C64, ecut=28.0, max_nvec=11)
+        lo, hi = ctx.bounds(0.0)
+        res = []
+        for nv in (1, 8, 11):
+            y = torch.zeros_like(x[:nv])
+            ctx.apply_H(x[:nv], y)
+            res.append(y[:, :N].clone())
+            y.zero_()
+            ctx.apply_H_noalloc(x[:nv], y)
+            res.append(y[:, :N].clone())
+            w = x[:nv, :N].clone(memory_format=torch.contiguous_format)
+            ctx.fermi_filter(w, np.array([0.3, -0.2, 0.5, 0.1, -0.4]), lo, hi)
+            res.append(w)
+        torch.cuda.synchronize()
+        ctx.close()
+        out.append(res)
+    for a, b in zip(*out):
+        assert torch.isfinite(torch.view_as_real(a)).all() and torch.equal(a, b)
