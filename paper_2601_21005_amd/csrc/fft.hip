@@ -522,7 +522,7 @@ __device__ __forceinline__ void pencil_pass(const PassArgs &a, int bx, int64_t v
 template <typename R, int N, int TX>
 __global__ __launch_bounds__((PencilShape<R, N, TX>::T)) void k_pencil(PassArgs a) {
   using Sh = PencilShape<R, N, TX>;
-  __shared__ R s[N * Sh::P * (Sh::SPLIT ? 1 : 2)];
+  __shared__ __align__(16) R s[N * Sh::P * (Sh::SPLIT ? 1 : 2)];   // complex unless SPLIT
   __shared__ cplx<R> tw[N];
   pencil_pass<R, N, TX>(a, blockIdx.x, vec_of(a, blockIdx.y, gridDim.y), s, tw);
 }

@@ -268,7 +268,7 @@ __global__ __launch_bounds__(NTK) void k_kb_gather_f64(
     const double *beta, double2 *partial, int nx, int ny, double dV, int ntile, int nvb,
     const uint32_t *__restrict__ tile_mask) {
   constexpr int NG = 16;
-  __shared__ __align__(16) double red[4 * MT * 256];
+  __shared__ __align__(32) double red[4 * MT * 256];
   int t;
   int64_t vb;
   if (!tile_block(blockIdx.x, ntile, nvb, t, vb)) return;
