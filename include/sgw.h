@@ -447,8 +447,9 @@ sgw_status sgw_cv_features(sgw_ctx *ctx, const float *phi, int32_t K, int64_t ld
  * eta-bar_{i,l} the white noise that sgw_sigma_estimate draws for sample i.
  * Arguments as sgw_cv_features; rows of x are ldx >= K floats apart (so the
  * zeta-bar and eta-bar features of one sample can share a row).  Needs
- * 4 nsamp n_eta K bytes of context scratch (K rounded up to 16), or 64 MiB
- * where that is less. */
+ * 4 nsamp n_eta K bytes of context scratch beside phi in BF16, or up to 256 MiB
+ * where that is less (or one sample's n_eta vectors, K rounded up to 16, where
+ * those take more). */
 sgw_status sgw_cv_features_eta(sgw_ctx *ctx, const float *phi, int32_t K, int64_t ld_phi,
                                uint64_t seed, int64_t first_sample, int64_t nsamp,
                                int32_t n_eta, float *x, int64_t ldx);

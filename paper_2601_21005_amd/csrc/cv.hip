@@ -158,6 +158,7 @@ __device__ __forceinline__ void spread_rows(uint32_t v, uint32_t *rows) {
 // dV (sum)^2 = |<phi_k|zeta_c>|^2 at rows ldx apart; else the sums go to
 // part[blockIdx.y][c][16 MT].
 constexpr int FEAT_COLS = 256;                 // vectors per workgroup
+constexpr double FEAT_PART_BYTES = 256 << 20;
 
 template <int MT>
 __global__ __launch_bounds__(NT) void k_features(const uint16_t *phi16, int64_t N, int K,
@@ -287,26 +288,36 @@ void features(sgw_ctx *ctx, const float *phi, int K, int64_t ld, uint64_t seed, 
   const int64_t cpp = (nch + np - 1) / np;
   np = (nch + cpp - 1) / cpp;
   const int direct = np == 1 && neta <= 0;
+  // the sums' rows of 16 mt floats take no more than rows of K would, or
+  // FEAT_PART_BYTES: past that the samples go in slices (2^20 vectors of 64
+  // states in one launch 28 ms, in four 31)
+  const double need = 4.0 * np * ncol * kp, most = std::max(FEAT_PART_BYTES, 4.0 * ncol * K);
+  const int64_t nslice = direct ? 1 : std::min<int64_t>(nsamp, (int64_t)std::ceil(need / most));
+  const int64_t per = (nsamp + nslice - 1) / nslice;
+  const int64_t cols = neta > 0 ? per * neta : per;
   float *part = direct ? x
-                       : ctx->buf("cv_part_sums", sizeof(float) * (size_t)np * ncol * kp).as<float>();
-  const dim3 g((unsigned)nblk, (unsigned)np);
-  const uint64_t col0 = neta > 0 ? (uint64_t)s0 * neta : (uint64_t)s0;
+                       : ctx->buf("cv_part_sums", sizeof(float) * (size_t)np * cols * kp).as<float>();
+  for (int64_t i = 0; i < nsamp; i += per) {
+    const int64_t ns = std::min(per, nsamp - i), nc = neta > 0 ? ns * neta : ns;
+    const dim3 g((unsigned)((nc + FEAT_COLS - 1) / FEAT_COLS), (unsigned)np);
+    const uint64_t col0 = (uint64_t)(s0 + i) * (neta > 0 ? neta : 1);
 #define SGW_F(M)                                                                                \
   case M:                                                                                       \
     hipLaunchKernelGGL(k_features<M>, g, dim3(NT), 0, ctx->stream, p16, N, K, seed,             \
-                       (int64_t)col0, ncol, cpp, (float)ctx->dV, part, ldx, neta, direct);      \
+                       (int64_t)col0, nc, cpp, (float)ctx->dV, part, ldx, neta, direct);        \
     break;
-  switch (mt) {
-    SGW_F(1) SGW_F(2) SGW_F(3) SGW_F(4)
-    default: throw Error{SGW_EUNSUPPORTED, "features: K must be in 1..64"};
-  }
+    switch (mt) {
+      SGW_F(1) SGW_F(2) SGW_F(3) SGW_F(4)
+      default: throw Error{SGW_EUNSUPPORTED, "features: K must be in 1..64"};
+    }
 #undef SGW_F
-  SGW_HIP(hipGetLastError());
-  if (direct) return;
-  hipLaunchKernelGGL(k_feature_sums, dim3((unsigned)((nsamp * K + NT - 1) / NT)), dim3(NT), 0,
-                     ctx->stream, part, nsamp, std::max(1, neta), (int)np, kp, K, (float)ctx->dV,
-                     x, ldx);
-  SGW_HIP(hipGetLastError());
+    SGW_HIP(hipGetLastError());
+    if (direct) return;
+    hipLaunchKernelGGL(k_feature_sums, dim3((unsigned)((ns * K + NT - 1) / NT)), dim3(NT), 0,
+                       ctx->stream, part, ns, std::max(1, neta), (int)np, kp, K, (float)ctx->dV,
+                       x + i * ldx, ldx);
+    SGW_HIP(hipGetLastError());
+  }
 }
 
 // ---------------------------------------------------------------- MLP GEMM

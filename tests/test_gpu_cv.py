@@ -185,6 +185,27 @@ def test_features_eta_match_oracle(which, K, first, nsamp, neta, request):
     assert np.max(np.abs(got - model)) < 1e-4 * np.max(model)
 
 
+def test_features_eta_scratch_is_bounded():
+    """2^24 eta-bar vectors of one state take 256 MiB of partial sums, not a row
+    of 16 floats for each of them, and slicing the samples changes no bit."""
+    s = systems.gaussian_wells(seed=2, n=16, h=0.5)
+    ctx = sgw.Context(s.grid.n, s.grid.h, s.v_loc, None, precision=sgw.SGW_C64, max_nvec=4)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    phi = torch.randn((1, s.grid.N), generator=g, device="cuda")
+    x = torch.empty((1 << 18, 1), device="cuda")
+    half = torch.empty((1 << 17, 1), device="cuda")
+    sgw.cv_features_eta(ctx, phi, 3, 0, 64, 64, x)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    sgw.cv_features_eta(ctx, phi, 3, 0, 1 << 18, 64, x)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 300 << 20
+    sgw.cv_features_eta(ctx, phi, 3, 1 << 17, 1 << 17, 64, half)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert torch.isfinite(x).all() and torch.equal(x[1 << 17:], half)
+
+
 # ------------------------------------------------------------------ network
 @pytest.fixture(scope="module")
 def net_case():
