@@ -808,10 +808,16 @@ sgw_status sgw_lanczos_bounds(sgw_ctx *ctx, int32_t k, uint64_t seed, double pad
     DevBuf &dk = ctx->buf("lz_key", sizeof(uint64_t));
     SGW_HIP(hipMemcpyAsync(dk.p, &key, sizeof key, hipMemcpyHostToDevice, ctx->stream));
     launch_fill_noise(ctx, dk.as<uint64_t>(), 1, u);
+    // powers of two: the noise near one, and s near |H| (see the kernels)
+    launch_scale_copy(ctx, u, N, u, N, 1, std::exp2(std::round(0.5 * std::log2(ctx->dV))), 0.0);
+    double lo_w = 0, hi_w = 0;
+    weyl_bounds(ctx, 0.0, lo_w, hi_w);
+    const double h_max = std::max(std::fabs(lo_w), std::fabs(hi_w));
+    const double s = h_max > 0 ? std::exp2(std::round(std::log2(h_max))) : 1.0;
     launch_lanczos_start(ctx, u, unorm);
     for (int j = 0; j < k; ++j) {
       apply_h(ctx, u, w, 1, N);
-      launch_lanczos_step(ctx, u, up, w, coef + j, coef + k + j, j == 0, dots, unorm, norms);
+      launch_lanczos_step(ctx, u, up, w, 1.0 / s, coef + j, coef + k + j, j == 0, dots, unorm, norms);
       std::swap(unorm, norms);
       std::swap(u, up);                   // the vector before
       std::swap(u, w);                    // the new one; the oldest takes the next product
@@ -823,7 +829,7 @@ sgw_status sgw_lanczos_bounds(sgw_ctx *ctx, int32_t k, uint64_t seed, double pad
     SGW_HIP(hipStreamSynchronize(ctx->stream));
     std::vector<double> alpha, beta;
     for (int j = 0; j < k; ++j) {
-      const double a = c[j], b = c[k + 1 + j];
+      const double a = c[j], b = s * c[k + 1 + j];
       SGW_REQUIRE(std::isfinite(a) && std::isfinite(b), SGW_EDIVERGED, "Lanczos produced a non-finite value");
       alpha.push_back(a);
       beta.push_back(b);
@@ -834,8 +840,6 @@ sgw_status sgw_lanczos_bounds(sgw_ctx *ctx, int32_t k, uint64_t seed, double pad
     tridiagonal_extremes(alpha, beta, th0, th1, y0, y1);
     const double r0 = beta[n - 1] * std::fabs(y0), r1 = beta[n - 1] * std::fabs(y1);
     const double width = th1 - th0;
-    double lo_w = 0, hi_w = 0;
-    weyl_bounds(ctx, 0.0, lo_w, hi_w);
     *emin = std::max(lo_w, th0 - r0 - pad * width);
     *emax = std::min(hi_w, th1 + r1 + pad * width);
   });

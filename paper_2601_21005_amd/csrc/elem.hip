@@ -246,9 +246,11 @@ void launch_redot(sgw_ctx *ctx, const void *a, const void *b, int64_t ld, int64_
 }
 
 // ============================================================ Lanczos
-// The Lanczos vectors are kept unnormalised: u_j = b_j v_j with b_j = |u_j|,
-//   a_j = <u_j|H u_j> / b_j^2,
-//   u_{j+1} = (H u_j - a_j u_j) / b_j - (b_j / b_{j-1}) u_{j-1},
+// The Lanczos vectors are kept unnormalised: u_j = c_j v_j with c_j = |u_j|,
+//   a_j = <u_j|H u_j> / c_j^2,
+//   u_{j+1} = (H u_j - a_j u_j) / (c_j s) - (c_j / c_{j-1}) u_{j-1},
+// and b_j = c_j s: s, a power of two near |H|, keeps their size near one
+// whatever the unit of H, and as a power of two changes no bit,
 // so a step is two launches beside those of H (the dot products, then the new
 // vector with its norm), its scalars stay on the device and the host waits
 // once at the end.  Both are bound by latency (2 MB a vector at 64^3): every
@@ -309,12 +311,13 @@ __global__ __launch_bounds__(NT) void k_lanczos_dot(const cplx<R> *a, const cplx
 // w = H u becomes the next vector; norms[block] = |w|^2 of the block's points.
 // dots, unorm: partial sums of <u|w> and |u|^2.  beta[j] = |u| is written,
 // beta[j - 1] is the one before (up = u_{j-1}, not read on the first step).
+// inv_s: 1 / s.
 template <typename R>
 __global__ __launch_bounds__(NT) void k_lanczos_update(const cplx<R> *u, const cplx<R> *up,
                                                        cplx<R> *w, int64_t N, int chunk,
                                                        const double *dots, const double *unorm,
-                                                       int nblk, double *alpha, double *beta,
-                                                       int first, double *norms) {
+                                                       int nblk, double inv_s, double *alpha,
+                                                       double *beta, int first, double *norms) {
   __shared__ double sh[NT / 64], tot[2];
   const int wave = threadIdx.x / 64;
   if (wave < 2) {
@@ -328,7 +331,7 @@ __global__ __launch_bounds__(NT) void k_lanczos_update(const cplx<R> *u, const c
   const double b2 = tot[1], b = sqrt(b2), ib = b > 0 ? 1.0 / b : 0.0;
   const double a = b > 0 ? tot[0] / b2 : 0.0;
   const double bp = first ? 0.0 : beta[-1];
-  const R ca = (R)-a, ci = (R)ib, cb = (R)(bp > 0 ? -b / bp : 0.0);
+  const R ca = (R)-a, ci = (R)(ib * inv_s), cb = (R)(bp > 0 ? -b / bp : 0.0);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *alpha = a;
     *beta = b;
@@ -372,15 +375,15 @@ static void lanczos_dot_t(sgw_ctx *ctx, const void *a, const void *b, double *ou
 }
 
 template <typename R>
-static void lanczos_step_t(sgw_ctx *ctx, const void *u, const void *up, void *w, double *alpha,
-                           double *beta, bool first, double *dots, const double *unorm,
-                           double *norms) {
+static void lanczos_step_t(sgw_ctx *ctx, const void *u, const void *up, void *w, double inv_s,
+                           double *alpha, double *beta, bool first, double *dots,
+                           const double *unorm, double *norms) {
   const int nblk = lanczos_blocks(ctx);
   lanczos_dot_t<R>(ctx, u, w, dots);
   hipLaunchKernelGGL(k_lanczos_update<R>, dim3(nblk), dim3(NT), 0, ctx->stream,
                      static_cast<const cplx<R> *>(u), static_cast<const cplx<R> *>(up),
                      static_cast<cplx<R> *>(w), ctx->N, lanczos_chunk(ctx), dots, unorm, nblk,
-                     alpha, beta, first ? 1 : 0, norms);
+                     inv_s, alpha, beta, first ? 1 : 0, norms);
 }
 
 void launch_lanczos_start(sgw_ctx *ctx, const void *u, double *norms) {
@@ -389,13 +392,13 @@ void launch_lanczos_start(sgw_ctx *ctx, const void *u, double *norms) {
   SGW_HIP(hipGetLastError());
 }
 
-void launch_lanczos_step(sgw_ctx *ctx, const void *u, const void *up, void *w, double *alpha,
-                         double *beta, bool first, double *dots, const double *unorm,
-                         double *norms) {
+void launch_lanczos_step(sgw_ctx *ctx, const void *u, const void *up, void *w, double inv_s,
+                         double *alpha, double *beta, bool first, double *dots,
+                         const double *unorm, double *norms) {
   if (ctx->dbl)
-    lanczos_step_t<double>(ctx, u, up, w, alpha, beta, first, dots, unorm, norms);
+    lanczos_step_t<double>(ctx, u, up, w, inv_s, alpha, beta, first, dots, unorm, norms);
   else
-    lanczos_step_t<float>(ctx, u, up, w, alpha, beta, first, dots, unorm, norms);
+    lanczos_step_t<float>(ctx, u, up, w, inv_s, alpha, beta, first, dots, unorm, norms);
   SGW_HIP(hipGetLastError());
 }
 

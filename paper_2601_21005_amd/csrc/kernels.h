@@ -46,10 +46,10 @@ int lanczos_blocks(const sgw_ctx *ctx);
 // norms = |u|^2
 void launch_lanczos_start(sgw_ctx *ctx, const void *u, double *norms);
 // with w = H u and unorm = |u|^2: *alpha = <u|w> / |u|^2, *beta = |u|, w = (w -
-// alpha u) / beta[0] - beta[0] / beta[-1] up (first: without up), norms = |w|^2
-void launch_lanczos_step(sgw_ctx *ctx, const void *u, const void *up, void *w, double *alpha,
-                         double *beta, bool first, double *dots, const double *unorm,
-                         double *norms);
+// alpha u) inv_s / beta[0] - beta[0] / beta[-1] up (first: without up), norms = |w|^2
+void launch_lanczos_step(sgw_ctx *ctx, const void *u, const void *up, void *w, double inv_s,
+                         double *alpha, double *beta, bool first, double *dots,
+                         const double *unorm, double *norms);
 // *beta = sqrt(sum of norms)
 void launch_lanczos_end(sgw_ctx *ctx, const double *norms, double *beta);
 

@@ -310,6 +310,22 @@ def test_lanczos_vector_rotation_and_block_edges(n, steps, prec):
     assert abs(lo - lo_o) < tol and abs(hi - hi_o) < tol
 
 
+@pytest.mark.parametrize("e", [1e22, 1e30, 1e-24])
+def test_lanczos_bounds_in_any_unit_of_energy(e):
+    """H scaled by e (h by 1 / sqrt(e), V by e): the FP32 interval is e times
+    the unscaled one to FP32 rounding, far from the ends of the range that the
+    vectors or their products could reach."""
+    rs = np.random.default_rng(8)
+    v = -4.0 * rs.random(16 ** 3)
+    out = []
+    for f in (1.0, e):
+        ctx = sgw.Context(16, 0.6 / np.sqrt(f), f * v, None, precision=sgw.SGW_C64, max_nvec=1)
+        out.append(np.array(ctx.lanczos_bounds(12, seed=2, pad=0.01)) / f)
+        ctx.close()
+    width = out[0][1] - out[0][0]
+    assert np.all(np.abs(out[1] - out[0]) < 1e-5 * width), out
+
+
 def test_lanczos_bounds_si35h36_fp32(si35):
     """On the 64^3 cluster in complex FP32 the Lanczos interval encloses the
     extreme eigenvalues that the oracle's ARPACK eigensolvers give
