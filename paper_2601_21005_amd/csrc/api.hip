@@ -170,15 +170,16 @@ void join_gather(sgw_ctx *ctx) {
 }
 
 // whether the projector gathers of a batch of nvec vectors go beside the FFT
-// passes (on the context's stream, with projectors, for batches that fill
-// more than a sliver of the device); creates the second stream on first use.
-// The two events of a term cost about 10 us: with fewer than some 320 gather
-// workgroups the term is too short for them (24^3 in complex FP32, 32 vectors,
-// 26 terms: 1084 us with them, 953 without; 40^3 split BF16, 24 vectors, 360
-// workgroups: 1439 and 1466)
+// passes: on the context's stream, with projectors that the passes do not carry
+// themselves, for batches that fill more than a sliver of the device; creates
+// the second stream on first use.  The two events of a term cost about 10 us,
+// so the line follows the gather's workgroups.  Time of 26 terms in line over
+// that beside, 24^3 to 80^3, 5 to 47 Si, 16 to 64 vectors: 0.72 to 1.00 up to
+// 256 workgroups (once 1.07, FP64 at 40^3 and 240); from 360 on 1.01 to 1.12 in
+// FP64, 0.99 to 1.06 in the others, 1.03 on average.
 bool gather_beside(sgw_ctx *ctx, int64_t nvec) {
   const bool ovl = ctx->has_kb && ctx->kb_overlap && ctx->ns.empty() && nvec >= 16 &&
-                   kb_gather_blocks(ctx, nvec) >= 320;
+                   kb_gather_blocks(ctx, nvec) >= 320 && !kb_rides(ctx, nvec, ctx->N);
   if (ovl) ctx->make_aux();
   return ovl;
 }
@@ -203,7 +204,6 @@ void cheb_term(sgw_ctx *ctx, void *cur, void *old, void *acc, void *tmp, void *k
   // ovl on the second stream beside them (all only read v_n; the scatter waits)
   const bool ride = kb_rides(ctx, nvec, N);
   const KbRide kb{cur, N, kbC};
-  ovl = ovl && !ride;
   if (ctx->has_kb && ovl) fork_gather(ctx, cur, nvec, N, kbC);
   else if (ctx->has_kb && !ride) kb_gather_e(ctx, cur, nvec, N, kbC);
   EpiArgs e;
