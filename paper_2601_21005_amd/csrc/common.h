@@ -275,7 +275,7 @@ enum PlaneMode : int {
   PLANE_INV_SPLIT = 5,    // r0 = Re, r1 = Im  (real fields)
 };
 
-enum MulMode : int { MUL_NONE = 0, MUL_KIN = 1, MUL_PROP = 2, MUL_COUL = 3 };
+enum MulMode : int { MUL_KIN = 1, MUL_PROP = 2, MUL_COUL = 3 };
 
 struct EpiArgs {
   const void *x = nullptr;    // complex: current vector (HPSI, CHEB)

@@ -116,8 +116,10 @@ __device__ __forceinline__ void epilogue(const PassArgs &a, int64_t v, int64_t r
 // (5.7 TB/s) where x lines and y pencils took 272 + 265, 96^2 283 from 303 +
 // 265, 80^2 286 from 372, FP64 64^2 301 from 282 + 270, FP64 128^2 321 from
 // 267 + 250; 32^2 to 64^2 as before (282 us).  The planes that would not fit
-// (FP64 160^2) or that spill registers (FP32 160^2, FP64 112^2: 391 and 401 us
-// against 304 + 263 and 297 + 255) keep the two passes.
+// (FP64 160^2) or that spill registers in every pass (FP32 160^2, FP64 112^2:
+// 391 and 401 us against 304 + 263 and 297 + 255) keep the two passes; of those
+// used, FP32 112^2 with the H psi epilogue spills four registers and FP64 128^2
+// with the Chebyshev epilogue six.
 template <typename R, int N, int MODE = PLANE_FWD> struct PlaneShape {
   static constexpr bool D = sizeof(R) == 8;
   static constexpr int T = N == 128 ? 1024 : N == 112 ? 448 : N == 96 ? 768 : N == 80 ? 448
@@ -129,7 +131,6 @@ template <typename R, int N, int MODE = PLANE_FWD> struct PlaneShape {
   // odd pitch: lanes on successive lines fall on distinct banks; at 128 and
   // 64 also wide enough that the runs of R1 points of neighbouring lines do
   static constexpr int P = N == 128 ? 145 : N == 64 ? 73 : N + 1;
-  static constexpr bool SPLIT = true;
   // FP32 inverse transforms of 96 and more take y before x, at one exchange
   // more: the order in which x lines and y pencils round.  The TDH's response
   // field, a small difference of orbitals, amplifies another rounding to some
@@ -137,11 +138,11 @@ template <typename R, int N, int MODE = PLANE_FWD> struct PlaneShape {
   // are (x before y: H psi on 24 vectors of 96^3 300 us against 304, 112^3 498
   // against 506, 128^3 669 against 672, as accurate)
   static constexpr bool YFIRST = !D && N >= 96;
-  static constexpr size_t lds = (size_t)N * P * sizeof(R) * (SPLIT ? 1 : 2) + N * sizeof(cplx<R>);
+  static constexpr size_t lds = (size_t)N * P * sizeof(R) + N * sizeof(cplx<R>);
   static constexpr bool fits = lds <= 160 * 1024 && !(D && N == 112) && !(!D && N == 160);
 };
 
-// plane z of vector v; s: N P values (twice as many unless SPLIT), tw: N
+// plane z of vector v; s: N P values, tw: N
 template <typename R, int N, int MODE>
 __device__ __forceinline__ void plane_pass(const PassArgs &a, int z, int64_t v, R *s,
                                            cplx<R> *tw) {
@@ -173,30 +174,29 @@ __device__ __forceinline__ void plane_pass(const PassArgs &a, int z, int64_t v, 
   auto y1o = [](int b, int i) { return ((b / N) * R1 + i) * P + b % N; };
   auto y2 = [](int b, int i) { return (b / N + i * R1) * P + b % N; };
   auto j_of = [](int b) { return b / N; };
-  constexpr bool SP = Sh::SPLIT;
   s1.template run<N, 1>(tid, tw, j_of);
   if constexpr (YF) {
-    exchange<SP, C>(s, tid, s1, s2, true, y1o, y2);
+    exchange<true, C>(s, tid, s1, s2, true, y1o, y2);
     s2.template run<N, R1>(tid, tw, j_of);
-    exchange<SP, C>(s, tid, s2, s1, true, y2, x1);
+    exchange<true, C>(s, tid, s2, s1, true, y2, x1);
     s1.template run<N, 1>(tid, tw, j_of);
-    exchange<SP, C>(s, tid, s1, s2, true, x1o, x2);
+    exchange<true, C>(s, tid, s1, s2, true, x1o, x2);
     s2.template run<N, R1>(tid, tw, j_of);
-    exchange<SP, C>(s, tid, s2, s2, false, x2, y2);   // rows again, for whole cache lines
+    exchange<true, C>(s, tid, s2, s2, false, x2, y2);   // rows again, for whole cache lines
   } else {
-    exchange<SP, C>(s, tid, s1, s2, true, x1l, x2);
+    exchange<true, C>(s, tid, s1, s2, true, x1l, x2);
     s2.template run<N, R1>(tid, tw, j_of);
-    exchange<SP, C>(s, tid, s2, s1, true, x2, y1);
+    exchange<true, C>(s, tid, s2, s1, true, x2, y1);
     s1.template run<N, 1>(tid, tw, j_of);
-    exchange<SP, C>(s, tid, s1, s2, false, y1o, y2);
+    exchange<true, C>(s, tid, s1, s2, false, y1o, y2);
     s2.template run<N, R1>(tid, tw, j_of);
   }
   constexpr int STEP = R1 * N;           // butterfly b's output i is at point b + i STEP
   if (INV) s2.map(tid, [](C z, int, int) { return cconj(z); });
   // epilogue operands are loaded CH points at a time before their stores (the
-  // stores would otherwise order every later load)
-  // (10 at once hold 132 registers: 80^2 filter terms of 24 vectors 255 us
-  // against 240 with 5, and 250 with the points in LDS)
+  // stores would otherwise order every later load); 10 at once hold 132
+  // registers (80^2 filter terms of 24 vectors 255 us against 240 with 5, and
+  // 250 with the points in LDS)
   constexpr int CH = R2 % 4 == 0 ? 4 : R2 % 5 == 0 ? 5 : R2;
   if constexpr (MODE == PLANE_INV_CHEB) {
     const C *xp = static_cast<const C *>(a.e.x) + v * a.ld_x + plane;
@@ -296,7 +296,7 @@ __device__ __forceinline__ int64_t vec_of(const PassArgs &a, int i, int nvec) {
 template <typename R, int N, int MODE>
 __global__ __launch_bounds__((PlaneShape<R, N>::T), (PlaneShape<R, N, MODE>::WPE)) void k_plane(PassArgs a) {
   using Sh = PlaneShape<R, N, MODE>;
-  __shared__ R s[N * Sh::P * (Sh::SPLIT ? 1 : 2)];
+  __shared__ R s[N * Sh::P];
   __shared__ cplx<R> tw[N];
   plane_pass<R, N, MODE>(a, blockIdx.x, vec_of(a, blockIdx.y, gridDim.y), s, tw);
 }
@@ -548,7 +548,6 @@ __global__ __launch_bounds__((PencilShape<float, N, TX>::T)) void k_pencil_reduc
 
 // ----------------------------------------------------------------- dispatch
 template <int N> constexpr int pencil_tx() { return N % 16 == 0 ? 16 : N % 8 == 0 ? 8 : 4; }
-// wider pencils (rows of 32 complex) where the length allows them
 // wider pencils where the length allows them (nx a multiple of the width)
 template <typename R, int N> constexpr int pencil_tx_wide() {
   constexpr bool D = sizeof(R) == 8;

@@ -592,8 +592,8 @@ void jacobi_eigen(int n, std::vector<double> &a, std::vector<double> &vals,
 
 // The k-th lowest eigenvalue (k from 0) by bisection on the number of
 // negative pivots of T - x (Sylvester's law of inertia), down to neighbouring
-// doubles; then the last component of its unit eigenvector by two steps of
-// inverse iteration (elimination with row exchanges).  O(n) a step: cyclic
+// doubles; then the last component of its unit eigenvector by three steps
+// of inverse iteration (elimination with row exchanges).  O(n) a step: cyclic
 // Jacobi rotations for all eigenpairs take O(n^3), 3 ms at n = 60.
 static double tridiagonal_value(const std::vector<double> &a, const std::vector<double> &b, int k) {
   const int n = (int)a.size();
