@@ -199,15 +199,17 @@ sgw_status sgw_gapped_coefficients(double e_homo, double e_lumo, double eps, dou
  * k < nvec, by the three-term recurrence.  The filter is real, so complex
  * vectors may carry two real orbitals each (real and imaginary parts).
  * coef: host [ncoef].  [emin, emax] must enclose spec(H); a recurrence that
- * grows anyway returns SGW_EDIVERGED (v is then undefined).  With projectors
- * and batches of 16 vectors or more, each term's projections of v_n are
- * computed on a second stream of the context beside the term's FFT passes
- * (they only read v_n), and the stream
- * of the context waits for them before the projector update; the call thus
- * orders itself on the context's stream as before, and its results are
- * bitwise those of one stream, which SGW_KB_OVERLAP=0 at sgw_create selects
- * (the same holds for sgw_cheb_propagate and the filter of
- * sgw_sigma_estimate). */
+ * grows anyway returns SGW_EDIVERGED (v is then undefined).  With projectors,
+ * where a term's projections of v_n are computed depends on the batch: in small
+ * ones (fewer than 1024 gather workgroups, about one per touched 512-point tile
+ * and 8 vectors) complex FP32 takes them along in the FFT passes of 32, 40, 56,
+ * 64, 80 and 96 points; from 320 workgroups and 16 vectors on, the others
+ * compute them on a second stream of the context beside the FFT passes (both
+ * only read v_n; the context's stream waits for them before the projector
+ * update); the rest in line.  The call orders itself on the context's stream
+ * and its results are bitwise the same in every case (SGW_KB_OVERLAP=0 at
+ * sgw_create keeps one stream; the same holds for sgw_cheb_propagate and the
+ * filter of sgw_sigma_estimate). */
 sgw_status sgw_fermi_filter(sgw_ctx *ctx, void *v, int64_t nvec, int64_t ld,
                             const double *coef, int32_t ncoef, double emin,
                             double emax);
