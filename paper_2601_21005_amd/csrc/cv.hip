@@ -363,6 +363,7 @@ template <int BM_, int BN_, int BK_, int THREADS_, int NBUF_> struct Tile {
   static int count(int M, int N) { return ((N + BN - 1) / BN) * ((M + BM - 1) / BM); }
 };
 using WideTile = Tile<64, 32, 64, 256, 2>;
+using ShortTile = Tile<64, 64, 32, 256, 2>;
 using DeepTile = Tile<32, 32, 256, 1024, 1>;
 constexpr int DEEP = DeepTile::THREADS;
 
@@ -533,39 +534,54 @@ template <int EPI, int STD> void gemm(hipStream_t st, const GemmArgs &a) {
   const GemmArgs g = finish_args(a);
   // deep tiles where their chunks of 256 are filled and the launch is at most
   // four workgroups per CU (256 x 256 layer, 1536 samples: 7.8 against 9.4 us;
-  // 64 inputs: 14.2 against 7.8, so wide; beyond, wide tiles read less)
+  // 64 inputs: 14.2 against 7.8, so wide; beyond, wide tiles read less); short
+  // tiles where half of a wide tile's chunk would be empty and one workgroup
+  // per CU is left (400000 samples through 32-32-32: forward 255 -> 109 us)
   if (g.K > 128 && DeepTile::count(g.M, g.N) <= 1024) launch_gemm<DeepTile, EPI, STD>(st, g);
+  else if (g.K <= 32 && ShortTile::count(g.M, g.N) >= 256) launch_gemm<ShortTile, EPI, STD>(st, g);
   else launch_gemm<WideTile, EPI, STD>(st, g);
 }
 
 // ---------------------------------------------------------------- output layer
 // g = w3 . a2 + b3 (FP32, in order of j) and, in training, the residual's
 // dg = 2 (g - y) / n, its square (FP64) and the layer's d2[j] = dg w3[j]
-// (1 - a2[j]^2).  16 samples per workgroup: their a2 rows are read coalesced
-// into LDS, one thread per sample adds its row (a chain of h2 FMAs, 1 us at
-// 256; one thread per sample straight from memory took 33 us at 1536 samples).
-constexpr int OUT_S = 16, OUT_J = 256;
+// (1 - a2[j]^2).  S samples per workgroup: their a2 rows are read coalesced
+// into LDS, J columns at a time, one thread per sample adds its row (a chain
+// of h2 FMAs, 1 us at 256; one thread per sample straight from memory took 33
+// us at 1536 samples).  16 samples and 256 columns; 64 and 64 where a row is
+// no longer than a wave and the samples fill the chip all the same, or most
+// threads would have no column (forward pass of 40000 samples through 9-16-24
+// 36.7 us, 22.4 with these and the short GEMM tile; 500 samples 18.7 and 19.7).
+template <int S_, int J_> struct OutTile {
+  static constexpr int S = S_, J = J_, R = NT / J;   // R rows at a time
+};
+using OutWide = OutTile<16, 256>;
+using OutNarrow = OutTile<64, 64>;
 
-template <bool TRAIN>
+template <class T, bool TRAIN>
 __global__ __launch_bounds__(NT) void k_output(const float *a2, const float *w3, const float *b3,
                                                int h2, int64_t n, float *g, const float *y,
                                                float *dg, double *e2, float *d2) {
-  __shared__ float sh[OUT_S * (OUT_J + 1)], sw[OUT_J], sd[OUT_S];
-  const int64_t s0 = (int64_t)blockIdx.x * OUT_S;
-  const int tid = threadIdx.x, ns = (int)min((int64_t)OUT_S, n - s0);
+  constexpr int S = T::S, J = T::J, R = T::R;
+  __shared__ float sh[S * (J + 1)], sw[J], sd[S];
+  const int64_t s0 = (int64_t)blockIdx.x * S;
+  const int tid = threadIdx.x, ns = (int)min((int64_t)S, n - s0);
+  const int col = R == 1 ? tid : tid % J, row = R == 1 ? 0 : tid / J;
   float acc = 0.f;
-  for (int j0 = 0; j0 < h2; j0 += OUT_J) {
-    const int nj = min(OUT_J, h2 - j0);
-    if (tid < nj) {
-      sw[tid] = w3[j0 + tid];
+  for (int j0 = 0; j0 < h2; j0 += J) {
+    const int nj = min(J, h2 - j0);
+    if (col < nj) {
+      if (row == 0) sw[col] = w3[j0 + col];
 #pragma unroll
-      for (int i = 0; i < OUT_S; ++i)
-        if (i < ns) sh[i * (OUT_J + 1) + tid] = a2[(s0 + i) * h2 + j0 + tid];
+      for (int k = 0; k < S / R; ++k) {
+        const int i = row + R * k;
+        if (i < ns) sh[i * (J + 1) + col] = a2[(s0 + i) * h2 + j0 + col];
+      }
     }
     __syncthreads();
     if (tid < ns) {
 #pragma unroll 16
-      for (int j = 0; j < nj; ++j) acc += sw[j] * sh[tid * (OUT_J + 1) + j];
+      for (int j = 0; j < nj; ++j) acc += sw[j] * sh[tid * (J + 1) + j];
     }
     __syncthreads();
   }
@@ -580,10 +596,11 @@ __global__ __launch_bounds__(NT) void k_output(const float *a2, const float *w3,
   }
   if constexpr (TRAIN) {
     __syncthreads();
-    for (int j = tid; j < h2; j += NT) {
+    for (int j = col; j < h2; j += J) {
       const float w = w3[j];
 #pragma unroll
-      for (int i = 0; i < OUT_S; ++i) {
+      for (int k = 0; k < S / R; ++k) {
+        const int i = row + R * k;
         if (i < ns) {
           const float h = a2[(s0 + i) * h2 + j];
           d2[(s0 + i) * h2 + j] = sd[i] * w * (1.f - h * h);
@@ -591,6 +608,19 @@ __global__ __launch_bounds__(NT) void k_output(const float *a2, const float *w3,
       }
     }
   }
+}
+
+template <bool TRAIN>
+void launch_output(hipStream_t st, const float *a2, const float *w3, const float *b3, int h2,
+                   int64_t n, float *g, const float *y, float *dg, double *e2, float *d2) {
+  auto go = [&](auto t) {
+    using T = decltype(t);
+    hipLaunchKernelGGL((k_output<T, TRAIN>), dim3((unsigned)((n + T::S - 1) / T::S)), dim3(NT), 0,
+                       st, a2, w3, b3, h2, n, g, y, dg, e2, d2);
+  };
+  if (h2 <= OutNarrow::J && n >= 256 * OutNarrow::S) go(OutNarrow{});
+  else go(OutWide{});
+  SGW_HIP(hipGetLastError());
 }
 
 // ---------------------------------------------------------------- weight gradients
@@ -790,16 +820,12 @@ void hidden(sgw_mlp *M, const float *x, int64_t n, const Acts &a) {
   gemm<EPI_TANH_BIAS, BSTD_NONE>(st, g);
 }
 
-unsigned output_blocks(int64_t n) { return (unsigned)((n + OUT_S - 1) / OUT_S); }
-
 // out = network(x) for n samples (x [n][din]); activations kept in `a`
 void forward(sgw_mlp *M, const float *x, int64_t n, const Acts &a, float *out) {
   const float *th = M->theta.as<float>();
   hidden(M, x, n, a);
-  hipLaunchKernelGGL(k_output<false>, dim3(output_blocks(n)), dim3(NT), 0, M->stream, a.a2,
-                     th + M->ow3(), th + M->ob3(), M->h2, n, out, nullptr, nullptr, nullptr,
-                     nullptr);
-  SGW_HIP(hipGetLastError());
+  launch_output<false>(M->stream, a.a2, th + M->ow3(), th + M->ob3(), M->h2, n, out, nullptr,
+                       nullptr, nullptr, nullptr);
 }
 
 AdamArgs adam_args(sgw_mlp *M, double lr, double b1, double b2, double eps) {
@@ -825,9 +851,7 @@ void gradient(sgw_mlp *M, const float *x, const float *y, int64_t n, const Acts 
   float *d2 = M->buf("d2", sizeof(float) * n * M->h2).as<float>();
   float *d1 = M->buf("d1", sizeof(float) * n * M->h1).as<float>();
   hidden(M, x, n, a);
-  hipLaunchKernelGGL(k_output<true>, dim3(output_blocks(n)), dim3(NT), 0, st, a.a2,
-                     th + M->ow3(), th + M->ob3(), M->h2, n, a.g, y, dg, e2, d2);
-  SGW_HIP(hipGetLastError());
+  launch_output<true>(st, a.a2, th + M->ow3(), th + M->ob3(), M->h2, n, a.g, y, dg, e2, d2);
   // d1[s][k] = (sum_j W2[j][k] d2[s][j]) (1 - a1[s][k]^2)
   GemmArgs g{};
   g.a = th + M->oW2(); g.sam = 1; g.sak = M->h1;

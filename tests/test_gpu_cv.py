@@ -296,6 +296,33 @@ def test_gradient_at_tile_and_range_edges(din, h1, h2, n):
         assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(b), k
 
 
+@pytest.mark.parametrize("din,h1,h2", [(9, 16, 24), (1, 3, 1), (32, 33, 64), (33, 32, 65)])
+def test_many_samples_of_a_small_network(din, h1, h2):
+    """16390 samples of layers up to a wave wide (64 x 64 GEMM tiles with chunks
+    of 32, 64 samples per output workgroup; the last case is past both): the
+    forward pass is bitwise that of parts of 500 samples, which take the other
+    tiles, and loss and gradient are held to the rounding model as above."""
+    rs = np.random.default_rng(din)
+    n = 16390
+    theta = systems.mlp_init(6, din, h1, h2)
+    theta = (theta + 0.05 * rs.standard_normal(theta.size)).astype(np.float32).astype(np.float64)
+    x = rs.gamma(1.0, 1.0, size=(n, din)).astype(np.float32)
+    y = (1.0 + rs.standard_normal(n)).astype(np.float32)
+    m = sgw.Mlp(theta, din, h1, h2)
+    xd = f32(x)
+    g = m.forward(xd)
+    parts = torch.cat([m.forward(xd[i:i + 500].contiguous()) for i in range(0, n, 500)])
+    L, gr = m.gradient(xd, f32(y))
+    m.close()
+    assert torch.equal(g, parts)
+    gm, _, _ = model_forward(theta, x.astype(np.float64), din, h1, h2)
+    Lm = np.mean((gm - y) ** 2)
+    assert abs(L - Lm) <= 2.0 ** -7 * Lm
+    mod = model_gradient(theta, x.astype(np.float64), y.astype(np.float64), din, h1, h2)
+    for k, (a, b) in enumerate(zip(blocks(gr, din, h1, h2), blocks(mod, din, h1, h2))):
+        assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(b), k
+
+
 def test_adam_steps_match_oracle(net_case):
     """Given gradients (host FP64 inputs), three Adam steps in FP32 against
     the oracle's FP64 Adam: relative 1e-6 of the parameters' scale."""
