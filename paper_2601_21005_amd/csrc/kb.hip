@@ -570,7 +570,8 @@ static KbReduce<R> reduce_args(const sgw_ctx *ctx, const void *partial, int64_t 
   a.ekb = ctx->d_kb_ekb.as<double>();
   a.use_e = use_e ? 1 : 0;
   a.nvec = nvec;
-  a.lv = nvec > 32 ? KB_LV_MANY : KB_LV_FEW;   // rows of 64 vectors are read in whole lines
+  a.lv = 3;
+  while (a.lv < 6 && (int64_t(1) << a.lv) < nvec) ++a.lv;
   a.out = static_cast<cplx<R> *>(out);
   a.gx = (int)((nvec + (1 << a.lv) - 1) >> a.lv);
   a.nproj = ctx->kb.nproj;

@@ -30,15 +30,13 @@ template <typename T> struct KbGather {
   const uint32_t *tile_mask;
   int gx, gy;
 };
-// vectors of a reduction workgroup (log2): rows of 16, or of 64 for wide batches
-constexpr int KB_LV_FEW = 4, KB_LV_MANY = 6;
 template <typename R> struct KbReduce {
   const cplx<R> *partial;
   const int *proj_off, *proj_entries;
   const double *ekb;
   int use_e;
   int64_t nvec;
-  int lv;
+  int lv;                                // 2^lv vectors a workgroup, 3 to 6
   cplx<R> *out;
   int gx, nproj;
 };
@@ -48,10 +46,11 @@ template <typename R> struct KbReduce {
 // in a tree: an order of the projector alone, so that a vector's result does
 // not depend on how many vectors share its launch.  A workgroup holds 2^LV
 // vectors of one projector; its threads of a vector share the slots.  Bound by
-// the latency of the entry list and the sums behind it: eight loads of a
-// thread are in flight (64^3, 260 vectors beside the FFT passes: 22 us, 26
-// with one thread's loads in a loop and an order that followed the batch).
-constexpr int KB_SLOTS = 16;
+// the latency of the entry list and the sums behind it: up to 16 loads of a
+// thread are in flight (80^3, 24 vectors beside the FFT passes: 9.8 us, 11.9
+// with a loop of loads and an order that followed the batch; with 16 slots one
+// or two vectors took 1 % longer in all).
+constexpr int KB_SLOTS = 32;
 
 template <int LV, typename R>
 __device__ __forceinline__ void reduce_slots(const KbReduce<R> &a, int bx, int p, double2 *sh) {
@@ -66,7 +65,7 @@ __device__ __forceinline__ void reduce_slots(const KbReduce<R> &a, int bx, int p
   if (v < a.nvec) {
     // IN rounds of the slots are requested before they are added, those past
     // the last entry (a zero then) at the last
-    constexpr int IN = 8 / SL;
+    constexpr int IN = SL < 4 ? 4 : 2;
     const int k1 = a.proj_off[p + 1];
     for (int k = a.proj_off[p] + part; k < k1; k += KB_SLOTS * IN) {
       cplx<R> c[IN][SL];
@@ -107,8 +106,12 @@ __device__ __forceinline__ void reduce_slots(const KbReduce<R> &a, int bx, int p
 
 template <typename R>
 __device__ __forceinline__ void reduce_projector(const KbReduce<R> &a, int bx, int p, double2 *sh) {
-  if (a.lv == KB_LV_FEW) reduce_slots<KB_LV_FEW>(a, bx, p, sh);
-  else reduce_slots<KB_LV_MANY>(a, bx, p, sh);
+  switch (a.lv) {
+    case 3: reduce_slots<3>(a, bx, p, sh); break;
+    case 4: reduce_slots<4>(a, bx, p, sh); break;
+    case 5: reduce_slots<5>(a, bx, p, sh); break;
+    default: reduce_slots<6>(a, bx, p, sh); break;
+  }
 }
 
 // ---------------------------------------------------------------- MFMA
