@@ -77,3 +77,34 @@ def test_riding_gather_changes_no_bit(n, pencil, monkeypatch):
         out.append(res)
     for a, b in zip(*out):
         assert torch.isfinite(torch.view_as_real(a)).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("ncoef", [6, 71])
+@pytest.mark.parametrize("n", [(32, 32, 32), (40, 40, 40), (80, 80, 96)])
+def test_riding_gather_in_replayed_graphs(n, ncoef):
+    """A short series (one graph) and a long one (pairs of terms) replayed three
+    times, with other work of the context between them, against eager runs."""
+    v, p = model(n)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        ctx = sgw.Context(n, H, v, p, precision=sgw.SGW_C64, ecut=28.0, max_nvec=4,
+                          stream=st.cuda_stream)
+        lo, hi = ctx.bounds(0.0)
+        g = torch.Generator(device="cuda").manual_seed(n[2])
+        coef = np.random.default_rng(ncoef).standard_normal(ncoef) / ncoef
+        xs = [torch.randn((4, ctx.N), dtype=torch.complex64, device="cuda", generator=g)
+              for _ in range(3)]
+        ref = [x.clone() for x in xs]
+        for r in ref:
+            ctx.fermi_filter(r, coef, lo, hi)
+        ctx.use_graphs(True)
+        w = torch.empty_like(xs[0])
+        for i in (0, 0, 1, 2):
+            w.copy_(xs[i])
+            ctx.fermi_filter(w, coef, lo, hi)
+            st.synchronize()
+            assert torch.equal(w, ref[i])
+            y = torch.empty_like(w)
+            ctx.apply_H(w, y)
+        st.synchronize()
+        ctx.close()
