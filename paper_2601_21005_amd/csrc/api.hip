@@ -808,8 +808,10 @@ sgw_status sgw_lanczos_bounds(sgw_ctx *ctx, int32_t k, uint64_t seed, double pad
     DevBuf &dk = ctx->buf("lz_key", sizeof(uint64_t));
     SGW_HIP(hipMemcpyAsync(dk.p, &key, sizeof key, hipMemcpyHostToDevice, ctx->stream));
     launch_fill_noise(ctx, dk.as<uint64_t>(), 1, u);
-    // powers of two: the noise near one, and s near |H| (see the kernels)
-    launch_scale_copy(ctx, u, N, u, N, 1, std::exp2(std::round(0.5 * std::log2(ctx->dV))), 0.0);
+    // powers of two: the noise near one where it is far from it, and s near |H|
+    // (see the kernels)
+    const double amp = std::round(0.5 * std::log2(ctx->dV));
+    if (std::fabs(amp) > 16) launch_scale_copy(ctx, u, N, u, N, 1, std::exp2(amp), 0.0);
     double lo_w = 0, hi_w = 0;
     weyl_bounds(ctx, 0.0, lo_w, hi_w);
     const double h_max = std::max(std::fabs(lo_w), std::fabs(hi_w));
